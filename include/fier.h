@@ -109,6 +109,11 @@ size_t fier_packed_meta_bytes(const fier_config *cfg);
 /* Scratch needed by fier_sparse_attn / fier_dense_attn / fier_decode_step for selections of at
  * most max_budget tokens per unit (fier_dense_attn: pass max_budget = max_ctx). */
 size_t fier_workspace_bytes(const fier_config *cfg, int32_t max_budget);
+/* The size from which fier_decode_step over n_layers layers runs them in as few launches as it can: a workspace of j
+ * times fier_workspace_bytes lets up to j layers share a launch (at most 16, fewer where the layers are large), as long
+ * as no two of them share an array they write.  Any size from fier_workspace_bytes on gives the same selections, and
+ * outputs that agree to the order of summation.  0 if invalid. */
+size_t fier_workspace_bytes_layers(const fier_config *cfg, int32_t max_budget, int32_t n_layers);
 /* For inspection: the byte offset inside such a workspace of the scores [units][max_ctx] float that the latest
  * fier_decode_step on it computed for its last layer (Alg. 1 step 2 as the fused step evaluates it).  0 if invalid. */
 size_t fier_workspace_scores_offset(const fier_config *cfg, int32_t max_budget);
@@ -192,7 +197,8 @@ int fier_dense_attn(const fier_config *cfg, const fier_cache *cache, const void 
  *   out      [n_layers][batch][n_q_heads][D] float device
  *   idx_out / count_out   optional (NULL): [n_layers][units][max_budget] / [n_layers][units], the
  *            selection of every layer, for inspection
- *   workspace  fier_workspace_bytes(cfg, max_budget) bytes, reused by every layer
+ *   workspace  at least fier_workspace_bytes(cfg, max_budget) bytes, reused by every layer; with more (see
+ *            fier_workspace_bytes_layers) several layers run side by side
  * seq_lens are not modified.  A sequence whose cache is full (seq_len >= max_ctx) is not appended
  * to: the step works on its max_ctx rows as if k_new were NULL for it.
  */

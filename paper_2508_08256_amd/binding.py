@@ -17,7 +17,8 @@ F16, BF16 = 0, 1
 OK = 0
 EINVAL, ESHAPE, EALIGN, EWORKSPACE, EUNSUPPORTED, EHIP = -1, -2, -3, -4, -5, -6
 
-SYMBOLS = ["fier_packed_bits_bytes", "fier_packed_meta_bytes", "fier_workspace_bytes", "fier_workspace_scores_offset",
+SYMBOLS = ["fier_packed_bits_bytes", "fier_packed_meta_bytes", "fier_workspace_bytes", "fier_workspace_bytes_layers",
+           "fier_workspace_scores_offset",
            "fier_status_string",
            "fier_check_config", "fier_quantize_keys", "fier_append_key", "fier_score", "fier_topk", "fier_topk_ws",
            "fier_sparse_attn", "fier_dense_attn", "fier_decode_step", "fier_decode_step_static", "fier_decode_step_mixed", "fier_decode_step_phase",
@@ -77,6 +78,8 @@ def lib():
         L.fier_packed_meta_bytes.argtypes = [cfgp]
         L.fier_workspace_bytes.restype = C.c_size_t
         L.fier_workspace_bytes.argtypes = [cfgp, i32]
+        L.fier_workspace_bytes_layers.restype = C.c_size_t
+        L.fier_workspace_bytes_layers.argtypes = [cfgp, i32, i32]
         L.fier_workspace_scores_offset.restype = C.c_size_t
         L.fier_workspace_scores_offset.argtypes = [cfgp, i32]
         L.fier_decode_step_kernels.restype = C.c_int
@@ -158,6 +161,10 @@ def workspace_bytes(cfg: Config, max_budget: int) -> int:
     return int(lib().fier_workspace_bytes(C.byref(cfg), int(max_budget)))
 
 
+def workspace_bytes_layers(cfg: Config, max_budget: int, n_layers: int) -> int:
+    return int(lib().fier_workspace_bytes_layers(C.byref(cfg), int(max_budget), int(n_layers)))
+
+
 def workspace_scores(cfg: Config, max_budget: int, workspace):
     """View of the step's score array [units][max_ctx] float32 inside a workspace tensor (for inspection)."""
     import torch
@@ -174,11 +181,12 @@ def decode_step_kernels(cfg: Config, max_budget: int, with_index_list: bool = Fa
     return int(lib().fier_decode_step_kernels(C.byref(cfg), int(max_budget), 1 if with_index_list else 0))
 
 
-def make_workspace(cfg: Config, max_budget: int):
-    """A zero-filled workspace on the GPU (the library keeps its counters zero from then on)."""
+def make_workspace(cfg: Config, max_budget: int, n_layers: int = 16):
+    """A zero-filled workspace on the GPU (the library keeps its counters zero from then on), sized for calls of up
+    to n_layers layers to share their launches (1: the smallest; longer calls work with any size)."""
     import torch
 
-    n = workspace_bytes(cfg, max_budget)
+    n = workspace_bytes_layers(cfg, max_budget, n_layers)
     assert n > 0
     return torch.zeros(n, dtype=torch.uint8, device="cuda")
 

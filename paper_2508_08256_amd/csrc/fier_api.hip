@@ -139,6 +139,68 @@ Workspace carve(const fier_config* c, int32_t max_budget, void* base) {
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? FIER_OK : FIER_EHIP; }
 
+// Layers of one fused-step launch: up to 16, and up to 2^25 cached tokens and units.  Layer by layer, a small layer pays
+// two launches, their prologues and drains and its serial hand-offs (threshold, merge) with most of the chip idle; side
+// by side the layers fill each other's gaps.  Measured (us per call, layer by layer / side by side): 16 layers of 64
+// units x 1k..8k, paged, 4 query heads per kv head 499 / 139; 8 layers of 8 units x 32k, 4 heads 209 / 55; 2 layers of
+// 16 units x 20k with the index list 73 / 42; 4 layers of 128 units x 8k..64k, whose steps fill the chip by
+// themselves, 396 / 401 two at a time, 374 all four.  The bound holds the workspace at about 300 MB.
+constexpr int64_t kBatchTokens = (int64_t)1 << 25;
+inline int layers_per_launch(const fier_config* c) {
+  const int64_t n = kBatchTokens / ((int64_t)units_of(c) * c->max_ctx);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(n, fier::kMaxLayersPerLaunch));
+}
+
+inline bool overlap(const void* a, const void* b, size_t bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y ? y - x < bytes : x - y < bytes;
+}
+
+// Whether the steps of two layers may run side by side: none of the arrays one of them writes is the other's.  (Two
+// layers on the same cache are legal: the second one's append then follows the first's.)  The extent of a pool of
+// blocks is the caller's: pools are told apart by their addresses.
+bool independent(const fier_config* c, const fier_cache* a, const fier_cache* b) {
+  if ((a->block_table == nullptr) != (b->block_table == nullptr) || a->block_tokens != b->block_tokens) return false;
+  const size_t units = (size_t)units_of(c);
+  const size_t rows = a->block_table ? 1 : units * (size_t)c->max_ctx * kD * 2;
+  return !(overlap(a->k, b->k, rows) || overlap(a->v, b->v, rows) || overlap(a->k, b->v, rows) ||
+           overlap(a->v, b->k, rows) || overlap(a->kbits, b->kbits, units * (size_t)c->max_ctx * 16) ||
+           overlap(a->kmeta, b->kmeta, units * (size_t)(c->max_ctx / c->group_size) * kD * sizeof(uint32_t)) ||
+           overlap(a->kabsmax, b->kabsmax, units * kD * sizeof(float)));
+}
+
+// The first layers of `layers` (at most `most`; up to the first one flagged dense) that can share a launch.
+fier::LayerBatch batch_of(const fier_config* c, const fier_cache* layers, const uint8_t* dense, int most,
+                          size_t ws_stride) {
+  fier::LayerBatch lb;
+  lb.ws_stride = (int64_t)ws_stride;
+  auto distance = [](const void* from, const void* to) {
+    return (int64_t)(reinterpret_cast<uintptr_t>(to) - reinterpret_cast<uintptr_t>(from));
+  };
+  for (lb.n = 0; lb.n < most; ++lb.n) {
+    const fier_cache &f = layers[0], &x = layers[lb.n];
+    bool ok = lb.n == 0 || !dense || !dense[lb.n];
+    for (int i = 0; i < lb.n && ok; ++i) ok = independent(c, &layers[i], &x);
+    if (!ok) break;
+    lb.at[lb.n] = {distance(f.k, x.k),           distance(f.v, x.v),
+                   distance(f.kbits, x.kbits),   distance(f.kmeta, x.kmeta),
+                   distance(f.kabsmax, x.kabsmax), distance(f.seq_lens, x.seq_lens),
+                   distance(f.block_table, x.block_table)};
+  }
+  return lb;
+}
+
+// Clears the leading `words` of each of gridDim.y parts of a workspace.
+__global__ void zero_words_kernel(uint32_t* __restrict__ p, size_t words, size_t stride_bytes) {
+  p += (size_t)blockIdx.y * (stride_bytes / sizeof(uint32_t));
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
+}
+hipError_t zero_parts(void* first, size_t words, size_t stride_bytes, int parts, hipStream_t st) {
+  const unsigned wgs = (unsigned)std::min<size_t>((words + 1023) / 1024, 256);
+  zero_words_kernel<<<dim3(wgs, (unsigned)parts), 256, 0, st>>>(static_cast<uint32_t*>(first), words, stride_bytes);
+  return hipGetLastError();
+}
+
 // The caller's workspace against what the call is going to carve from it.
 inline int check_workspace(const void* ws, size_t have, size_t need) {
   if (!ws || have < need) return FIER_EWORKSPACE;
@@ -179,6 +241,12 @@ size_t fier_workspace_bytes(const fier_config* cfg, int32_t max_budget) {
   if (check_cfg(cfg) != FIER_OK || max_budget < 1) return 0;
   if (max_budget > cfg->max_ctx) max_budget = cfg->max_ctx;
   return carve(cfg, max_budget, nullptr).bytes;
+}
+
+size_t fier_workspace_bytes_layers(const fier_config* cfg, int32_t max_budget, int32_t n_layers) {
+  if (n_layers < 1) return 0;
+  const size_t one = fier_workspace_bytes(cfg, max_budget);
+  return one ? one * (size_t)std::min<int32_t>(n_layers, layers_per_launch(cfg)) : 0;
 }
 
 size_t fier_workspace_scores_offset(const fier_config* cfg, int32_t max_budget) {
@@ -226,10 +294,12 @@ int fier_score(const fier_config* cfg, const fier_cache* cache, const void* q, i
   if (st != FIER_OK) return st;
   if (!q || !scores || extra_tokens < 0 || extra_tokens > 1) return FIER_EINVAL;
   if (misaligned(q) || misaligned(scores)) return FIER_EALIGN;
+  fier::LayerBatch one;
+  one.n = 1;
   return hip_status(fier::launch_score(cfg->kv_dtype, layout_of(cfg, cache), n_rep_of(cfg), cache->kbits, cache->kmeta, cache->kabsmax, q,
                                        cache->seq_lens, extra_tokens, scores, nullptr, nullptr, 0, nullptr, nullptr,
                                        nullptr, nullptr, units_of(cfg), cfg->n_kv_heads, cfg->max_ctx,
-                                       cfg->group_size, (hipStream_t)stream));
+                                       cfg->group_size, one, (hipStream_t)stream));
 }
 
 int fier_topk(const fier_config* cfg, const float* scores, const int32_t* seq_lens, int32_t extra_tokens,
@@ -329,7 +399,13 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
   const size_t esz = 2;
   hipStream_t s = (hipStream_t)stream;
   Workspace w = carve(cfg, max_budget, workspace);
-  for (int l = 0; l < n_layers; ++l) {
+  // Layers that share their launches: as many as the workspace has parts for (one kernel alone, phase > 0, works on
+  // what the phases before it left: layer by layer).  Only the first part is known to be clear, the others are
+  // cleared here before they are first used, and again after a dense layer, which carves the workspace its own way.
+  const int most = phase != 0 ? 1 : (int)std::min<size_t>((size_t)layers_per_launch(cfg), workspace_bytes / w.bytes);
+  int clear_parts = 1;
+  for (int l = 0, n_done = 1; l < n_layers; l += n_done) {
+    n_done = 1;
     const fier_cache* c = &layers[l];
     const char* ql = static_cast<const char*>(q) + (size_t)l * cfg->batch * cfg->n_q_heads * kD * esz;
     float* outl = out + (size_t)l * cfg->batch * cfg->n_q_heads * kD;
@@ -353,12 +429,22 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
                             rows_per_wg, n_splits, cfg->sm_scale, wd.po, wd.pm, wd.pl, wd.sb.ctl, outl, units,
                             cfg->n_kv_heads, cfg->max_ctx, s);
       if (e != hipSuccess) return FIER_EHIP;
+      clear_parts = 1;
       continue;
+    }
+    const fier::LayerBatch lb =
+        batch_of(cfg, c, dense_layers ? dense_layers + l : nullptr, std::min(most, n_layers - l), w.bytes);
+    n_done = lb.n;
+    if (lb.n > clear_parts) {
+      e = zero_parts(static_cast<char*>(workspace) + clear_parts * w.bytes, w.zero_bytes / sizeof(uint32_t), w.bytes,
+                     lb.n - clear_parts, s);
+      if (e != hipSuccess) return FIER_EHIP;
+      clear_parts = lb.n;
     }
     if (phase == 0 || phase == 1) {
       e = fier::launch_score(cfg->kv_dtype, lay, n_rep, c->kbits, c->kmeta, c->kabsmax, ql, c->seq_lens, extra,
                              w.sb.scores, &w.sb, budgets, max_budget, c->k, c->v, kn, vn, units, cfg->n_kv_heads,
-                             cfg->max_ctx, cfg->group_size, s);
+                             cfg->max_ctx, cfg->group_size, lb, s);
       if (e != hipSuccess) return FIER_EHIP;
     }
     // After scoring: one launch (exact threshold + attention + merge, then the index list if asked for) wherever
@@ -367,17 +453,17 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
     // is asked for (that form writes it while it selects).
     const bool two_kernels =
         phase > 3 ? (phase >> 4) <= 3
-                  : fier::step_two_kernel_form(units, n_rep, max_budget, cfg->max_ctx, idx_out != nullptr);
+                  : lb.n > 1 || fier::step_two_kernel_form(units, n_rep, max_budget, cfg->max_ctx, idx_out != nullptr);
     if (two_kernels) {
       if (phase == 0 || (phase & 15) == 2) {
         e = fier::launch_step_attend(cfg->kv_dtype, lay, n_rep, w.sb, c->k, c->v, ql, c->seq_lens, extra, budgets,
                                      max_budget, cfg->sm_scale, cntl, outl, c->kabsmax, units, cfg->n_kv_heads,
-                                     cfg->max_ctx, phase >> 4, s);
+                                     cfg->max_ctx, phase >> 4, lb, s);
         if (e != hipSuccess) return FIER_EHIP;
       }
       if ((phase == 0 || (phase & 15) == 3) && idxl) {
         e = fier::launch_step_emit_idx(w.sb, c->seq_lens, extra, max_budget, idxl, units, n_rep, cfg->n_kv_heads,
-                                         cfg->max_ctx, s);
+                                         cfg->max_ctx, lb, s);
         if (e != hipSuccess) return FIER_EHIP;
       }
     } else {
@@ -431,10 +517,6 @@ constexpr int kMaxDevices = 64;
 void* g_scratch_ptr[kMaxDevices];
 std::mutex g_scratch_mutex;
 
-__global__ void zero_words_kernel(uint32_t* __restrict__ p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
-}
-
 // Device address of the current device's copy of `scratch` (resolved on the first call on that device).
 int static_scratch(void** out) {
   int dev = -1;
@@ -467,10 +549,8 @@ int fier_decode_step_static(const fier_config* cfg, const fier_cache* layers, in
   if (st != FIER_OK) return st;
   // The array keeps what the last call left, possibly laid out for another shape: the part that has to start at
   // zero is cleared by a kernel on the caller's stream (a fill kernel, not a memset node: callers may be capturing).
-  const size_t words = need.zero_bytes / sizeof(uint32_t);
-  zero_words_kernel<<<(unsigned)((words + 1023) / 1024 < 256 ? (words + 1023) / 1024 : 256), 256, 0,
-                      (hipStream_t)stream>>>(static_cast<uint32_t*>(ptr), words);
-  if (hipGetLastError() != hipSuccess) return FIER_EHIP;
+  if (zero_parts(ptr, need.zero_bytes / sizeof(uint32_t), need.bytes, 1, (hipStream_t)stream) != hipSuccess)
+    return FIER_EHIP;
   return decode_step_impl(cfg, layers, n_layers, nullptr, q, k_new, v_new, budgets, max_budget, out, idx_out, count_out,
                           ptr, kStaticScratchBytes, 0, stream);
 }

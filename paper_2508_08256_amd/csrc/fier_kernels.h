@@ -98,6 +98,27 @@ struct StepBuffers {    // carved from the caller's workspace
   int seg_pitch;        // workgroup entries per unit in seg_cnt and sel_cnt
 };
 
+// ---- several layers in one launch --------------------------------------------------------------------------------------
+// The layers of one fused-step launch lie along blockIdx.z.  The launch gets the first layer's pointers as they are
+// and, by value, how many bytes from there every layer's arrays lie; q, k_new, v_new, out, idx and count are arrays over
+// the layers already.  Every layer has a part of the workspace of its own, the last layer the first part.
+constexpr int kMaxLayersPerLaunch = 16;
+struct LayerShift {  // bytes from the first layer's arrays to this layer's
+  int64_t k, v, kbits, kmeta, kabsmax, seq_lens, table;
+};
+struct LayerBatch {
+  int n;
+  int64_t ws_stride;  // bytes from one part of the workspace to the next
+  LayerShift at[kMaxLayersPerLaunch];
+  __device__ __forceinline__ int64_t ws_shift(int z) const { return (int64_t)(n - 1 - z) * ws_stride; }
+};
+struct OneLayer {};  // a launch of a single layer: nothing to look up (the table in front of a workgroup's first loads
+                     // cost 0.7 us of 19 at 8 units x 4k, 1.4 us of 31 at 32 units x 32k)
+template <typename T>
+__device__ __forceinline__ T* shifted(T* p, int64_t bytes) {
+  return (T*)((char*)p + bytes);  // char arithmetic, not integers: the result keeps its address space
+}
+
 hipError_t launch_quantize(int dtype, KvLayout lay, const void* K, uint32_t* kbits, uint32_t* kmeta, float* kabsmax,
                            const int32_t* seq_lens, int units, int n_kv_heads, int max_ctx, int group_size,
                            hipStream_t st);
@@ -111,7 +132,8 @@ hipError_t launch_append(int dtype, KvLayout lay, void* K, void* V, uint32_t* kb
 hipError_t launch_score(int dtype, KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta, const float* kabsmax,
                         const void* q, const int32_t* seq_lens, int extra, float* scores, const StepBuffers* sb,
                         const int32_t* budgets, int max_budget, void* K, void* V, const void* k_new,
-                        const void* v_new, int units, int n_kv_heads, int max_ctx, int group_size, hipStream_t st);
+                        const void* v_new, int units, int n_kv_heads, int max_ctx, int group_size,
+                        const LayerBatch& lb, hipStream_t st);
 
 // The same selection by many workgroups per unit where a unit's scores do not fit one workgroup's registers.
 hipError_t launch_topk_ws(const StepBuffers& sb, const float* scores, const int32_t* seq_lens, int extra,
@@ -133,10 +155,10 @@ hipError_t launch_select_attend(int dtype, KvLayout lay, int n_rep, const StepBu
 hipError_t launch_step_attend(int dtype, KvLayout lay, int n_rep, const StepBuffers& sb, const void* K, const void* V,
                               const void* q, const int32_t* seq_lens, int extra, const int32_t* budgets, int max_budget,
                               float sm_scale, int32_t* count_out, float* out, float* kabsmax, int units, int n_kv_heads,
-                              int max_ctx, int flags, hipStream_t st);
+                              int max_ctx, int flags, const LayerBatch& lb, hipStream_t st);
 // The ascending index list of the selection that kernel made (an optional output of the step).
 hipError_t launch_step_emit_idx(const StepBuffers& sb, const int32_t* seq_lens, int extra, int max_budget, int32_t* idx,
-                                int units, int n_rep, int n_kv_heads, int max_ctx, hipStream_t st);
+                                int units, int n_rep, int n_kv_heads, int max_ctx, const LayerBatch& lb, hipStream_t st);
 int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx);
 bool step_two_kernel_form(int units, int n_rep, int max_budget, int max_ctx, bool with_index_list);
 

@@ -83,7 +83,7 @@ __device__ __forceinline__ uint32_t row_allmax_u32(uint32_t x) {
 // its registers; the other workgroups leave those tokens alone.  The bound R uses the absmax of before the
 // append (every workgroup must bin with the same R); the new group's contribution is handed to the last kernel
 // of the step through `newmax`.  A score outside [-R, R] simply lands in the outermost bin.
-template <int DT, int NREP, bool HIST, bool STREAM>
+template <int DT, int NREP, bool HIST, bool STREAM, class LAYERS>
 __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const uint4* kmeta,
                                                     const float* __restrict__ kabsmax, const uint16_t* __restrict__ q,
                                                     const int32_t* __restrict__ seq_lens, int extra,
@@ -92,7 +92,8 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
                                                     int max_budget, uint32_t* __restrict__ K, uint32_t* __restrict__ V,
                                                     const uint32_t* __restrict__ k_new,
                                                     const uint32_t* __restrict__ v_new, float* __restrict__ newmax,
-                                                    int n_kv_heads, int max_ctx, int bpw, int gshift, int n_x, KvLayout lay) {
+                                                    int n_kv_heads, int max_ctx, int bpw, int gshift, int n_x, KvLayout lay,
+                                                    const LAYERS lb) {
   __shared__ uint32_t lhist[HIST ? kSelBins : 1];
   __shared__ __attribute__((aligned(16))) unsigned char a_lds[4 * kAWave];
   // The workgroup's scores wait here and leave as one contiguous burst at the end: stores interleaved block by block
@@ -111,6 +112,28 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
   const int unit = append_wg ? (int)blockIdx.x : wid / n_x;
   const int range = append_wg ? -1 : wid - unit * n_x;
   const int b = unit / n_kv_heads;
+  if constexpr (std::is_same<LAYERS, LayerBatch>::value) {  // this workgroup's layer
+    const int z = (int)blockIdx.z;
+    const LayerShift at = lb.at[z];
+    const int64_t ws = lb.ws_shift(z);
+    kbits = shifted(kbits, at.kbits);
+    kmeta = shifted(kmeta, at.kmeta);
+    kabsmax = shifted(kabsmax, at.kabsmax);
+    seq_lens = shifted(seq_lens, at.seq_lens);
+    K = shifted(K, at.k);
+    V = shifted(V, at.v);
+    lay.table = lay.table ? shifted(lay.table, at.table) : nullptr;
+    scores = shifted(scores, ws);
+    ctl = shifted(ctl, ws);
+    ghist = shifted(ghist, ws);
+    newmax = shifted(newmax, ws);
+    const size_t zu = (size_t)z * n_units;
+    q += zu * NREP * kD;
+    if (k_new != nullptr) {
+      k_new += zu * (kD / 2);
+      v_new += zu * (kD / 2);
+    }
+  }
   const uint16_t* qb = q + (size_t)unit * NREP * kD;
   // The appending wavefront's chain of dependent loads is the longest in the kernel: what it needs and what does
   // not depend on the sequence length (the new rows, its lanes' query values) leaves before anything else.
@@ -483,7 +506,7 @@ static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits
                                   const void* q, const int32_t* seq_lens, int extra, float* scores,
                                   const StepBuffers* sb, const int32_t* budgets, int max_budget, void* K, void* V,
                                   const void* k_new, const void* v_new, int units, int n_kv_heads, int max_ctx,
-                                  int group_size, hipStream_t st) {
+                                  int group_size, const LayerBatch& lb, hipStream_t st) {
   const int gshift = group_size == 256 ? 3 : group_size == 128 ? 2 : group_size == 64 ? 1 : 0;
   // Blocks per wavefront.  The smallest that lets every workgroup be resident at once (256 CUs; the registers
   // allow 5 workgroups per CU for the fused kernel -- 4 with 8 query heads per kv head --, 8 for the score-only
@@ -494,8 +517,9 @@ static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits
   // block in flight per wavefront.  Strides of a power of two between the workgroups' streams are avoided (they
   // collide in the memory channels: measured 8 vs 7 or 9, 16 vs 13).
   const int n_blocks = (max_ctx + kPair - 1) / kPair;
-  const int wg_slots = HIST ? 256 * 5 - units : 256 * 8;
-  const int per_unit = wg_slots / units > 0 ? wg_slots / units : 1;
+  const int all_units = units * lb.n;  // of all layers of the launch
+  const int wg_slots = HIST ? 256 * 5 - all_units : 256 * 8;
+  const int per_unit = wg_slots / all_units > 0 ? wg_slots / all_units : 1;
   int bpw = (n_blocks + 4 * per_unit - 1) / (4 * per_unit);
   bpw = bpw < 4 ? 4 : bpw;
   const int rounds = (bpw + 11) / 12;
@@ -503,12 +527,12 @@ static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits
   if (bpw >= 8 && (bpw & (bpw - 1)) == 0) ++bpw;
   if (bpw > kScoreMaxBpw) return hipErrorInvalidValue;  // cannot happen: at most 12, + 1
   const int n_x = (n_blocks + 4 * bpw - 1) / (4 * bpw);  // scoring workgroups per unit
-  dim3 grid((unsigned)units * (unsigned)(n_x + (HIST ? 1 : 0)));
+  dim3 grid((unsigned)units * (unsigned)(n_x + (HIST ? 1 : 0)), 1, (unsigned)lb.n);
   // Streaming hint on the loads of the codes and their metadata (read once per step).  Measured with the step
   // rotating over 12 layer caches, this kernel alone, us without / with it: 32 units x 128k 34.4 / 30.6, 32 x 64k
   // 19.2 / 16.5, the ragged 128-unit batch 34.5 / 31.5 (whole steps: 62.2 / 61.5, 32.6 / 31.9, 102.3 / 100.7);
   // shapes of 32 units x 32k and below lost 0.2-0.4 us per step with it.  Hence from 64 MB per launch.
-  const bool stream = (long)units * max_ctx * 32 >= (64L << 20);
+  const bool stream = (long)all_units * max_ctx * 32 >= (64L << 20);
 #define FIER_SCORE_ARGS                                                                                            \
   (const uint4*)kbits, (const uint4*)kmeta, kabsmax, (const uint16_t*)q, seq_lens, extra, scores,                  \
       sb ? sb->ctl : nullptr, sb ? sb->hist : nullptr, budgets, max_budget, (uint32_t*)K, (uint32_t*)V,            \
@@ -516,10 +540,18 @@ static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits
       n_x, lay
 #define FIER_SCORE_CASE(R)                                                                                         \
   case R:                                                                                                          \
+    if constexpr (HIST)                                                                                            \
+      if (lb.n > 1) {                                                                                              \
+        if (stream)                                                                                                \
+          score_kernel<DT, R, HIST, true, LayerBatch><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, lb);                  \
+        else                                                                                                       \
+          score_kernel<DT, R, HIST, false, LayerBatch><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, lb);                 \
+        break;                                                                                                     \
+      }                                                                                                            \
     if (stream)                                                                                                    \
-      score_kernel<DT, R, HIST, true><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS);                                      \
+      score_kernel<DT, R, HIST, true, OneLayer><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, OneLayer());                \
     else                                                                                                           \
-      score_kernel<DT, R, HIST, false><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS);                                     \
+      score_kernel<DT, R, HIST, false, OneLayer><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, OneLayer());               \
     break;
   switch (n_rep) {
     FIER_SCORE_CASE(1)
@@ -541,19 +573,20 @@ static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits
 hipError_t launch_score(int dtype, KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta, const float* kabsmax,
                         const void* q, const int32_t* seq_lens, int extra, float* scores, const StepBuffers* sb,
                         const int32_t* budgets, int max_budget, void* K, void* V, const void* k_new,
-                        const void* v_new, int units, int n_kv_heads, int max_ctx, int group_size, hipStream_t st) {
+                        const void* v_new, int units, int n_kv_heads, int max_ctx, int group_size, const LayerBatch& lb,
+                        hipStream_t st) {
   if (sb) {
     if (dtype == DT_F16)
       return launch_score_dt<DT_F16, true>(lay, n_rep, kbits, kmeta, kabsmax, q, seq_lens, extra, scores, sb, budgets,
-                                           max_budget, K, V, k_new, v_new, units, n_kv_heads, max_ctx, group_size, st);
+                                           max_budget, K, V, k_new, v_new, units, n_kv_heads, max_ctx, group_size, lb, st);
     return launch_score_dt<DT_BF16, true>(lay, n_rep, kbits, kmeta, kabsmax, q, seq_lens, extra, scores, sb, budgets,
-                                          max_budget, K, V, k_new, v_new, units, n_kv_heads, max_ctx, group_size, st);
+                                          max_budget, K, V, k_new, v_new, units, n_kv_heads, max_ctx, group_size, lb, st);
   }
   if (dtype == DT_F16)
     return launch_score_dt<DT_F16, false>(lay, n_rep, kbits, kmeta, kabsmax, q, seq_lens, extra, scores, nullptr, nullptr,
-                                          0, nullptr, nullptr, nullptr, nullptr, units, n_kv_heads, max_ctx, group_size, st);
+                                          0, nullptr, nullptr, nullptr, nullptr, units, n_kv_heads, max_ctx, group_size, lb, st);
   return launch_score_dt<DT_BF16, false>(lay, n_rep, kbits, kmeta, kabsmax, q, seq_lens, extra, scores, nullptr, nullptr, 0,
-                                         nullptr, nullptr, nullptr, nullptr, units, n_kv_heads, max_ctx, group_size, st);
+                                         nullptr, nullptr, nullptr, nullptr, units, n_kv_heads, max_ctx, group_size, lb, st);
 }
 
 }  // namespace fier

@@ -239,7 +239,7 @@ struct StepArgs {
   int32_t* count_out;
   float* kabsmax;
   const float* newmax;
-  int n_kv_heads, max_ctx, order, wgs_per_unit;
+  int units, n_kv_heads, max_ctx, order, wgs_per_unit;
   size_t cand_pitch;
   int flags;  // tests: bit 0 = no workgroup picks up the threshold (the merging workgroup attends over all
               // threshold-bin rows); bit 1 = checksums of the attended rows
@@ -667,10 +667,34 @@ __device__ __forceinline__ void step_unit_wg(const StepArgs& a, int id_x, int id
 constexpr int step_wgs_per_cu(int n_rep) { return n_rep <= 2 ? 5 : (n_rep <= 3 ? 4 : (n_rep <= 5 ? 3 : 2)); }
 // STREAM: the gathered rows are loaded with the streaming hint (with three or more query heads per kv head, where
 // the K rows go to the matrix cores in four pieces per row, the V rows only).
-template <int DT, int NREP, int RPW, bool STREAM>
+template <int DT, int NREP, int RPW, bool STREAM, class LAYERS>
 __global__ __launch_bounds__(kStepThreads, step_wgs_per_cu(NREP)) void step_attend_kernel(
-    const StepArgs a) {
+    StepArgs a, const LAYERS lb) {
   __shared__ StepLds<NREP, RPW> lds;
+  if constexpr (std::is_same<LAYERS, LayerBatch>::value) {  // this workgroup's layer
+    const int z = (int)blockIdx.z;
+    const LayerShift at = lb.at[z];
+    const int64_t ws = lb.ws_shift(z);
+    const size_t heads = (size_t)z * a.units * NREP;
+    a.K = shifted(a.K, at.k);
+    a.V = shifted(a.V, at.v);
+    a.kabsmax = shifted(a.kabsmax, at.kabsmax);
+    a.seq_lens = shifted(a.seq_lens, at.seq_lens);
+    a.lay.table = a.lay.table ? shifted(a.lay.table, at.table) : nullptr;
+    a.scores = shifted(a.scores, ws);
+    a.ctl = shifted(a.ctl, ws);
+    a.ghist = shifted(a.ghist, ws);
+    a.cand = shifted(a.cand, ws);
+    a.sel_cnt = shifted(a.sel_cnt, ws);
+    a.seg_cnt = shifted(a.seg_cnt, ws);
+    a.newmax = shifted(a.newmax, ws);
+    a.po = shifted(a.po, ws);
+    a.pm = shifted(a.pm, ws);
+    a.pl = shifted(a.pl, ws);
+    a.q += heads * (kD / 8);
+    a.out += heads * kD;
+    if (a.count_out) a.count_out += (size_t)z * a.units;
+  }
   int unit, wg;
   step_unit_wg(a, (int)blockIdx.x, (int)blockIdx.y, unit, wg);
   step_attend_body<DT, NREP, RPW, STREAM>(a, unit, wg, lds);
@@ -688,10 +712,19 @@ __global__ __launch_bounds__(kStepThreads) void step_emit_idx_kernel(const float
                                                                      const uint32_t* __restrict__ sel_cnt,
                                                                      int wgs_per_unit, int max_budget,
                                                                      int32_t* __restrict__ idx, int n_kv_heads,
-                                                                     int max_ctx) {
+                                                                     int max_ctx, const LayerBatch lb) {
   __shared__ uint32_t wtot[RPW + 1][4];  // per wavefront: selected tokens of each range, rows of the workgroups before
   const int unit = blockIdx.x, wg = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
+  {  // this workgroup's layer
+    const int z = (int)blockIdx.z;
+    const int64_t ws = lb.ws_shift(z);
+    scores = shifted(scores, ws);
+    ctl = shifted(ctl, ws);
+    sel_cnt = shifted(sel_cnt, ws);
+    seq_lens = shifted(seq_lens, lb.at[z].seq_lens);
+    idx += (size_t)z * gridDim.x * max_budget;
+  }
   int n = seq_lens[unit / n_kv_heads] + extra;
   n = n < 0 ? 0 : (n > max_ctx ? max_ctx : n);
   const int tok0 = wg * RPW * kRangeTokens;
@@ -756,6 +789,7 @@ __global__ __launch_bounds__(kStepThreads) void step_emit_idx_kernel(const float
 // Workgroups of the step's second kernel that a 256-CU chip holds at once (the kernel's second launch bound).
 static long step_resident_wgs(int n_rep) { return 256L * step_wgs_per_cu(n_rep); }
 
+#ifndef FIER_STEP_PART
 // Ranges per workgroup of the one-launch form (rows per 1024-token range = 1024 * budget / context):
 //   * at least 96 selected rows per workgroup;
 //   * more where fewer, larger workgroups make the grid resident at once;
@@ -763,6 +797,8 @@ static long step_resident_wgs(int n_rep) { return 256L * step_wgs_per_cu(n_rep);
 //     (us per step): 32 units x 32k, 112 rows per range: 35.0 with one range per workgroup, 34.0 with two, 38.1 with
 //     four; 32 units x 16k (two ranges = one workgroup per CU): 25.8 / 27.4; 32 units x 64k, B = 7209: 50.9 with two
 //     ranges (225 rows), 51.5 with four; 64 units x 32k: 50.6 with two, 51.9 with four.
+//   units: of all layers of the launch (8 layers of 8 units x 32k: 81 us per call at one range, 62 at two, 55 at four, 63
+// at eight; 16 layers of 64 units x 1k..8k: 174 / 180 / 149 / 139 at 1 / 2 / 4 / 8, its rule gives eight).
 int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
   const double per_range = 1024.0 * (double)max_budget / (double)max_ctx;
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
@@ -773,6 +809,7 @@ int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
   if (rpw < 8 && per_range * (2 * rpw) <= 288.0 && wgs(2 * rpw) >= 512) rpw *= 2;
   return rpw;
 }
+#endif
 
 static bool fill_step_args(StepArgs& a, int rpw, int order, KvLayout lay, const StepBuffers& sb, const void* K,
                            const void* V, const void* q, const int32_t* seq_lens, int extra, const int32_t* budgets,
@@ -801,6 +838,7 @@ static bool fill_step_args(StepArgs& a, int rpw, int order, KvLayout lay, const 
   a.count_out = count_out;
   a.kabsmax = kabsmax;
   a.newmax = sb.newmax;
+  a.units = units;
   a.n_kv_heads = n_kv_heads;
   a.max_ctx = max_ctx;
   a.order = order;
@@ -811,11 +849,14 @@ static bool fill_step_args(StepArgs& a, int rpw, int order, KvLayout lay, const 
   return (size_t)n_wgs * (rpw * kRangeTokens / 4) <= sb.cand_pitch && n_wgs <= sb.seg_pitch;
 }
 
-template <int DT, int RPW>
-static hipError_t launch_step_attend_dt(KvLayout lay, int n_rep, const StepBuffers& sb, const void* K, const void* V,
+// The kernel's variants are many and large: they are compiled in parts, FIER_STEP_PART = 2 MULTI + DT (MULTI: launches
+// of several layers), next to the rest of this file.
+template <int DT, int RPW, bool MULTI>
+hipError_t launch_step_attend_dt(KvLayout lay, int n_rep, const StepBuffers& sb, const void* K, const void* V,
                                         const void* q, const int32_t* seq_lens, int extra, const int32_t* budgets,
                                         int max_budget, float sm_scale, int32_t* count_out, float* out, float* kabsmax,
-                                        int units, int n_kv_heads, int max_ctx, int flags, hipStream_t st) {
+                                        int units, int n_kv_heads, int max_ctx, int flags, const LayerBatch& lb,
+                                        hipStream_t st) {
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
   const int n_wgs = (n_ranges + RPW - 1) / RPW;
   // Dispatch order.  Workgroups go round-robin to the 8 XCDs in the order of their linear index; when a unit's
@@ -829,8 +870,9 @@ static hipError_t launch_step_attend_dt(KvLayout lay, int n_rep, const StepBuffe
   // workgroups per CU, 256 CUs): its workgroups poll for their unit's threshold, and a unit spread over two rounds
   // of workgroups would have the first round waiting for the second.
   const long resident = step_resident_wgs(n_rep);
-  const int order = (long)units * n_wgs <= resident ? 1 : (units % 8 == 0 ? 2 : 0);
+  const int order = (long)units * lb.n * n_wgs <= resident ? 1 : (units % 8 == 0 ? 2 : 0);
   dim3 grid = order == 2 ? dim3((unsigned)units * (unsigned)n_wgs) : (order ? dim3(units, n_wgs) : dim3(n_wgs, units));
+  grid.z = (unsigned)lb.n;
   StepArgs a;
   if (!fill_step_args(a, RPW, order, lay, sb, K, V, q, seq_lens, extra, budgets, max_budget, sm_scale, count_out, out,
                       kabsmax, units, n_kv_heads, max_ctx, flags))
@@ -843,11 +885,12 @@ static hipError_t launch_step_attend_dt(KvLayout lay, int n_rep, const StepBuffe
   // at 32 x 32k.)  The matrix-core gather (3 or more heads per kv head) lost by it on the K rows, which it loads in
   // four pieces per row (32 units x 128k +0.6 us, the ragged 128-unit batch +4), and gains on the V rows alone:
   // 32 x 128k 61.5 / 59.7, the ragged batch 101.3 / 100.8.
-  const bool stream = (long)units * max_budget * (2 * kD * 2) >= (8L << 20);
+  const bool stream = (long)units * lb.n * max_budget * (2 * kD * 2) >= (8L << 20);
 #define FIER_STEP_CASE_S(R)                                                       \
   case R:                                                                         \
-    if (stream) step_attend_kernel<DT, R, RPW, true><<<grid, kStepThreads, 0, st>>>(a);  \
-    else step_attend_kernel<DT, R, RPW, false><<<grid, kStepThreads, 0, st>>>(a); \
+    if constexpr (MULTI) step_attend_kernel<DT, R, RPW, true, LayerBatch><<<grid, kStepThreads, 0, st>>>(a, lb);        \
+    else if (stream) step_attend_kernel<DT, R, RPW, true, OneLayer><<<grid, kStepThreads, 0, st>>>(a, OneLayer());      \
+    else step_attend_kernel<DT, R, RPW, false, OneLayer><<<grid, kStepThreads, 0, st>>>(a, OneLayer());                 \
     break;
   switch (n_rep) {
     FIER_STEP_CASE_S(1)
@@ -865,14 +908,29 @@ static hipError_t launch_step_attend_dt(KvLayout lay, int n_rep, const StepBuffe
   return hipGetLastError();
 }
 
+#define FIER_STEP_INSTANCES(WORD, DT, MULTI)                                                                          \
+  FIER_STEP_INSTANCE(WORD, DT, 1, MULTI) FIER_STEP_INSTANCE(WORD, DT, 2, MULTI) FIER_STEP_INSTANCE(WORD, DT, 4, MULTI) \
+  FIER_STEP_INSTANCE(WORD, DT, 8, MULTI)
+#define FIER_STEP_INSTANCE(WORD, DT, RPW, MULTI)                                                                      \
+  WORD template hipError_t launch_step_attend_dt<DT, RPW, MULTI>(                                                     \
+      KvLayout, int, const StepBuffers&, const void*, const void*, const void*, const int32_t*, int, const int32_t*,  \
+      int, float, int32_t*, float*, float*, int, int, int, int, const LayerBatch&, hipStream_t);
+#ifdef FIER_STEP_PART
+FIER_STEP_INSTANCES(, FIER_STEP_PART & 1, (FIER_STEP_PART >> 1) != 0)
+#else
+FIER_STEP_INSTANCES(extern, DT_F16, false)
+FIER_STEP_INSTANCES(extern, DT_BF16, false)
+FIER_STEP_INSTANCES(extern, DT_F16, true)
+FIER_STEP_INSTANCES(extern, DT_BF16, true)
+
 hipError_t launch_step_attend(int dtype, KvLayout lay, int n_rep, const StepBuffers& sb, const void* K, const void* V,
                               const void* q, const int32_t* seq_lens, int extra, const int32_t* budgets, int max_budget,
                               float sm_scale, int32_t* count_out, float* out, float* kabsmax, int units, int n_kv_heads,
-                              int max_ctx, int flags, hipStream_t st) {
+                              int max_ctx, int flags, const LayerBatch& lb, hipStream_t st) {
 #define FIER_STEP_RPW(DT, RPW)                                                                                        \
-  return launch_step_attend_dt<DT, RPW>(lay, n_rep, sb, K, V, q, seq_lens, extra, budgets, max_budget, sm_scale,      \
-                                        count_out, out, kabsmax, units, n_kv_heads, max_ctx, flags, st)
-  const int rpw = step_ranges_per_wg(units, n_rep, max_budget, max_ctx);
+  return (lb.n > 1 ? launch_step_attend_dt<DT, RPW, true> : launch_step_attend_dt<DT, RPW, false>)(lay, n_rep, sb, K, V, q, seq_lens, extra, budgets, max_budget, sm_scale,      \
+                                        count_out, out, kabsmax, units, n_kv_heads, max_ctx, flags, lb, st)
+  const int rpw = step_ranges_per_wg(units * lb.n, n_rep, max_budget, max_ctx);
   if (dtype == DT_F16) {
     if (rpw == 1) FIER_STEP_RPW(DT_F16, 1);
     if (rpw == 2) FIER_STEP_RPW(DT_F16, 2);
@@ -908,15 +966,16 @@ bool step_two_kernel_form(int units, int n_rep, int max_budget, int max_ctx, boo
 }
 
 hipError_t launch_step_emit_idx(const StepBuffers& sb, const int32_t* seq_lens, int extra, int max_budget, int32_t* idx,
-                                int units, int n_rep, int n_kv_heads, int max_ctx, hipStream_t st) {
+                                int units, int n_rep, int n_kv_heads, int max_ctx, const LayerBatch& lb,
+                                hipStream_t st) {
   // the same split into workgroups as the step's second kernel
-  const int rpw = step_ranges_per_wg(units, n_rep, max_budget, max_ctx);
+  const int rpw = step_ranges_per_wg(units * lb.n, n_rep, max_budget, max_ctx);
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
   const int n_wgs = (n_ranges + rpw - 1) / rpw;
-  const dim3 grid(units, n_wgs);
+  const dim3 grid(units, n_wgs, lb.n);
 #define FIER_EMIT(RPW)                                                                                              \
   step_emit_idx_kernel<RPW><<<grid, kStepThreads, 0, st>>>(sb.scores, seq_lens, extra, sb.ctl, sb.sel_cnt, n_wgs, \
-                                                           max_budget, idx, n_kv_heads, max_ctx)
+                                                           max_budget, idx, n_kv_heads, max_ctx, lb)
   if (rpw == 1) FIER_EMIT(1);
   else if (rpw == 2) FIER_EMIT(2);
   else if (rpw == 4) FIER_EMIT(4);
@@ -924,5 +983,6 @@ hipError_t launch_step_emit_idx(const StepBuffers& sb, const int32_t* seq_lens, 
 #undef FIER_EMIT
   return hipGetLastError();
 }
+#endif  // FIER_STEP_PART
 
 }  // namespace fier

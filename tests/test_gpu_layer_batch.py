@@ -1,0 +1,116 @@
+"""fier_decode_step over several layers: layers that share a launch give what single-layer calls give."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2508_08256_amd import binding as B
+from paper_2508_08256_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+F16, BF16 = synth.F16, synth.BF16
+
+
+def _layers(seed, n, batch, hq, hkv, lens, buds, dtype, max_ctx, bt, group):
+    import gpu_util
+
+    dws = []
+    for l in range(n):
+        wl = synth.make_workload(f"b{l}", seed + l, batch, hq, hkv, lens, buds, dtype, max_ctx=max_ctx, n_planted=4)
+        dw = gpu_util.PagedWorkload(wl, bt, group, seed=l) if bt else gpu_util.DeviceWorkload(wl, group)
+        B.quantize_keys(dw.cfg, dw.cache)
+        dws.append(dw)
+    return dws
+
+
+def _state(dw):
+    c = dw.cache
+    return [t.clone() for t in (dw.K, dw.V, c.kbits, c.kmeta, c.kabsmax)]
+
+
+def _restore(dw, st):
+    c = dw.cache
+    for t, s in zip((dw.K, dw.V, c.kbits, c.kmeta, c.kabsmax), st):
+        t.copy_(s)
+
+
+def _run(dws, order, dense, ws, with_list, append, one_by_one):
+    cfg, n, mb = dws[0].cfg, len(order), int(dws[0].wl.budgets.max())
+    rep = cfg.n_rep
+    pick = [dws[i] for i in order]
+    q = torch.stack([(d.q if i % 2 == 0 else -d.q).reshape(cfg.batch, -1, 128) for i, d in enumerate(pick)]).contiguous()
+    kn = torch.stack([d.k_new * (1 + i % 3) for i, d in enumerate(pick)]).contiguous() if append else None
+    vn = torch.stack([d.v_new for d in pick]).contiguous() if append else None
+    out = torch.zeros((n, cfg.units, rep, 128), dtype=torch.float32, device="cuda")
+    idx = torch.full((n, cfg.units, mb), -1, dtype=torch.int32, device="cuda") if with_list else None
+    cnt = torch.zeros((n, cfg.units), dtype=torch.int32, device="cuda") if with_list else None
+    calls = [slice(l, l + 1) for l in range(n)] if one_by_one else [slice(0, n)]
+    for c in calls:
+        B.decode_step_mixed(cfg, [d.cache for d in pick[c]], dense[c], q[c], kn[c] if append else None,
+                            vn[c] if append else None, dws[0].budgets, mb, out[c], idx[c] if with_list else None,
+                            cnt[c] if with_list else None, ws)
+    torch.cuda.synchronize()
+    return out, idx, cnt, [_state(d) for d in dws]
+
+
+CASES = [
+    # batch, query heads, kv heads, contexts, budgets, dtype, capacity, block tokens, group, index list, append, order of the layers, dense layers
+    (1, 8, 8, [1500], [160], F16, 1536, 0, 32, False, True, range(5), ()),
+    (2, 8, 2, [1500, 700], [160, 80], BF16, 1536, 0, 32, False, True, range(17), ()),       # more than one launch holds
+    (2, 6, 2, [2500, 33], [300, 40], F16, 2560, 0, 128, True, True, range(3), ()),          # index list, 3 heads per kv head
+    (1, 3, 3, [5000], [700], F16, 5056, 0, 32, True, True, range(2), ()),                   # units not a multiple of 8
+    (2, 16, 16, [1024, 1], [90, 1], BF16, 1088, 64, 32, True, True, range(4), ()),          # paged; a one-token sequence
+    (1, 8, 4, [1536], [100], F16, 1536, 0, 64, False, True, range(3), ()),                  # a full cache: nothing appended
+    (2, 4, 2, [0, 900], [50, 0], BF16, 960, 0, 32, True, False, range(4), ()),              # empty sequence, budget 0
+    (1, 8, 2, [1200], [130], BF16, 1280, 0, 32, False, True, (0, 1, 1, 2, 0), ()),          # a cache twice in one call
+    (1, 4, 2, [1200], [130], F16, 1280, 64, 32, True, True, (0, 0, 1), ()),
+    (2, 8, 2, [1500, 700], [160, 80], BF16, 1536, 0, 32, False, True, range(7), (0, 4)),    # dense layers in between
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("parts", [1, 2, 16])
+def test_layers_of_one_call_equal_single_layer_calls(case, parts):
+    """Contexts cross group, pair-block and range edges; the workspace holds one, two or 16 layers, and what lies
+    behind its first part is garbage.  Appended rows, packed caches and (with the list) selections must be the same,
+    outputs too up to the order of summation: at most 700 terms in binary32, |error| <= 700 * 2^-24 * max|v| (about
+    4.5) < 2e-4, far above what is seen."""
+    batch, hq, hkv, lens, buds, dtype, max_ctx, bt, group, with_list, append, order, dense_at = case
+    order = list(order)
+    dws = _layers(700, max(order) + 1, batch, hq, hkv, lens, buds, dtype, max_ctx, bt, group)
+    dense = [l in dense_at for l in range(len(order))]
+    cfg, mb = dws[0].cfg, max_ctx if dense_at else int(dws[0].wl.budgets.max())
+    one = B.workspace_bytes(cfg, mb)
+    start = [_state(d) for d in dws]
+    want = _run(dws, order, dense, B.make_workspace(cfg, mb, 1), with_list, append, True)
+    for d, s in zip(dws, start):
+        _restore(d, s)
+    ws = torch.full((one * parts,), 0x5A, dtype=torch.uint8, device="cuda")
+    ws[:one] = 0
+    got = _run(dws, order, dense, ws, with_list, append, False)
+    assert torch.isfinite(got[0]).all()
+    assert float((got[0] - want[0]).abs().max()) <= 2e-4
+    if with_list:
+        assert torch.equal(got[2], want[2])
+        assert torch.equal(got[1], want[1])
+    for a, b in zip(got[3], want[3]):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
+    # the scores the workspace shows are those of the call's last layer
+    if not dense_at:
+        ref = B.make_workspace(cfg, mb, 1)
+        for d, s in zip(dws, start):
+            _restore(d, s)
+        _run(dws, order, dense, ref, with_list, append, True)
+        a, b = (B.workspace_scores(cfg, mb, w) for w in (ws, ref))
+        for u in range(cfg.units):
+            n = min(lens[u // hkv] + (1 if append else 0), max_ctx)
+            assert torch.equal(a[u, :n], b[u, :n])
+
+
+def test_workspace_for_layers_follows_the_number_of_layers():
+    cfg = B.make_config(1, 8, 8, 4160)
+    one = B.workspace_bytes(cfg, 512)
+    assert [B.workspace_bytes_layers(cfg, 512, n) // one for n in (1, 2, 16, 40)] == [1, 2, 16, 16]
+    big = B.make_config(16, 64, 32, 131072)
+    assert B.workspace_bytes_layers(big, 512, 16) == B.workspace_bytes(big, 512)
