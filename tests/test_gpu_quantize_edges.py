@@ -1,0 +1,79 @@
+"""fier_quantize_keys where its decision threshold, its wavefront exchanges and its work split can go wrong: bit-exact."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2508_08256_amd import binding as B
+from paper_2508_08256_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+F16, BF16 = synth.F16, synth.BF16
+
+
+def _words(kind, rng, shape, dtype):
+    """uint16 words of finite values."""
+    top = 0x7BFF if dtype == F16 else 0x7F7F
+    sign = (rng.integers(0, 2, shape) << 15).astype(np.uint16)
+    if kind == "any":          # every finite bit pattern, subnormals and the largest included
+        return rng.integers(0, top + 1, shape).astype(np.uint16) | sign
+    if kind == "near":         # a channel's values within a few steps of each other: ranges of a few ulps, midpoints hit
+        base = rng.integers(8, top - 8, shape[:1] + (1,) + shape[2:])
+        return (base + rng.integers(-3, 4, shape)).astype(np.uint16) | sign[:, :1, :]
+    if kind == "zero-mid":     # +-m at the ends, +-0 and values far below m's last place around the midpoint at 0
+        m = rng.integers(1, top + 1, shape[:1] + (1,) + shape[2:])
+        pick = rng.integers(0, 6, shape)
+        small = np.where(pick < 2, 0, rng.integers(0, 1 << 15, shape) % (m + 1) // np.where(pick == 2, 1, 1 << rng.integers(1, 15, shape)))
+        w = np.where(pick == 5, m, small).astype(np.uint16) | sign
+        w[:, ::16, :] = m.astype(np.uint16)
+        w[:, 1::16, :] = m.astype(np.uint16) | 0x8000
+        return w
+    assert kind == "constant"
+    return np.broadcast_to(_words("any", rng, shape[:1] + (1,) + shape[2:], dtype), shape).copy()
+
+
+def _check(oracle, batch, heads, lens, max_ctx, dtype, g, kind, bt=0):
+    import gpu_util
+
+    rng = np.random.default_rng(hash((max_ctx, dtype, g, len(kind))) % 1000)
+    wl = synth.make_workload("edges", 3, batch, heads, heads, lens, [1] * batch, dtype, max_ctx=max_ctx, plant=False)
+    wl.K[:] = _words(kind, rng, wl.K.shape, dtype)
+    dw = gpu_util.PagedWorkload(wl, bt, g) if bt else gpu_util.DeviceWorkload(wl, g)
+    B.quantize_keys(dw.cfg, dw.cache)
+    torch.cuda.synchronize()
+    L = wl.unit_lens
+    bits_o, s_o, z_o = oracle.quantize(wl.K, L, g, dtype, 8)
+    bits, s, z = dw.cache.unpack()
+    amax = dw.cache.kabsmax.cpu().numpy().reshape(wl.units, 128)
+    for u in range(wl.units):
+        n = int(L[u])
+        ng = -(-n // g)
+        assert np.array_equal(s[u, :ng], s_o[u, :ng]) and np.array_equal(z[u, :ng], z_o[u, :ng])
+        bad = np.argwhere(bits[u, :n] != bits_o[u, :n])
+        assert len(bad) == 0, (kind, u, bad[:4], len(bad))
+        assert np.all(bits[u, n:-(-n // 64) * 64] == 0)
+        zf, sf = oracle.to_f32(z_o[u, :ng], dtype), oracle.to_f32(s_o[u, :ng], dtype)
+        with np.errstate(over="ignore"):  # the upper level of a range held at the top of the format
+            want = np.maximum(np.abs(zf), np.abs(zf + sf)).max(axis=0) if ng else np.zeros(128, np.float32)
+        assert np.array_equal(amax[u], want.astype(np.float32))
+
+
+@pytest.mark.parametrize("kind", ["any", "near", "zero-mid", "constant"])
+@pytest.mark.parametrize("g", [32, 64, 128, 256])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+def test_thresholds_and_partial_groups(oracle, dtype, g, kind):
+    """Lengths one short of, at and one past a group, a pair block and a workgroup's share, an empty and a one-token
+    sequence; values that put the decision threshold everywhere a 16-bit format can have it."""
+    lens = [0, 1, 31, 33, 63, 64, 65, g - 1, g, g + 1, 256, 257, 511, 1023, 1024]
+    _check(oracle, len(lens), 1, lens, 1024, dtype, g, kind)
+
+
+@pytest.mark.parametrize("dtype,g,bt", [(F16, 32, 64), (BF16, 128, 128), (BF16, 256, 256)])
+def test_paged_rows(oracle, dtype, g, bt):
+    _check(oracle, 3, 2, [700, 256, 1], 768, dtype, g, "any", bt)
+
+
+@pytest.mark.parametrize("dtype,g", [(F16, 32), (BF16, 64), (BF16, 128)])
+def test_two_blocks_per_wavefront(oracle, dtype, g):
+    """8224 pair blocks: the size from which a wavefront takes two of them in turn (four: the full-size tests)."""
+    _check(oracle, 2, 8, [32896, 20000], 32896, dtype, g, "any")
