@@ -47,10 +47,12 @@ def build(verbose: bool = False, prof: bool = False) -> str:
     flags = FLAGS + (["-DFIER_PROF_ENABLE", "-fgpu-rdc"] if prof else [])
     lib = os.path.join(HERE, "libfier_prof.so") if prof else LIB
     jobs = []
-    for part in range(4):  # the variants of the step's second kernel, the longest compilations, first
-        obj = os.path.join(objdir, "fier_step_%d.o" % part)
-        jobs.append(([hipcc] + flags + ["-DFIER_STEP_PART=%d" % part, "-c", os.path.join(CSRC, "fier_step.hip"), "-o", obj],
-                     obj))
+    # the variants of the step's two kernels, the longest compilations, in parts of their own and first
+    for name, parts in (("score", 2), ("step", 4)):
+        for part in range(parts):
+            obj = os.path.join(objdir, "fier_%s_%d.o" % (name, part))
+            jobs.append(([hipcc] + flags + ["-DFIER_%s_PART=%d" % (name.upper(), part), "-c",
+                                            os.path.join(CSRC, "fier_%s.hip" % name), "-o", obj], obj))
     for src in SOURCES + (["fier_prof.hip"] if prof else []):
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
         jobs.append(([hipcc] + flags + ["-c", os.path.join(CSRC, src), "-o", obj], obj))

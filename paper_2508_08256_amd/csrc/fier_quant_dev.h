@@ -186,58 +186,84 @@ __device__ __forceinline__ void append_finish(uint32_t* __restrict__ K, uint32_t
   }
 }
 
-template <int DT>
-__device__ __forceinline__ void append_row(uint32_t* __restrict__ K, uint32_t* __restrict__ V, const KvRows kv,
-                                           uint32_t* __restrict__ kbits, uint32_t* __restrict__ kmeta, int unit,
-                                           int L, int max_ctx, uint32_t kn, uint32_t vn, int lane, GroupCode& gc,
-                                           int& t0, int& ntok, uint4& mine) {
-  uint32_t rows[kG];
-  append_load_rows<DT>(K, kv, L, kn, lane, rows, t0, ntok);
-  append_finish<DT>(K, V, kv, kbits, kmeta, unit, L, max_ctx, kn, vn, lane, rows, t0, ntok, gc, mine);
+// The same for groups of g = 32 ns tokens (ns in {2, 4, 8}), by a workgroup of four wavefronts: wavefront w takes the
+// group's 32-token chunks w and w + 4 (the second one only at g = 256).  Latency bound, a chain of dependent steps at the
+// start of every decode step: one wavefront that read the group twice, 32 rows at a time, made the first kernel of the
+// step 15.8 us at 16 units x 20k tokens and g = 128, and two such layers per call 42.2 us; this way they take 37.5.
+//
+// The rows of chunk c of the tail group (t0 its first token, ntok tokens with the new one), zeros past the end.
+__device__ __forceinline__ void append_load_chunk(const uint32_t* __restrict__ K, const KvRows kv, int t0, int ntok, int c,
+                                                  uint32_t kn, int lane, uint32_t (&rows)[kG]) {
+  const uint32_t* src = K + kv.row(t0) * (kD / 2) + lane;  // a group lies inside one block
+  const int first = c * kG;
+#pragma unroll
+  for (int t = 0; t < kG; ++t) {
+    // rows before the new one come from memory (never the row the append writes)
+    const uint32_t r = first + t < ntok - 1 ? src[(size_t)(first + t) * (kD / 2)] : 0u;
+    rows[t] = first + t == ntok - 1 ? kn : r;
+  }
 }
 
-// The same for groups of g = 32 ns tokens (ns in {2, 4, 8}): the tail group (up to g rows) is read twice, 32 rows at a
-// time.  Every pair block of the group that holds a token gets its code words rewritten; on_block(pb, mine, gs)
-// is called once per such block with the calling lane's code word of token t0 + 64 pb + lane (zero if absent) and the
-// group's scale.
-template <int DT, class OnBlock>
+// rows: chunk `wave`, from append_load_chunk.  xch: 256 float4 in LDS.  Every pair block of the group that holds a token
+// gets its code words rewritten; on_chunk(c, mine, gs) is called for each of the wavefront's chunks that holds a token,
+// `mine` the code word of token t0 + 64 (c >> 1) + lane in the lanes of the chunk's half.  Called by all four wavefronts.
+template <int DT, class OnChunk>
 __device__ __forceinline__ GroupScale append_row_long(uint32_t* __restrict__ K, uint32_t* __restrict__ V,
                                                       const KvRows kv, uint32_t* __restrict__ kbits,
-                                                      uint32_t* __restrict__ kmeta,
-                                                      int unit, int L, int max_ctx, int ns, uint32_t kn, uint32_t vn,
-                                                      int lane, int& t0, int& ntok, OnBlock on_block) {
+                                                      uint32_t* __restrict__ kmeta, int unit, int L, int max_ctx, int ns,
+                                                      uint32_t kn, uint32_t vn, int lane, int wave,
+                                                      uint32_t (&rows)[kG], float4* xch, OnChunk on_chunk) {
   const int g = kG * ns;
   const int n_groups = max_ctx / g;
-  K[kv.row(L) * (kD / 2) + lane] = kn;
-  V[kv.row(L) * (kD / 2) + lane] = vn;
-  const int Gi = L / g;
-  t0 = Gi * g;
-  ntok = L - t0 + 1;
-  const int n_present = ntok;
-  const uint32_t* src = K + kv.row(t0) * (kD / 2) + lane;  // a group lies inside one block
-  // rows before the new one come from memory (never the row written above), the new one from registers
-  auto row_at = [&](int t) { return t == n_present - 1 ? kn : src[(size_t)t * (kD / 2)]; };
-  const GroupScale gs = long_group_scale<DT>(row_at, ntok);
-  uint2* mdst = reinterpret_cast<uint2*>(kmeta + ((size_t)unit * n_groups + Gi) * kD) + lane;
-  *mdst = make_uint2(gs.s0 | (gs.z0 << 16), gs.s1 | (gs.z1 << 16));
-  uint4* bdst = reinterpret_cast<uint4*>(kbits) + (size_t)unit * max_ctx + t0;
-  for (int pb = 0; pb * kPair < ntok; ++pb) {
-    uint4 mine = make_uint4(0, 0, 0, 0);
+  const int Gi = L / g, t0 = Gi * g, ntok = L - t0 + 1;
+  if (wave == 0) {
+    K[kv.row(L) * (kD / 2) + lane] = kn;
+    V[kv.row(L) * (kD / 2) + lane] = vn;
+  }
+  // the number of tokens is the same in every lane: a row that is not there costs a scalar branch
+  MinMax m = {INFINITY, -INFINITY, INFINITY, -INFINITY};
+  const int n_first = ntok - wave * kG;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int c0 = pb * kPair + h * kG;
-      int nt = ntok - c0;
-      nt = nt > kG ? kG : nt;
-      if (nt > 0) {
-        uint32_t rows[kG];
+  for (int t = 0; t < kG; ++t)
+    if (t < n_first) minmax_update<DT>(m, rows[t], true);
+  const int n_second = ntok - (wave + 4) * kG;
+  if (n_second > 0) {  // eight at a time: they are read again to be coded, the registers hold the first chunk
+    const uint32_t* src = K + kv.row(t0) * (kD / 2) + lane;
+    const int first = (wave + 4) * kG;
+#pragma unroll 1
+    for (int t1 = 0; t1 < kG; t1 += 8) {
+      uint32_t r[8];
 #pragma unroll
-        for (int t = 0; t < kG; ++t) rows[t] = row_at(c0 + t < ntok ? c0 + t : 0);
-        uint32_t b0, b1;
-        code_rows<DT>(rows, nt, gs, lane, h * kG, mine, b0, b1);
-      }
+      for (int t = 0; t < 8; ++t) r[t] = first + t1 + t < ntok - 1 ? src[(size_t)(first + t1 + t) * (kD / 2)] : kn;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) minmax_update<DT>(m, r[t], true);  // past the end: the new row once more
     }
-    bdst[pb * kPair + lane] = mine;
-    on_block(pb, mine, gs);
+  }
+  xch[wave * 64 + lane] = make_float4(m.mn0, m.mx0, m.mn1, m.mx1);
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float4 o = xch[w * 64 + lane];
+    m.mn0 = fminf(m.mn0, o.x), m.mx0 = fmaxf(m.mx0, o.y), m.mn1 = fminf(m.mn1, o.z), m.mx1 = fmaxf(m.mx1, o.w);
+  }
+  const GroupScale gs = group_scale<DT>(m);
+  if (wave == 0) {
+    uint2* mdst = reinterpret_cast<uint2*>(kmeta + ((size_t)unit * n_groups + Gi) * kD) + lane;
+    *mdst = make_uint2(gs.s0 | (gs.z0 << 16), gs.s1 | (gs.z1 << 16));
+  }
+  uint4* bdst = reinterpret_cast<uint4*>(kbits) + (size_t)unit * max_ctx + t0;
+#pragma unroll 1
+  for (int c = wave;;) {
+    int nt = ntok - c * kG;
+    nt = nt > kG ? kG : nt;
+    uint4 mine = make_uint4(0, 0, 0, 0);
+    uint32_t b0, b1;
+    code_rows<DT>(rows, nt, gs, lane, (c & 1) * kG, mine, b0, b1);
+    if (c < ns && (c >> 1) * kPair < ntok && lane >> 5 == (c & 1)) bdst[(c >> 1) * kPair + lane] = mine;
+    if (nt > 0) on_chunk(c, mine, gs);
+    c += 4;
+    if (c >= ns) break;
+    append_load_chunk(K, kv, t0, ntok, c, kn, lane, rows);
   }
   return gs;
 }

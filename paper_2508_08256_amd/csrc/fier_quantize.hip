@@ -425,33 +425,40 @@ __global__ void zero_absmax_kernel(float* __restrict__ kabsmax, int n) {
   if (i < n) kabsmax[i] = 0.f;
 }
 
-// grid (units), block 64: one wavefront per unit.  Writes the new K/V rows at position L = seq_len and
+// grid (units), block 64 (g = 32) or 256 (longer groups).  Writes the new K/V rows at position L = seq_len and
 // re-derives the group that row falls in from the rows present (the new row comes from registers).
-template <int DT>
-__global__ __launch_bounds__(64) void append_kernel(uint32_t* __restrict__ K, uint32_t* __restrict__ V,
-                                                    uint32_t* __restrict__ kbits, uint32_t* __restrict__ kmeta,
-                                                    float* __restrict__ kabsmax,
-                                                    const int32_t* __restrict__ seq_lens,
-                                                    const uint32_t* __restrict__ k_new,
-                                                    const uint32_t* __restrict__ v_new, int n_kv_heads, int max_ctx,
-                                                    int ns, KvLayout lay) {
-  const int lane = threadIdx.x;
+template <int DT, bool LONG>
+__global__ __launch_bounds__(LONG ? 256 : 64) void append_kernel(uint32_t* __restrict__ K, uint32_t* __restrict__ V,
+                                                                 uint32_t* __restrict__ kbits,
+                                                                 uint32_t* __restrict__ kmeta,
+                                                                 float* __restrict__ kabsmax,
+                                                                 const int32_t* __restrict__ seq_lens,
+                                                                 const uint32_t* __restrict__ k_new,
+                                                                 const uint32_t* __restrict__ v_new, int n_kv_heads,
+                                                                 int max_ctx, int ns, KvLayout lay) {
+  const int lane = threadIdx.x & 63;
+  const int wave = LONG ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int unit = blockIdx.x;
   const int L = seq_lens[unit / n_kv_heads];
   if (L < 0 || L >= max_ctx) return;
   const uint32_t kn = k_new[(size_t)unit * (kD / 2) + lane];
   const uint32_t vn = v_new[(size_t)unit * (kD / 2) + lane];
-  int t0, ntok;
   float amax_lo, amax_hi;
-  if (ns == 1) {
+  uint32_t rows[kG];
+  if constexpr (!LONG) {
     GroupCode gc;
     uint4 mine;
-    append_row<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, kn, vn, lane, gc, t0, ntok, mine);
+    int t0, ntok;
+    append_load_rows<DT>(K, lay.rows_of(unit), L, kn, lane, rows, t0, ntok);
+    append_finish<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, kn, vn, lane, rows, t0, ntok, gc, mine);
     amax_lo = gc.amax_lo, amax_hi = gc.amax_hi;
   } else {
+    __shared__ float4 xch[4 * 64];
+    const int t0 = L / (kG * ns) * (kG * ns);
+    append_load_chunk(K, lay.rows_of(unit), t0, L - t0 + 1, wave, kn, lane, rows);
     const GroupScale gs = append_row_long<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, ns, kn, vn, lane,
-                                              t0, ntok,
-                                              [](int, const uint4&, const GroupScale&) {});
+                                              wave, rows, xch, [](int, const uint4&, const GroupScale&) {});
+    if (wave != 0) return;
     amax_lo = fmaxf(fabsf(gs.zf0), fabsf(gs.zf0 + gs.sf0));
     amax_hi = fmaxf(fabsf(gs.zf1), fabsf(gs.zf1 + gs.sf1));
   }
@@ -503,14 +510,18 @@ hipError_t launch_append(int dtype, KvLayout lay, void* K, void* V, uint32_t* kb
                          const int32_t* seq_lens, const void* k_new, const void* v_new, int units, int n_kv_heads,
                          int max_ctx, int group_size, hipStream_t st) {
   const int ns = group_size / kG;
-  if (dtype == DT_F16)
-    append_kernel<DT_F16><<<units, 64, 0, st>>>((uint32_t*)K, (uint32_t*)V, kbits, kmeta, kabsmax, seq_lens,
-                                                (const uint32_t*)k_new, (const uint32_t*)v_new, n_kv_heads, max_ctx,
-                                                ns, lay);
-  else
-    append_kernel<DT_BF16><<<units, 64, 0, st>>>((uint32_t*)K, (uint32_t*)V, kbits, kmeta, kabsmax, seq_lens,
-                                                 (const uint32_t*)k_new, (const uint32_t*)v_new, n_kv_heads, max_ctx,
-                                                 ns, lay);
+#define FIER_APPEND(DT, LONG)                                                                                       \
+  append_kernel<DT, LONG><<<units, LONG ? 256 : 64, 0, st>>>((uint32_t*)K, (uint32_t*)V, kbits, kmeta, kabsmax,     \
+                                                             seq_lens, (const uint32_t*)k_new,                      \
+                                                             (const uint32_t*)v_new, n_kv_heads, max_ctx, ns, lay)
+  if (dtype == DT_F16) {
+    if (ns == 1) FIER_APPEND(DT_F16, false);
+    else FIER_APPEND(DT_F16, true);
+  } else {
+    if (ns == 1) FIER_APPEND(DT_BF16, false);
+    else FIER_APPEND(DT_BF16, true);
+  }
+#undef FIER_APPEND
   return hipGetLastError();
 }
 

@@ -78,13 +78,16 @@ __device__ __forceinline__ uint32_t row_allmax_u32(uint32_t x) {
 // scoring and histogramming are one pass.  The workgroup's LDS histogram is added to the unit's histogram in
 // memory with device atomics and the workgroup is done: nobody waits or counts arrivals here; the threshold
 // kernel reads the merged histogram (and clears it for the next call).
-// The extra workgroup of a unit performs the decode-stage append (Sec. 3.1) when k_new is given: one wavefront
+// The extra workgroup of a unit performs the decode-stage append (Sec. 3.1) when k_new is given: it (one wavefront, four for
+// groups longer than 32 tokens)
 // writes the new K/V rows, re-quantizes the group the row falls in and scores that group's tokens straight from
 // its registers; the other workgroups leave those tokens alone.  The bound R uses the absmax of before the
 // append (every workgroup must bin with the same R); the new group's contribution is handed to the last kernel
 // of the step through `newmax`.  A score outside [-R, R] simply lands in the outermost bin.
-template <int DT, int NREP, bool HIST, bool STREAM, class LAYERS>
-__global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const uint4* kmeta,
+// LONG: quantization groups longer than 32 tokens.  (Separate variants: the long groups' append takes more registers, and
+// in one kernel with the other cost the 32-token groups their fifth workgroup per CU: 56 -> 60 us at 32 units x 128k.)
+template <int DT, int NREP, bool HIST, bool STREAM, bool LONG, class LAYERS>
+__global__ __launch_bounds__(256, HIST && LONG ? (NREP <= 6 ? 5 : 4) : 1) void score_kernel(const uint4* kbits, const uint4* kmeta,
                                                     const float* __restrict__ kabsmax, const uint16_t* __restrict__ q,
                                                     const int32_t* __restrict__ seq_lens, int extra,
                                                     float* __restrict__ scores, UnitCtl* __restrict__ ctl,
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
                                                     int max_budget, uint32_t* __restrict__ K, uint32_t* __restrict__ V,
                                                     const uint32_t* __restrict__ k_new,
                                                     const uint32_t* __restrict__ v_new, float* __restrict__ newmax,
-                                                    int n_kv_heads, int max_ctx, int bpw, int gshift, int n_x, KvLayout lay,
+                                                    int n_kv_heads, int max_ctx, int bpw, int group_shift, int n_x, KvLayout lay,
                                                     const LAYERS lb) {
   __shared__ uint32_t lhist[HIST ? kSelBins : 1];
   __shared__ __attribute__((aligned(16))) unsigned char a_lds[4 * kAWave];
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
   uint32_t kn = 0, vn = 0, qpair[NREP];
 #pragma unroll
   for (int r = 0; r < NREP; ++r) qpair[r] = 0;
-  if (append_wg && wave == 0 && k_new != nullptr) {
+  if (append_wg && (wave == 0 || LONG) && k_new != nullptr) {
     kn = k_new[(size_t)unit * (kD / 2) + lane];
     vn = v_new[(size_t)unit * (kD / 2) + lane];
 #pragma unroll
@@ -151,6 +154,7 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
   const bool app = HIST && k_new != nullptr && Lold < max_ctx;  // this unit receives a new row in this step
   int L = HIST ? Lold + (app ? 1 : 0) : Lold + extra;
   L = L > max_ctx ? max_ctx : L;
+  const int gshift = LONG ? group_shift : 0;
   const int gsize = kG << gshift;  // tokens per quantization group: 32, 64, 128 or 256
   const int tail_start = app ? (Lold / gsize) * gsize : L;  // tokens from here on are scored by the appending wave
   if (append_wg) {
@@ -159,12 +163,17 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
     // range 0 of a unit always runs so that an empty unit still gets its control block written
     if (range * (4 * kPair) * bpw >= L && !(HIST && range == 0)) return;
   }
-  // ... and the rows of the group the new token falls in as soon as the length is known (g = 32; the longer groups
-  // read theirs in two passes inside append_row_long)
+  // ... and the rows of the group the new token falls in as soon as the length is known (longer groups than 32: each of
+  // the four wavefronts its chunk)
   uint32_t tail_rows[kG];
   int tail_t0 = 0, tail_ntok = 0;
-  if (HIST && append_wg && wave == 0 && gshift == 0)
+  if (HIST && !LONG && append_wg && wave == 0)
     append_load_rows<DT>(K, lay.rows_of(unit), Lold, kn, lane, tail_rows, tail_t0, tail_ntok);
+  if (HIST && LONG && append_wg) {
+    tail_t0 = tail_start;
+    tail_ntok = Lold - tail_start + 1;
+    append_load_chunk(K, lay.rows_of(unit), tail_t0, tail_ntok, wave, kn, lane, tail_rows);
+  }
   const int n_groups = max_ctx / gsize;
   const int row = lane >> 4, n = lane & 15;
   const int gsel = row >> 1;  // the group of the pair block whose (s, z) this row of lanes holds
@@ -240,7 +249,7 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
   FIER_PROF(1, HIST && unit == 0 && range == 3)
   if (append_wg) {
     if constexpr (HIST) {
-      if (wave == 0 && gshift == 0) {  // lane = channel pair (2 lane, 2 lane + 1)
+      if (!LONG && wave == 0) {  // lane = channel pair (2 lane, 2 lane + 1)
         GroupCode gc;
         const int t0 = tail_t0, ntok = tail_ntok;
         uint4 mine;  // lane t < 32: the code word of token t0 + t
@@ -281,24 +290,25 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
           scores[(size_t)unit * max_ctx + t0 + lane] = sc;
           atomicAdd(&lhist[sel_bin(sc, R, hscale, kSelBins)], 1u);
         }
-      } else if (wave == 0) {
-        // Groups of 64, 128 or 256 tokens: the tail group is re-derived 32 rows at a time; each of its pair blocks
-        // is scored as soon as its code words exist, lane = token, the 128 weights q_c s_c read from LDS in the
-        // order of the code word's bits (bit i of word d is channel 64 (d & 1) + 2 i + (d >> 1)).
-        float* wl = reinterpret_cast<float*>(a_lds);  // 128 floats; this workgroup scores nothing else
+      } else if constexpr (LONG) {
+        // Groups of 64, 128 or 256 tokens: all four wavefronts, 32 tokens at a time; a chunk is scored as soon as its
+        // code words exist, lane = token, the 128 weights q_c s_c read from LDS in the order of the code word's bits
+        // (bit i of word d is channel 64 (d & 1) + 2 i + (d >> 1)).
+        static_assert(kAWave >= 512 && sizeof(lscore) >= 4 * 64 * sizeof(float4), "scratch of the appending workgroup");
+        float* wl = reinterpret_cast<float*>(a_lds + wave * kAWave);  // 128 floats; this workgroup scores nothing else
         float q0 = 0.f, q1 = 0.f;
 #pragma unroll
         for (int r = 0; r < NREP; ++r) {
           q0 += lo16f<DT>(qpair[r]);
           q1 += hi16f<DT>(qpair[r]);
         }
-        int t0, ntok;
         float base = 0.f;
         bool have_w = false;
+        const int t0 = tail_t0, ntok = tail_ntok;
         const GroupScale gs = append_row_long<DT>(
             K, V, lay.rows_of(unit), const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kbits)),
             const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kmeta)), unit, Lold, max_ctx, 1 << gshift, kn, vn, lane,
-            t0, ntok, [&](int pb, const uint4& mine, const GroupScale& g) {
+            wave, tail_rows, reinterpret_cast<float4*>(lscore), [&](int c, const uint4& mine, const GroupScale& g) {
               if (!have_w) {
                 have_w = true;
                 // channel 2 lane is bit (lane & 31) of word lane >> 5, channel 2 lane + 1 of word 2 + (lane >> 5)
@@ -311,7 +321,7 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
               const uint32_t wd[4] = {mine.x, mine.y, mine.z, mine.w};
               float acc = 0.f;
 #pragma unroll
-              for (int d = 0; d < 4; ++d)
+              for (int d = 0; d < 4; ++d) {
 #pragma unroll
                 for (int i = 0; i < 32; i += 4) {
                   const float4 w4 = *reinterpret_cast<const float4*>(wl + 32 * d + i);
@@ -320,15 +330,19 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
                   acc += (wd[d] >> (i + 2) & 1u) ? w4.z : 0.f;
                   acc += (wd[d] >> (i + 3) & 1u) ? w4.w : 0.f;
                 }
-              const int tok = pb * kPair + lane;  // within the group
-              if (tok < ntok) {
+                asm volatile("" : "+v"(acc));  // a word's weights at a time: all 128 at once would not fit the registers
+              }
+              const int tok = (c >> 1) * kPair + lane;  // within the group
+              if (tok < ntok && lane >> 5 == (c & 1)) {
                 const float sc = acc + base;
                 scores[(size_t)unit * max_ctx + t0 + tok] = sc;
                 atomicAdd(&lhist[sel_bin(sc, R, hscale, kSelBins)], 1u);
               }
             });
-        newmax[(size_t)unit * kD + 2 * lane] = fmaxf(fabsf(gs.zf0), fabsf(gs.zf0 + gs.sf0));
-        newmax[(size_t)unit * kD + 2 * lane + 1] = fmaxf(fabsf(gs.zf1), fabsf(gs.zf1 + gs.sf1));
+        if (wave == 0) {
+          newmax[(size_t)unit * kD + 2 * lane] = fmaxf(fabsf(gs.zf0), fabsf(gs.zf0 + gs.sf0));
+          newmax[(size_t)unit * kD + 2 * lane + 1] = fmaxf(fabsf(gs.zf1), fabsf(gs.zf1 + gs.sf1));
+        }
       }
     }
   }
@@ -501,8 +515,9 @@ __global__ __launch_bounds__(256) void score_kernel(const uint4* kbits, const ui
   }
 }
 
+// Compiled in parts, FIER_SCORE_PART = DT, next to the rest of this file.
 template <int DT, bool HIST>
-static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta, const float* kabsmax,
+hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta, const float* kabsmax,
                                   const void* q, const int32_t* seq_lens, int extra, float* scores,
                                   const StepBuffers* sb, const int32_t* budgets, int max_budget, void* K, void* V,
                                   const void* k_new, const void* v_new, int units, int n_kv_heads, int max_ctx,
@@ -538,20 +553,26 @@ static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits
       sb ? sb->ctl : nullptr, sb ? sb->hist : nullptr, budgets, max_budget, (uint32_t*)K, (uint32_t*)V,            \
       (const uint32_t*)k_new, (const uint32_t*)v_new, sb ? sb->newmax : nullptr, n_kv_heads, max_ctx, bpw, gshift, \
       n_x, lay
+  auto launch = [&](auto long_tag, auto rep_tag) {
+    constexpr bool LONG = decltype(long_tag)::value;  // without HIST nothing is appended: any group size
+    constexpr int R = decltype(rep_tag)::value;
+    if constexpr (HIST)
+      if (lb.n > 1) {
+        if (stream) score_kernel<DT, R, HIST, true, LONG, LayerBatch><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, lb);
+        else score_kernel<DT, R, HIST, false, LONG, LayerBatch><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, lb);
+        return;
+      }
+    if (stream) score_kernel<DT, R, HIST, true, LONG, OneLayer><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, OneLayer());
+    else score_kernel<DT, R, HIST, false, LONG, OneLayer><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, OneLayer());
+  };
 #define FIER_SCORE_CASE(R)                                                                                         \
   case R:                                                                                                          \
-    if constexpr (HIST)                                                                                            \
-      if (lb.n > 1) {                                                                                              \
-        if (stream)                                                                                                \
-          score_kernel<DT, R, HIST, true, LayerBatch><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, lb);                  \
-        else                                                                                                       \
-          score_kernel<DT, R, HIST, false, LayerBatch><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, lb);                 \
-        break;                                                                                                     \
-      }                                                                                                            \
-    if (stream)                                                                                                    \
-      score_kernel<DT, R, HIST, true, OneLayer><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, OneLayer());                \
-    else                                                                                                           \
-      score_kernel<DT, R, HIST, false, OneLayer><<<grid, 256, 0, st>>>(FIER_SCORE_ARGS, OneLayer());               \
+    if constexpr (HIST) {                                                                                          \
+      if (gshift) launch(std::true_type(), std::integral_constant<int, R>());                                      \
+      else launch(std::false_type(), std::integral_constant<int, R>());                                            \
+    } else {                                                                                                       \
+      launch(std::true_type(), std::integral_constant<int, R>());                                                  \
+    }                                                                                                              \
     break;
   switch (n_rep) {
     FIER_SCORE_CASE(1)
@@ -569,6 +590,20 @@ static hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits
 #undef FIER_SCORE_ARGS
   return hipGetLastError();
 }
+
+#define FIER_SCORE_INSTANCE(WORD, DT, HIST)                                                                          \
+  WORD template hipError_t launch_score_dt<DT, HIST>(                                                               \
+      KvLayout, int, const uint32_t*, const uint32_t*, const float*, const void*, const int32_t*, int, float*,      \
+      const StepBuffers*, const int32_t*, int, void*, void*, const void*, const void*, int, int, int, int,          \
+      const LayerBatch&, hipStream_t);
+#ifdef FIER_SCORE_PART
+FIER_SCORE_INSTANCE(, FIER_SCORE_PART, true)
+FIER_SCORE_INSTANCE(, FIER_SCORE_PART, false)
+#else
+FIER_SCORE_INSTANCE(extern, DT_F16, true)
+FIER_SCORE_INSTANCE(extern, DT_F16, false)
+FIER_SCORE_INSTANCE(extern, DT_BF16, true)
+FIER_SCORE_INSTANCE(extern, DT_BF16, false)
 
 hipError_t launch_score(int dtype, KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta, const float* kabsmax,
                         const void* q, const int32_t* seq_lens, int extra, float* scores, const StepBuffers* sb,
@@ -588,5 +623,6 @@ hipError_t launch_score(int dtype, KvLayout lay, int n_rep, const uint32_t* kbit
   return launch_score_dt<DT_BF16, false>(lay, n_rep, kbits, kmeta, kabsmax, q, seq_lens, extra, scores, nullptr, nullptr, 0,
                                          nullptr, nullptr, nullptr, nullptr, units, n_kv_heads, max_ctx, group_size, lb, st);
 }
+#endif  // FIER_SCORE_PART
 
 }  // namespace fier

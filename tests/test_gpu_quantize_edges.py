@@ -77,3 +77,38 @@ def test_paged_rows(oracle, dtype, g, bt):
 def test_two_blocks_per_wavefront(oracle, dtype, g):
     """8224 pair blocks: the size from which a wavefront takes two of them in turn (four: the full-size tests)."""
     _check(oracle, 2, 8, [32896, 20000], 32896, dtype, g, "any")
+
+
+@pytest.mark.parametrize("g", [32, 64, 128, 256])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("fused", [False, True])
+def test_append_at_every_chunk_edge(dtype, g, fused):
+    """The row joins an empty cache, a group's first, middle and last 32-token chunk, a fresh group: afterwards rows and
+    packed cache are those of a bulk quantization of the longer prefix, in the append call and in the fused step."""
+    import gpu_util
+
+    lens = sorted({0, 1, 31, 32, 33, 63, 64, 95, 96, 127, 128, 159, 160, 191, 192, 223, 224, 255, 256, 300, g - 1, g, 511})
+    rng = np.random.default_rng(g + dtype)
+    wl = synth.make_workload("app", 5, len(lens), 2, 1, lens, [min(20, n + 1) for n in lens], dtype, max_ctx=512, plant=False)
+    wl.K[:] = _words("any" if not fused else "near", rng, wl.K.shape, dtype)
+    dw, ref = gpu_util.DeviceWorkload(wl, g), gpu_util.DeviceWorkload(wl, g)
+    B.quantize_keys(dw.cfg, dw.cache)
+    if fused:
+        out = torch.zeros((1, wl.units, 2, 128), dtype=torch.float32, device="cuda")
+        B.decode_step(dw.cfg, [dw.cache], dw.q[None].contiguous(), dw.k_new[None].contiguous(),
+                      dw.v_new[None].contiguous(), dw.budgets, 20, out, None, None, dw.workspace(20))
+    else:
+        B.append_key(dw.cfg, dw.cache, dw.k_new, dw.v_new)
+    for u, n in enumerate(lens):
+        ref.K[u, n] = ref.k_new.reshape(wl.units, 128)[u]
+        ref.V[u, n] = ref.v_new.reshape(wl.units, 128)[u]
+    ref.seq_lens.add_(1)
+    B.quantize_keys(ref.cfg, ref.cache)
+    torch.cuda.synchronize()
+    assert torch.equal(dw.K.view(torch.int16), ref.K.view(torch.int16))
+    assert torch.equal(dw.V.view(torch.int16), ref.V.view(torch.int16))
+    a, b = dw.cache.unpack(), ref.cache.unpack()
+    for u, n in enumerate(lens):
+        m, ng = -(-(n + 1) // 64) * 64, -(-(n + 1) // g)
+        assert np.array_equal(a[0][u, :m], b[0][u, :m]), (u, n)
+        assert np.array_equal(a[1][u, :ng], b[1][u, :ng]) and np.array_equal(a[2][u, :ng], b[2][u, :ng]), (u, n)
