@@ -78,10 +78,9 @@ __device__ __forceinline__ uint32_t row_allmax_u32(uint32_t x) {
 // scoring and histogramming are one pass.  The workgroup's LDS histogram is added to the unit's histogram in
 // memory with device atomics and the workgroup is done: nobody waits or counts arrivals here; the threshold
 // kernel reads the merged histogram (and clears it for the next call).
-// The extra workgroup of a unit performs the decode-stage append (Sec. 3.1) when k_new is given: it (one wavefront, four for
-// groups longer than 32 tokens)
-// writes the new K/V rows, re-quantizes the group the row falls in and scores that group's tokens straight from
-// its registers; the other workgroups leave those tokens alone.  The bound R uses the absmax of before the
+// The extra workgroup of a unit performs the decode-stage append (Sec. 3.1) when k_new is given: one wavefront (four
+// for groups longer than 32 tokens) writes the new K/V rows, re-quantizes the group the row falls in and scores that
+// group's tokens straight from its registers; the other workgroups leave those tokens alone.  The bound R uses the absmax of before the
 // append (every workgroup must bin with the same R); the new group's contribution is handed to the last kernel
 // of the step through `newmax`.  A score outside [-R, R] simply lands in the outermost bin.
 // LONG: quantization groups longer than 32 tokens.  (Separate variants: the long groups' append takes more registers, and
