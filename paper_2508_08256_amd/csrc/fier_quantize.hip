@@ -162,6 +162,10 @@ __device__ __forceinline__ int code_threshold(float z, float s) {
 // What the coding pass needs of a row's dword: operands of min / max, and a word whose sign bits say "below threshold".
 // fp16: the packed half-precision instructions on the values themselves (exact: a min / max picks an input, and a sum
 // rounds to a value of the exact sum's sign, denormals included).  bf16 has none: integer ones on the ordered keys.
+//   min / max go down a lane's tokens; for fp16 they are written as the instruction, because the builtin adds a quieting
+// of signalling NaNs to every operand.  The compiler does not count such a statement as a vector instruction when it
+// places the two wait states that a permlane swap needs after a write of its operands: settle() goes between the two, and
+// the minima and maxima between swaps (cross_min / cross_max) are the builtin.
 template <int DT>
 struct Pair16 {
   static __device__ __forceinline__ uint32_t prepare(uint32_t w) {
@@ -170,7 +174,7 @@ struct Pair16 {
   static __device__ __forceinline__ uint32_t words(uint32_t p) { return prepare(p); }  // the map is its own inverse
   static __device__ __forceinline__ uint32_t min(uint32_t a, uint32_t b) {
     if constexpr (DT == DT_F16) {
-      uint32_t d;  // as the instruction: the builtin adds a quieting of signalling NaNs to every operand
+      uint32_t d;
       asm("v_pk_min_f16 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
       return d;
     } else {
@@ -185,6 +189,22 @@ struct Pair16 {
     } else {
       return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(short2_t, a), __builtin_bit_cast(short2_t, b)));
     }
+  }
+  static __device__ __forceinline__ void settle(uint32_t (&mn)[4], uint32_t (&mx)[4]) {
+    if constexpr (DT == DT_F16)
+      asm volatile("s_nop 1" : "+v"(mn[0]), "+v"(mn[1]), "+v"(mn[2]), "+v"(mn[3]), "+v"(mx[0]), "+v"(mx[1]), "+v"(mx[2]), "+v"(mx[3]));
+  }
+  static __device__ __forceinline__ uint32_t cross_min(uint32_t a, uint32_t b) {
+    if constexpr (DT == DT_F16)
+      return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(half2_t, a), __builtin_bit_cast(half2_t, b)));
+    else
+      return min(a, b);
+  }
+  static __device__ __forceinline__ uint32_t cross_max(uint32_t a, uint32_t b) {
+    if constexpr (DT == DT_F16)
+      return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(half2_t, a), __builtin_bit_cast(half2_t, b)));
+    else
+      return max(a, b);
   }
   // fp16: the negated threshold, +0 for a threshold of -0 (then -0 and +0 both add up to +0: not below); bf16: its key
   static __device__ __forceinline__ uint32_t threshold(float z0, float s0, float z1, float s1) {
@@ -301,17 +321,18 @@ __global__ __launch_bounds__(256, 4) void quantize_kernel(const uint32_t* __rest
           mx[w] = i ? P16::max(mx[w], v[w]) : v[w];
         }
       }
+      P16::settle(mn, mx);
       // rows 0 | 1 and 2 | 3 together: even rows keep the lane's dwords 0, 1, odd rows dwords 2, 3
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
         const u32x2_t a = swap16(mn[w], mn[w + 2]), b = swap16(mx[w], mx[w + 2]);
-        mn[w] = P16::min(a[0], a[1]);
-        mx[w] = P16::max(b[0], b[1]);
+        mn[w] = P16::cross_min(a[0], a[1]);
+        mx[w] = P16::cross_max(b[0], b[1]);
       }
       if constexpr (NS >= 2) {  // all four rows: rows 0, 1 keep the first of these, rows 2, 3 the second
         const u32x2_t a = swap32(mn[0], mn[1]), b = swap32(mx[0], mx[1]);
-        mn[0] = P16::min(a[0], a[1]);
-        mx[0] = P16::max(b[0], b[1]);
+        mn[0] = P16::cross_min(a[0], a[1]);
+        mx[0] = P16::cross_max(b[0], b[1]);
       }
     }
     if constexpr (NS >= 4) {
@@ -322,8 +343,8 @@ __global__ __launch_bounds__(256, 4) void quantize_kernel(const uint32_t* __rest
 #pragma unroll
         for (int k = 1; k < kWavesPerGroup; ++k) {
           const uint2 o = xch[it & 1][first + ((wave + k) & (kWavesPerGroup - 1))][lane];
-          mn[0] = P16::min(mn[0], o.x);
-          mx[0] = P16::max(mx[0], o.y);
+          mn[0] = P16::cross_min(mn[0], o.x);
+          mx[0] = P16::cross_max(mx[0], o.y);
         }
       }
     }

@@ -1,0 +1,100 @@
+"""Properties of the compiled kernels that no result shows reliably: read from the gfx950 code objects in libfier.so."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2508_08256_amd import binding as B
+from paper_2508_08256_amd import build
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+def _sections(elf):
+    shoff = struct.unpack_from("<Q", elf, 0x28)[0]
+    size, n, names = struct.unpack_from("<HHH", elf, 0x3A)
+    sec = [struct.unpack_from("<IIQQQQ", elf, shoff + i * size) for i in range(n)]
+    text = lambda at: elf[at:elf.index(b"\0", at)].decode()  # noqa: E731
+    return {text(sec[names][4] + s[0]): elf[s[4]:s[4] + s[5]] for s in sec}
+
+
+def _code_objects(lib):
+    """The gfx950 ELF images of a library: one offload bundle per translation unit."""
+    fat, magic, at, out = _sections(open(lib, "rb").read())[".hip_fatbin"], b"__CLANG_OFFLOAD_BUNDLE__", 0, []
+    while (at := fat.find(magic, at)) >= 0:
+        pos = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", fat, at + len(magic))[0]):
+            off, size, name = struct.unpack_from("<QQQ", fat, pos)
+            if size and b"gfx950" in fat[pos + 24:pos + 24 + name]:
+                out.append(fat[at + off:at + off + size])
+            pos += 24 + name
+        at += len(magic)
+    return out
+
+
+@pytest.fixture(scope="module")
+def objects():
+    objs = _code_objects(B.LIB_PATH)
+    assert len(objs) >= len(build.SOURCES)
+    return objs
+
+
+def _vgprs(operand):
+    m = re.fullmatch(r"v(\d+)|v\[(\d+):(\d+)\]", operand)
+    if not m:
+        return set()
+    return {int(m[1])} if m[1] else set(range(int(m[2]), int(m[3]) + 1))
+
+
+def _too_close(lines):
+    """Cross-lane reads (permlane swaps, DPP) of a vector register less than two wait states after a vector instruction
+    wrote it.  The hardware does not wait by itself; the compiler does not count inline assembly.  Straight-line code."""
+    past, bad, seen = [], [], 0        # past: (wait states, registers written) of the last few instructions
+    for line in lines:
+        line = line.split("//")[0].strip()
+        if line.endswith(">:"):
+            kernel, past = line, []
+            continue
+        op, _, rest = line.partition(" ")
+        if not op or not rest and not op.startswith("s_"):
+            continue
+        args = [a.split()[0] for a in rest.split(",") if a.strip()]
+        swap = op.startswith("v_permlane") and "_swap" in op
+        reads = set()
+        if swap:
+            reads = _vgprs(args[0]) | _vgprs(args[1])
+        elif "_dpp" in op:
+            reads = _vgprs(args[1])
+        if reads:
+            seen += 1
+            waited = 0
+            for states, writes in reversed(past):
+                if waited >= 2:
+                    break
+                if writes & reads:
+                    bad.append((kernel, line, waited))
+                    break
+                waited += states
+        writes = set()
+        if op.startswith("v_") and args:
+            writes = _vgprs(args[0]) | (_vgprs(args[1]) if swap else set())
+        past = (past + [(int(args[0]) + 1 if op == "s_nop" else 1, writes)])[-4:]
+    return seen, bad
+
+
+def test_cross_lane_reads_keep_their_distance(objects, tmp_path):
+    assert _too_close(["<k>:", "v_pk_max_f16 v1, v2, v3", "s_nop 0", "v_permlane32_swap_b32_e32 v0, v1"])[1]
+    assert not _too_close(["<k>:", "v_pk_max_f16 v1, v2, v3", "s_nop 1", "v_permlane32_swap_b32_e32 v0, v1"])[1]
+    assert _too_close(["<k>:", "v_add_u32_e32 v1, v2, v3", "v_mov_b32_dpp v0, v1 quad_perm:[1,0,3,2]"])[1]
+    seen = 0
+    for i, obj in enumerate(objects):
+        path = tmp_path / f"{i}.elf"
+        path.write_bytes(obj)
+        out = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(path)], check=True,
+                             capture_output=True, text=True).stdout
+        n, bad = _too_close(out.splitlines())
+        assert not bad, bad[:4]
+        seen += n
+    assert seen > 100
