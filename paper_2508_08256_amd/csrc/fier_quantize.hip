@@ -245,7 +245,7 @@ __device__ __forceinline__ uint32_t transpose_nibbles(uint32_t v, uint32_t sel4,
   return (v & keep1) | (o & ~keep1);
 }
 
-// Whole groups, and the partial one at a unit's end.  Grid units * (1 + n_x), n_x = ceil(n_pairs / (4 bpw)), block 256.
+// Whole groups, and the partial one at a unit's end.  Grid units * (1 + n_x), n_x >= ceil(n_pairs / (4 bpw)), block 256.
 // The first `units` workgroups do the units' partial groups (one wavefront, the longest chain of dependent loads:
 // started last it would end the kernel late, and as a kernel of its own it took 4 to 17 us after this one); then wave w
 // of workgroup x of a unit owns the pair blocks 4 bpw x + w, + 4, + 8, ...; NS = group size / 32.
@@ -517,7 +517,10 @@ hipError_t launch_quantize(int dtype, KvLayout lay, const void* K, uint32_t* kbi
   // 267 / 239 / 230 / 236 / 246, 128 ragged units up to 64k 306 / 265 / 272 / 273 / 283 / 288.
   const long blocks = (long)n_pairs * units;
   const int bpw = blocks >= 4L * 4 * 1024 ? 4 : blocks >= 4L * 2 * 1024 ? 2 : 1;
-  const int n_x = (n_pairs + 4 * bpw - 1) / (4 * bpw);
+  // An odd number per unit: where only the first tokens of a large capacity are there, the workgroups with work lie n_x
+  // apart, and workgroups go round-robin to the 8 XCDs and their CUs: at a multiple of 8 one XCD did everything.  512
+  // units of 1000 tokens in 65536 rows: 331 us at n_x = 64, 55 at 65; 128 ragged units up to 64k 279 / 259.
+  const int n_x = (n_pairs + 4 * bpw - 1) / (4 * bpw) | 1;
   if (dtype == DT_F16)
     launch_quantize_dt<DT_F16>(lay, (const uint32_t*)K, kbits, kmeta, kabsmax, seq_lens, units, n_kv_heads, max_ctx, ns,
                                bpw, n_x, st);
