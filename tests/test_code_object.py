@@ -4,6 +4,7 @@ import re
 import struct
 import subprocess
 
+import msgpack
 import pytest
 
 from paper_2508_08256_amd import binding as B
@@ -39,6 +40,20 @@ def objects():
     objs = _code_objects(B.LIB_PATH)
     assert len(objs) >= len(build.SOURCES)
     return objs
+
+
+def _kernels(obj):
+    note = _sections(obj)[".note"]
+    name, desc, _ = struct.unpack_from("<III", note)
+    at = 12 + (name + 3) // 4 * 4
+    return msgpack.unpackb(note[at:at + desc])["amdhsa.kernels"]
+
+
+def test_no_kernel_spills_registers(objects):
+    """Scratch per lane means registers written to memory and read back."""
+    bad = [(k[".name"], k[".private_segment_fixed_size"]) for o in objects for k in _kernels(o)
+           if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]]
+    assert not bad, bad
 
 
 def _vgprs(operand):
