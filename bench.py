@@ -212,8 +212,9 @@ def measure(args, workload, budget_arg, detail):
 
     # the timed steps share ONE workspace (as a model's layers would); the per-kernel timing below needs every
     # layer cache to keep its own intermediate state, hence one workspace per layer cache there
-    wss = [[B.make_workspace(cfg, budget) for _ in range(NL)] for _ in range(R)]
-    ws_dense = B.make_workspace(cfg, max_ctx)
+    ws_step = B.make_workspace(cfg, budget, NL)
+    wss = [[B.make_workspace(cfg, budget, 1) for _ in range(NL)] for _ in range(R)]
+    ws_dense = B.make_workspace(cfg, max_ctx, 1)
     out = torch.zeros((NL, batch, Hq, 128), dtype=torch.float32, device="cuda")
     out1 = torch.zeros((1, batch, Hq, 128), dtype=torch.float32, device="cuda")
     idx = torch.zeros((NL, units, budget), dtype=torch.int32, device="cuda")
@@ -258,7 +259,7 @@ def measure(args, workload, budget_arg, detail):
             B.page_mean_score(cfg, scores, seq_lens, 1, PG, pscores)
         B.topk(pcfg, pscores, page_lens, 0, page_budgets, max_pages, pidx, pcnt)
         B.expand_pages(cfg, pidx, pcnt, max_pages, seq_lens, 1, PG, tidx, tcnt, budget)
-        B.sparse_attn(cfg, c, qs[r][0], tidx, tcnt, budget, out1, wss[0][0])
+        B.sparse_attn(cfg, c, qs[r][0], tidx, tcnt, budget, out1, ws_step)
 
     def step(i):
         r = i % R
@@ -268,11 +269,11 @@ def measure(args, workload, budget_arg, detail):
             B.decode_step_mixed(cfg, caches[r], dense_flags, qs[r], kns[r], vns[r], budgets, budget, out, idx, cnt,
                                 ws_mixed)
         else:
-            B.decode_step(cfg, caches[r], qs[r], kns[r], vns[r], budgets, budget, out, None, None, wss[0][0])
+            B.decode_step(cfg, caches[r], qs[r], kns[r], vns[r], budgets, budget, out, None, None, ws_step)
 
     def step_with_index_list(i):
         r = i % R
-        B.decode_step(cfg, caches[r], qs[r], kns[r], vns[r], budgets, budget, out, idx, cnt, wss[0][0])
+        B.decode_step(cfg, caches[r], qs[r], kns[r], vns[r], budgets, budget, out, idx, cnt, ws_step)
 
     def timed(fn, n, warm):
         for i in range(warm):
@@ -423,11 +424,11 @@ def measure(args, workload, budget_arg, detail):
         B.topk(cfg, scores, seq_lens, 1, budgets, budget, idx[0:1], cnt[0:1])
 
     def st_topk_ws(i):
-        B.topk_ws(cfg, scores, seq_lens, 1, budgets, budget, idx[0:1], cnt[0:1], wss[0][0])
+        B.topk_ws(cfg, scores, seq_lens, 1, budgets, budget, idx[0:1], cnt[0:1], ws_step)
 
     def st_attn(i):
         r, l = flat[i % len(flat)]
-        B.sparse_attn(cfg, caches[r][l], qs[r][l:l + 1], idx[0:1], cnt[0:1], budget, out1, wss[0][0])
+        B.sparse_attn(cfg, caches[r][l], qs[r][l:l + 1], idx[0:1], cnt[0:1], budget, out1, ws_step)
 
     us_score, _ = timed(st_score, max(24, ns // 4), 4)
     us_topk, _ = timed(st_topk, max(24, ns // 4), 4)
@@ -465,7 +466,7 @@ def measure(args, workload, budget_arg, detail):
 
         def st_pattn(i):
             r = i % R
-            B.sparse_attn(cfg, caches[r][0], qs[r][0], tidx, tcnt, budget, out1, wss[0][0])
+            B.sparse_attn(cfg, caches[r][0], qs[r][0], tidx, tcnt, budget, out1, ws_step)
 
         stages = {"importance_estimation": round(timed(st_est, ns, 4)[0], 3),
                   "topk_recall": round(timed(st_recall, ns, 4)[0], 3),

@@ -111,8 +111,9 @@ size_t fier_packed_meta_bytes(const fier_config *cfg);
 size_t fier_workspace_bytes(const fier_config *cfg, int32_t max_budget);
 /* The size from which fier_decode_step over n_layers layers runs them in as few launches as it can: a workspace of j
  * times fier_workspace_bytes lets up to j layers share a launch (at most 16, fewer where the layers are large), as long
- * as no two of them share an array they write.  Any size from fier_workspace_bytes on gives the same selections, and
- * outputs that agree to the order of summation.  0 if invalid. */
+ * as no two of them share an array they write.  At most 512 MiB, or fier_workspace_bytes where that is more.  Any size from
+ * fier_workspace_bytes on gives the same selections, and outputs that agree to the order of summation.  For
+ * fier_decode_step_mixed the larger of this, at its max_budget, and fier_workspace_bytes(cfg, max_ctx).  0 if invalid. */
 size_t fier_workspace_bytes_layers(const fier_config *cfg, int32_t max_budget, int32_t n_layers);
 /* For inspection: the byte offset inside such a workspace of the scores [units][max_ctx] float that the latest
  * fier_decode_step on it computed for its last layer (Alg. 1 step 2 as the fused step evaluates it).  0 if invalid. */

@@ -184,7 +184,9 @@ def decode_step_kernels(cfg: Config, max_budget: int, with_index_list: bool = Fa
 
 def make_workspace(cfg: Config, max_budget: int, n_layers: int = 16):
     """A zero-filled workspace on the GPU (the library keeps its counters zero from then on), sized for calls of up
-    to n_layers layers to share their launches (1: the smallest; longer calls work with any size)."""
+    to n_layers layers to share their launches: up to 16 times workspace_bytes, at most 512 MiB where one layer takes
+    less.  n_layers = 1, the smallest, is all that calls other than decode_step and decode_step_mixed use, and longer
+    calls of these work with any size."""
     import torch
 
     n = workspace_bytes_layers(cfg, max_budget, n_layers)

@@ -139,15 +139,18 @@ Workspace carve(const fier_config* c, int32_t max_budget, void* base) {
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? FIER_OK : FIER_EHIP; }
 
-// Layers of one fused-step launch: up to 16, and up to 2^25 cached tokens and units.  Layer by layer, a small layer pays
-// two launches, their prologues and drains and its serial hand-offs (threshold, merge) with most of the chip idle; side
-// by side the layers fill each other's gaps.  Measured (us per call, layer by layer / side by side): 16 layers of 64
-// units x 1k..8k, paged, 4 query heads per kv head 499 / 139; 8 layers of 8 units x 32k, 4 heads 209 / 55; 2 layers of
-// 16 units x 20k with the index list 73 / 42; 4 layers of 128 units x 8k..64k, whose steps fill the chip by
-// themselves, 396 / 401 two at a time, 374 all four.  The bound holds the workspace at about 300 MB.
+// Layers of one fused-step launch: up to 16, up to 2^25 cached tokens and units, and up to 512 MiB of workspace.  Layer by
+// layer, a small layer pays two launches, their prologues and drains and its serial hand-offs (threshold, merge) with most
+// of the chip idle; side by side the layers fill each other's gaps.  Measured (us per call, layer by layer / side by side):
+// 16 layers of 64 units x 1k..8k, paged, 4 query heads per kv head 499 / 139; 8 layers of 8 units x 32k, 4 heads 209 / 55; 2
+// layers of 16 units x 20k with the index list 73 / 42.  Layers that fill the chip by themselves gain little: 4 layers of
+// 128 units x 8k..64k (65600 rows of capacity) 409 one by one, 399 as 2 + 2, 390 as 3 + 1, 372 all four.  The two bounds
+// hold the memory back: 2^25 tokens need 270 MB at one head per kv head (3 layers of that batch), several times as much at
+// 8 heads and budgets of the whole context, which the bytes stop.
 constexpr int64_t kBatchTokens = (int64_t)1 << 25;
-inline int layers_per_launch(const fier_config* c) {
-  const int64_t n = kBatchTokens / ((int64_t)units_of(c) * c->max_ctx);
+constexpr size_t kBatchBytes = (size_t)512 << 20;
+inline int layers_per_launch(const fier_config* c, size_t part_bytes) {
+  const int64_t n = std::min<int64_t>(kBatchTokens / ((int64_t)units_of(c) * c->max_ctx), (int64_t)(kBatchBytes / part_bytes));
   return (int)std::max<int64_t>(1, std::min<int64_t>(n, fier::kMaxLayersPerLaunch));
 }
 
@@ -246,7 +249,7 @@ size_t fier_workspace_bytes(const fier_config* cfg, int32_t max_budget) {
 size_t fier_workspace_bytes_layers(const fier_config* cfg, int32_t max_budget, int32_t n_layers) {
   if (n_layers < 1) return 0;
   const size_t one = fier_workspace_bytes(cfg, max_budget);
-  return one ? one * (size_t)std::min<int32_t>(n_layers, layers_per_launch(cfg)) : 0;
+  return one ? one * (size_t)std::min<int32_t>(n_layers, layers_per_launch(cfg, one)) : 0;
 }
 
 size_t fier_workspace_scores_offset(const fier_config* cfg, int32_t max_budget) {
@@ -402,7 +405,7 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
   // Layers that share their launches: as many as the workspace has parts for (one kernel alone, phase > 0, works on
   // what the phases before it left: layer by layer).  Only the first part is known to be clear, the others are
   // cleared here before they are first used, and again after a dense layer, which carves the workspace its own way.
-  const int most = phase != 0 ? 1 : (int)std::min<size_t>((size_t)layers_per_launch(cfg), workspace_bytes / w.bytes);
+  const int most = phase != 0 ? 1 : (int)std::min<size_t>((size_t)layers_per_launch(cfg, w.bytes), workspace_bytes / w.bytes);
   int clear_parts = 1;
   for (int l = 0, n_done = 1; l < n_layers; l += n_done) {
     n_done = 1;

@@ -211,3 +211,16 @@ def test_form_of_the_step_follows_from_the_shape():
     assert k(B.make_config(4, 32, 8, 131136, B.BF16), 4096, True) == 3
     assert k(B.make_config(2, 30, 8, 4096), 64) == 0
     assert k(B.make_config(1, 8, 8, 4160), 0) == 0
+
+
+@pytest.mark.parametrize("batch,hq,hkv,max_ctx,budget", [
+    (8, 64, 8, 32768, 32768), (64, 64, 8, 4096, 4096), (256, 64, 8, 1024, 512), (16, 64, 8, 16384, 4096),
+    (16, 32, 8, 65600, 65600), (1, 32, 32, 131136, 131136), (1, 32, 32, 32832, 3604), (1, 8, 8, 4160, 512), (1, 1, 1, 64, 1)])
+def test_the_workspace_for_layers_is_bounded(batch, hq, hkv, max_ctx, budget):
+    """A whole number of parts, at most 16, together no more than 512 MiB unless one part alone is."""
+    cfg = B.make_config(batch, hq, hkv, max_ctx, B.BF16)
+    one = B.workspace_bytes(cfg, budget)
+    sizes = [B.workspace_bytes_layers(cfg, budget, n) for n in range(1, 41)]
+    assert sizes[0] == one and sizes == sorted(sizes) and all(s % one == 0 for s in sizes)
+    assert sizes[-1] <= min(16 * one, max(one, 512 << 20)), sizes[-1] / 2**20
+    assert B.workspace_bytes_layers(cfg, budget, 0) == 0 and B.workspace_bytes_layers(cfg, 0, 4) == 0
