@@ -797,8 +797,6 @@ static long step_resident_wgs(int n_rep) { return 256L * step_wgs_per_cu(n_rep);
 //     (us per step): 32 units x 32k, 112 rows per range: 35.0 with one range per workgroup, 34.0 with two, 38.1 with
 //     four; 32 units x 16k (two ranges = one workgroup per CU): 25.8 / 27.4; 32 units x 64k, B = 7209: 50.9 with two
 //     ranges (225 rows), 51.5 with four; 64 units x 32k: 50.6 with two, 51.9 with four.
-//   units: of all layers of the launch (8 layers of 8 units x 32k: 81 us per call at one range, 62 at two, 55 at four, 63
-// at eight; 16 layers of 64 units x 1k..8k: 174 / 180 / 149 / 139 at 1 / 2 / 4 / 8, its rule gives eight).
 int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
   const double per_range = 1024.0 * (double)max_budget / (double)max_ctx;
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
@@ -808,6 +806,28 @@ int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
   while (rpw < 8 && wgs(rpw) > step_resident_wgs(n_rep)) rpw *= 2;
   if (rpw < 8 && per_range * (2 * rpw) <= 288.0 && wgs(2 * rpw) >= 512) rpw *= 2;
   return rpw;
+}
+
+// The same for a launch of several layers of `units` units each: from the units of all of them (8 layers of 8 units x 32k:
+// 81 us per call at one range, 62 at two, 55 at four, 63 at eight; 16 layers of 64 units x 1k..8k: 174 / 180 / 149 / 139 at
+// 1 / 2 / 4 / 8, its rule gives eight), and half of that where long workgroups would end the launch late:
+//   * 1000 rows or more in workgroups that cut the units unevenly, the longest 1.45 times the mean (us per call of 2 layers,
+//     layer by layer / whole rule / half: 320 units x 9.4k, 4 heads, B = 3168, with the list, 10 ranges cut as 8 + 2 or
+//     4 + 4 + 2: 307 / 327 / 272; 88 units x 10k, 8 heads, B = 3239: 110 / 129 / 114);
+//   * 1500 rows or more where two layers need up to 1.4 times the workgroups the GPU holds: the second round is short,
+//     but lasts as long as a workgroup (200 units x 11.5k, 4 heads, B = 2969: 163 / 208 / 161).
+// Of 6218 measured pairs of a shape and a number of layers 151 had been slower by 2 to 27 % than layer by layer; 57 still
+// are, by 2 to 17 %, most of them two layers that fill the GPU one by one.
+static int step_ranges_per_wg_layers(int units, int layers, int n_rep, int max_budget, int max_ctx) {
+  const int rpw = step_ranges_per_wg(units * layers, n_rep, max_budget, max_ctx);
+  const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
+  if (layers == 1 || rpw < 4 || n_ranges <= rpw) return rpw;
+  const double rows = 1024.0 * (double)max_budget / (double)max_ctx * rpw;
+  const int per_unit = (n_ranges + rpw - 1) / rpw;
+  const double grid = (double)units * layers * per_unit / (double)step_resident_wgs(n_rep);
+  const bool uneven = rows >= 1000.0 && rpw * per_unit >= 1.45 * n_ranges;
+  const bool short_round = rows >= 1500.0 && layers == 2 && grid > 1.0 && grid <= 1.4;
+  return uneven || short_round ? rpw / 2 : rpw;
 }
 #endif
 
@@ -930,7 +950,7 @@ hipError_t launch_step_attend(int dtype, KvLayout lay, int n_rep, const StepBuff
 #define FIER_STEP_RPW(DT, RPW)                                                                                        \
   return (lb.n > 1 ? launch_step_attend_dt<DT, RPW, true> : launch_step_attend_dt<DT, RPW, false>)(lay, n_rep, sb, K, V, q, seq_lens, extra, budgets, max_budget, sm_scale,      \
                                         count_out, out, kabsmax, units, n_kv_heads, max_ctx, flags, lb, st)
-  const int rpw = step_ranges_per_wg(units * lb.n, n_rep, max_budget, max_ctx);
+  const int rpw = step_ranges_per_wg_layers(units, lb.n, n_rep, max_budget, max_ctx);
   if (dtype == DT_F16) {
     if (rpw == 1) FIER_STEP_RPW(DT_F16, 1);
     if (rpw == 2) FIER_STEP_RPW(DT_F16, 2);
@@ -969,7 +989,7 @@ hipError_t launch_step_emit_idx(const StepBuffers& sb, const int32_t* seq_lens, 
                                 int units, int n_rep, int n_kv_heads, int max_ctx, const LayerBatch& lb,
                                 hipStream_t st) {
   // the same split into workgroups as the step's second kernel
-  const int rpw = step_ranges_per_wg(units * lb.n, n_rep, max_budget, max_ctx);
+  const int rpw = step_ranges_per_wg_layers(units, lb.n, n_rep, max_budget, max_ctx);
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
   const int n_wgs = (n_ranges + rpw - 1) / rpw;
   const dim3 grid(units, n_wgs, lb.n);
