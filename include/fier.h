@@ -247,7 +247,8 @@ int fier_decode_step_mixed(const fier_config *cfg, const fier_cache *layers, int
  *   3 kernels otherwise: phase 2 = exact threshold, phase 3 = selection + attention + merge, which also writes
  *     idx_out (may be repeated).
  * Same arguments as fier_decode_step.  Phase p works on what phases 1..p-1 of the latest step on this workspace and
- * these layers left behind, so the sequence 1, 2, 3 equals fier_decode_step.  Phase 1 adds its scores to the
+ * these layers left behind, so the sequence 1, 2, 3 equals fier_decode_step (of several layers: if they all share one
+ * launch).  Phase 1 adds its scores to the
  * workspace's histograms and phase 2 consumes and clears them: phase 1 may be repeated for timing (follow it with one
  * phase 2 before the next real step), phase 2 only after a phase 1.  Phases 2 + 16 f and 3 + 16 f, f = 1..3, are for
  * tests: the two-kernel form whatever the shape, its second kernel with flags f (1: no workgroup picks up the

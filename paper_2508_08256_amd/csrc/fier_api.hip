@@ -402,10 +402,10 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
   const size_t esz = 2;
   hipStream_t s = (hipStream_t)stream;
   Workspace w = carve(cfg, max_budget, workspace);
-  // Layers that share their launches: as many as the workspace has parts for (one kernel alone, phase > 0, works on
-  // what the phases before it left: layer by layer).  Only the first part is known to be clear, the others are
-  // cleared here before they are first used, and again after a dense layer, which carves the workspace its own way.
-  const int most = phase != 0 ? 1 : (int)std::min<size_t>((size_t)layers_per_launch(cfg, w.bytes), workspace_bytes / w.bytes);
+  // Layers that share their launches: as many as the workspace has parts for (the kernels of the three-kernel form take
+  // one layer).  Only the first part is known to be clear, the others are cleared here before they are first used, and
+  // again after a dense layer, which carves the workspace its own way.
+  const int most = (phase >> 4) == 4 ? 1 : (int)std::min<size_t>((size_t)layers_per_launch(cfg, w.bytes), workspace_bytes / w.bytes);
   int clear_parts = 1;
   for (int l = 0, n_done = 1; l < n_layers; l += n_done) {
     n_done = 1;
@@ -438,7 +438,7 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
     const fier::LayerBatch lb =
         batch_of(cfg, c, dense_layers ? dense_layers + l : nullptr, std::min(most, n_layers - l), w.bytes);
     n_done = lb.n;
-    if (lb.n > clear_parts) {
+    if (lb.n > clear_parts && phase < 2) {  // later phases work on what phase 1 left there
       e = zero_parts(static_cast<char*>(workspace) + clear_parts * w.bytes, w.zero_bytes / sizeof(uint32_t), w.bytes,
                      lb.n - clear_parts, s);
       if (e != hipSuccess) return FIER_EHIP;

@@ -1,4 +1,6 @@
 """fier_decode_step over several layers: layers that share a launch give what single-layer calls give."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -146,3 +148,109 @@ def test_two_long_layers_are_not_slower_side_by_side(batch, hq, hkv, ctx, budget
         torch.cuda.synchronize()
         best[parts] = min(best.get(parts, 1e9), e0.elapsed_time(e1) / 12)
     assert best[2] <= 1.08 * best[1], best
+
+
+class RandomLayer:
+    """A layer's cache, queries and new rows with values made on the GPU: large layers are quick to make."""
+
+    def __init__(self, seed, batch, hq, hkv, lens, budgets, dtype, max_ctx, bt, group):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(seed)
+        td = torch.float16 if dtype == F16 else torch.bfloat16
+        normal = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(td)  # noqa: E731
+        self.cfg = B.make_config(batch, hq, hkv, max_ctx, dtype, group_size=group)
+        shape, table = (self.cfg.units, max_ctx, 128), None
+        if bt:
+            n = batch * (max_ctx // bt)
+            shape = (n, hkv, bt, 128)
+            table = torch.randperm(n, generator=gen, device="cuda").to(torch.int32).view(batch, -1).contiguous()
+        self.K, self.V = normal(*shape), normal(*shape)
+        self.q, self.k_new, self.v_new = normal(batch, hq, 128), normal(self.cfg.units, 128), normal(self.cfg.units, 128)
+        i32 = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")  # noqa: E731
+        self.seq_lens, self.budgets = i32(lens), i32(budgets)
+        self.wl = SimpleNamespace(budgets=np.asarray(budgets))
+        self.cache = B.DeviceCache(self.cfg, self.K, self.V, self.seq_lens, table)
+        B.quantize_keys(self.cfg, self.cache)
+
+
+LARGE = [
+    # batch, query heads, kv heads, contexts, budget in per cent, dtype, capacity, block tokens, group, list, layers
+    (4, 40, 8, (20000, 3), 11, BF16, 20032, 0, 32, True, 4),         # 5 heads; 4 ranges per workgroup, 5 workgroups per unit
+    (2, 28, 4, (32000, 3), 11, F16, 32064, 0, 32, False, 8),         # 7 heads; 4 ranges
+    (1, 8, 8, (32768, 1), 11, BF16, 32832, 0, 32, True, 8),          # 1 head; 2 ranges, 17 workgroups per unit
+    (21, 18, 3, (9300, 2), 11, BF16, 9344, 0, 128, False, 5),        # 6 heads; 8 ranges, 63 units: order 0, not resident at once
+    (5, 9, 3, (131000, 1.2), 4.58, F16, 131136, 0, 32, True, 6),      # 3 heads; the same with 17 workgroups per unit
+    (16, 64, 8, (6000, 2), 11, BF16, 6016, 64, 32, True, 6),         # 8 heads, paged, 128 units: order 2, not resident at once
+    (21, 15, 3, (5000, 2), 30, F16, 5056, 64, 64, True, 3),          # 5 heads, paged; 1 range
+]
+
+
+def _large(case):
+    batch, hq, hkv, (top, spread), pct, dtype, max_ctx, bt, group, with_list, n = case
+    rng = np.random.default_rng(top)
+    lens = [top] + [int(x) for x in rng.integers(top / spread, top + 1, batch - 1)]
+    buds = [max(1, round(pct / 100 * x)) for x in lens]
+    return [RandomLayer(40 + l, batch, hq, hkv, lens, buds, dtype, max_ctx, bt, group) for l in range(n)], with_list
+
+
+@pytest.mark.parametrize("case", LARGE)
+def test_large_layers_side_by_side_equal_one_by_one(case):
+    """5 to 8 heads per kv head, 1 to 8 ranges per workgroup, all three dispatch orders, grids beyond the resident one:
+    the same state, selections and, up to the order of at most 6000 binary32 terms, outputs (|v| up to about 5:
+    6000 * 2^-24 * 5 < 2e-3)."""
+    dws, with_list = _large(case)
+    order, mb = range(len(dws)), int(dws[0].wl.budgets.max())
+    start = [_state(d) for d in dws]
+    dense = [False] * len(dws)
+    want = _run(dws, order, dense, B.make_workspace(dws[0].cfg, mb, 1), with_list, True, True)
+    for d, s in zip(dws, start):
+        _restore(d, s)
+    del start
+    ws = B.make_workspace(dws[0].cfg, mb, len(dws))
+    assert ws.numel() == len(dws) * B.workspace_bytes(dws[0].cfg, mb)
+    got = _run(dws, order, dense, ws, with_list, True, False)
+    assert torch.isfinite(got[0]).all()
+    assert float((got[0] - want[0]).abs().max()) <= 2e-3
+    if with_list:
+        assert torch.equal(got[2], want[2]) and torch.equal(got[1], want[1])
+    for a, b in zip(got[3], want[3]):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
+
+
+CHECKSUMS, FORCE_LATE = 2, 1
+
+
+@pytest.mark.parametrize("case", [LARGE[0], LARGE[3], LARGE[4], LARGE[6], (1, 8, 4, (5000, 1), 20, F16, 5056, 0, 32, True, 3)])
+@pytest.mark.parametrize("flags", [CHECKSUMS, CHECKSUMS | FORCE_LATE])
+def test_attended_rows_of_shared_launches(case, flags):
+    """Count and index sum of the rows each layer's workgroups gathered, in that layer's part of the workspace, are those
+    of its list; with FORCE_LATE no workgroup picks up the threshold, as after a wait that has run out, and the merging
+    workgroup attends over all threshold-bin rows."""
+    dws, _ = _large(case)
+    cfg, n, mb = dws[0].cfg, len(dws), int(dws[0].wl.budgets.max())
+    part = B.workspace_bytes(cfg, mb)
+    ws = B.make_workspace(cfg, mb, n)
+    assert ws.numel() == n * part
+    stack = lambda name: torch.stack([getattr(d, name) for d in dws]).contiguous()  # noqa: E731
+    args = lambda out, idx, cnt: (cfg, [d.cache for d in dws], stack("q"), stack("k_new"), stack("v_new"),  # noqa: E731
+                                  dws[0].budgets, mb, out, idx, cnt, ws)
+    new = lambda: (torch.zeros((n, cfg.batch, cfg.n_q_heads, 128), device="cuda"),  # noqa: E731
+                   torch.full((n, cfg.units, mb), -1, dtype=torch.int32, device="cuda"),
+                   torch.zeros((n, cfg.units), dtype=torch.int32, device="cuda"))
+    want = new()
+    B.decode_step(*args(*want))
+    ctl = [ws[z * part:z * part + 64 * cfg.units].view(torch.int32).view(cfg.units, 16) for z in range(n)]
+    for c in ctl:
+        c[:, 14:16] = 0
+    got = new()
+    for p in (1, 2 + 16 * flags, 3 + 16 * flags):
+        B.decode_step_phase(*args(*got), p)
+    torch.cuda.synchronize()
+    assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    assert float((got[0] - want[0]).abs().max()) <= 2e-3
+    for l in range(n):
+        c = ctl[n - 1 - l].cpu()  # the last layer has the first part
+        sel = torch.where(got[1][l] < 0, 0, got[1][l]).long().sum(dim=1).cpu()
+        assert torch.equal(c[:, 14], got[2][l].cpu())
+        assert torch.equal(c[:, 15].long() & 0xFFFFFFFF, sel & 0xFFFFFFFF)
