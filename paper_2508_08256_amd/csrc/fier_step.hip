@@ -904,13 +904,17 @@ hipError_t launch_step_attend_dt(KvLayout lay, int n_rep, const StepBuffers& sb,
   // with it.  Hence from 8 MB of gathered rows per launch.  (Rotating over 3 to 6 caches overstates the gain: 2 us
   // at 32 x 32k.)  The matrix-core gather (3 or more heads per kv head) lost by it on the K rows, which it loads in
   // four pieces per row (32 units x 128k +0.6 us, the ragged 128-unit batch +4), and gains on the V rows alone:
-  // 32 x 128k 61.5 / 59.7, the ragged batch 101.3 / 100.8.
+  // 32 x 128k 61.5 / 59.7, the ragged batch 101.3 / 100.8.  The rows of a launch are those of all its layers (calls of 2 to
+  // 16 layers that gather 1.8 to 7.4 MB, one query head, us with / without the hint, 12 to 48 layer caches in turn: 3 layers of
+  // 8 units x 4k 23.2 / 22.3, 2 of 8 x 16k 26.2 / 25.4, 16 of 8 x 1k 25.1 / 24.1; with 4 heads the same to 0.3).
   const bool stream = (long)units * lb.n * max_budget * (2 * kD * 2) >= (8L << 20);
-#define FIER_STEP_CASE_S(R)                                                       \
-  case R:                                                                         \
-    if constexpr (MULTI) step_attend_kernel<DT, R, RPW, true, LayerBatch><<<grid, kStepThreads, 0, st>>>(a, lb);        \
-    else if (stream) step_attend_kernel<DT, R, RPW, true, OneLayer><<<grid, kStepThreads, 0, st>>>(a, OneLayer());      \
-    else step_attend_kernel<DT, R, RPW, false, OneLayer><<<grid, kStepThreads, 0, st>>>(a, OneLayer());                 \
+  using Layers = std::conditional_t<MULTI, LayerBatch, OneLayer>;
+  Layers layers;
+  if constexpr (MULTI) layers = lb;
+#define FIER_STEP_CASE_S(R)                                                                                   \
+  case R:                                                                                                     \
+    if (stream) step_attend_kernel<DT, R, RPW, true, Layers><<<grid, kStepThreads, 0, st>>>(a, layers);       \
+    else step_attend_kernel<DT, R, RPW, false, Layers><<<grid, kStepThreads, 0, st>>>(a, layers);             \
     break;
   switch (n_rep) {
     FIER_STEP_CASE_S(1)

@@ -56,6 +56,17 @@ def test_no_kernel_spills_registers(objects):
     assert not bad, bad
 
 
+def test_every_variant_of_the_gather_has_both_kinds_of_loads(objects):
+    """step_attend_kernel<type, heads, ranges, STREAM, layers>: the launcher's rule on STREAM has both to choose from."""
+    names = " ".join(k[".name"] for o in objects for k in _kernels(o))
+    for dt in (0, 1):
+        for heads in range(1, 9):
+            for ranges in (1, 2, 4, 8):
+                for stream in (0, 1):
+                    for layers in ("8OneLayer", "10LayerBatch"):
+                        assert f"18step_attend_kernelILi{dt}ELi{heads}ELi{ranges}ELb{stream}ENS_{layers}E" in names
+
+
 def _vgprs(operand):
     m = re.fullmatch(r"v(\d+)|v\[(\d+):(\d+)\]", operand)
     if not m:
