@@ -111,9 +111,11 @@ size_t fier_packed_meta_bytes(const fier_config *cfg);
 size_t fier_workspace_bytes(const fier_config *cfg, int32_t max_budget);
 /* The size from which fier_decode_step over n_layers layers runs them in as few launches as it can: a workspace of j
  * times fier_workspace_bytes lets up to j layers share a launch (at most 16, fewer where the layers are large), as long
- * as no two of them share an array they write.  At most 512 MiB, or fier_workspace_bytes where that is more.  Any size from
- * fier_workspace_bytes on gives the same selections, and outputs that agree to the order of summation.  For
- * fier_decode_step_mixed the larger of this, at its max_budget, and fier_workspace_bytes(cfg, max_ctx).  0 if invalid. */
+ * as no two of them share an array they write; those that do run in order.  Block pools count as shared if their base
+ * addresses are equal: pools that overlap at different bases must not hold one block for two layers of a call.
+ * At most 512 MiB, or fier_workspace_bytes where that is more.  Any size from fier_workspace_bytes on gives the same
+ * selections, and outputs that agree to the order of summation.  For fier_decode_step_mixed the larger of this, at its
+ * max_budget, and fier_workspace_bytes(cfg, max_ctx).  0 if invalid. */
 size_t fier_workspace_bytes_layers(const fier_config *cfg, int32_t max_budget, int32_t n_layers);
 /* For inspection: the byte offset inside such a workspace of the scores [units][max_ctx] float that the latest
  * fier_decode_step on it computed for its last layer (Alg. 1 step 2 as the fused step evaluates it).  0 if invalid. */
@@ -248,8 +250,7 @@ int fier_decode_step_mixed(const fier_config *cfg, const fier_cache *layers, int
  *     idx_out (may be repeated).
  * Same arguments as fier_decode_step.  Phase p works on what phases 1..p-1 of the latest step on this workspace and
  * these layers left behind, so the sequence 1, 2, 3 equals fier_decode_step (of several layers: if they all share one
- * launch).  Phase 1 adds its scores to the
- * workspace's histograms and phase 2 consumes and clears them: phase 1 may be repeated for timing (follow it with one
+ * launch).  Phase 1 adds its scores to the workspace's histograms and phase 2 consumes and clears them: phase 1 may be repeated for timing (follow it with one
  * phase 2 before the next real step), phase 2 only after a phase 1.  Phases 2 + 16 f and 3 + 16 f, f = 1..3, are for
  * tests: the two-kernel form whatever the shape, its second kernel with flags f (1: no workgroup picks up the
  * threshold itself, the merging workgroup attends over all threshold-bin rows; 2: checksums of the attended rows in

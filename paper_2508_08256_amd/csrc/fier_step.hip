@@ -1,5 +1,5 @@
 // Second kernel of the fused decode step: exact top-B threshold (Alg. 1 step 3) and attention over the selected
-// rows (Alg. 1 step 4) in ONE launch, for grids whose workgroups are all resident at once.
+// rows (Alg. 1 step 4) in ONE launch, of one layer or of several that share it (blockIdx.z).
 //
 // The score kernel has left, per unit, its scores and their 512-bin histogram over [-R, R].  Here a workgroup owns
 // RPW consecutive 1024-token ranges of a unit and
@@ -21,10 +21,10 @@
 //   6. the unit's last arriver there merges the partials.
 // A workgroup whose poll runs out says so in its partial (the sign of its l) and in the upper half of the second
 // arrival counter; the merging workgroup then attends over that workgroup's threshold-bin rows itself before it
-// merges.  The result therefore never depends on a poll
-// succeeding, every wait is bounded and every wavefront exits.  A poll only ever lasts long when the unit's
-// workgroups are not running together, which is why the launcher uses this kernel for resident grids and the
-// three-kernel form (threshold kernel, then selection + attention) otherwise.
+// merges.  The result therefore never depends on a poll succeeding, every wait is bounded and every wavefront exits.  A poll
+// only ever lasts long when the unit's workgroups are not running together; the dispatch order keeps them together on grids
+// that are not resident at once.  Which calls take this kernel and which the three-kernel form (threshold kernel, then
+// selection + attention): step_two_kernel_form below, for layers with launches of their own; shared launches always this one.
 // All selection decisions are integer comparisons of order-preserving keys: exact and deterministic.
 //
 // The ascending index list of the selection (idx_out of the step, an optional output) is written by a small
@@ -716,7 +716,8 @@ __global__ __launch_bounds__(kStepThreads) void step_emit_idx_kernel(const float
   __shared__ uint32_t wtot[RPW + 1][4];  // per wavefront: selected tokens of each range, rows of the workgroups before
   const int unit = blockIdx.x, wg = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  {  // this workgroup's layer
+  {  // this workgroup's layer (one layer's launches pay nothing for the table here: 8 units x 4k 21.6 us per step without
+     // it, 21.5 with it, 32 x 32k 36.9 / 36.8, 32 x 60k, 2 heads 45.8 / 45.5)
     const int z = (int)blockIdx.z;
     const int64_t ws = lb.ws_shift(z);
     scores = shifted(scores, ws);
