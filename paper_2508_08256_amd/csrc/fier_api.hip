@@ -455,7 +455,7 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
     // instead, whose workgroups never wait for each other and which write the index list while they select, on
     // grouped-query grids far beyond the resident one and whenever such a shape is asked for the list.  Layers that share
     // their launches always take the one launch: there the other layers fill the chip while a unit's workgroups wait, and
-    // it is the faster also where the single layer's form has three kernels (us per call of 2 layers, three kernels layer
+    // it is as fast or faster also where the single layer's form has three kernels (us per call of 2 layers, three kernels layer
     // by layer / side by side, 3300 to 3750 rows of 11 or 25 %, with the list: 128 units x 30k, 4 heads 181 / 181, 8 heads
     // 243 / 198; 256 x 15k, 4 heads 303 / 306, 8 heads 402 / 313; 4 layers of 128 ragged units up to 65k, 4 heads 477 /
     // 405; without the list, 512 x 30k, 4 heads 624 / 567, 5 heads 668 / 590).
