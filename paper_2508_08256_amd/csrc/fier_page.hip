@@ -7,6 +7,8 @@
 //   page score, mode 0 (Eq. 3 as printed): max over the channels of max(q_i kmax_i, q_i kmin_i);
 //   page score, mode 1: the same summed over the channels, an upper bound of q . k for every key of the page;
 //   with several query heads per kv head the per-head page scores are added.
+#include <algorithm>
+
 #include "fier_dev.h"
 #include "fier_kernels.h"
 
@@ -153,26 +155,27 @@ __global__ __launch_bounds__(256) void page_mean_kernel(const float* __restrict_
   out[(size_t)unit * n_pages + p] = r;
 }
 
-// grid (ceil(entries / 1024), units), block 256: all tokens of the selected pages (ascending page list), clipped to the
+// grid (up to ceil(entries / 1024), units), block 256: all tokens of the selected pages (ascending page list), clipped to the
 // length; a thread writes four consecutive entries, which lie in one page.  Only the last page of a sequence can be
 // partial and it can only be last in the list, so entry k starts at k * P = k << pshift.  Latency bound (a page number,
 // then its tokens): one workgroup per unit walking the list took 7.0 us at 32 units x 3600 tokens, this
 // takes 3.0 (the page selector's step replayed as a graph 41.4 -> 38.2; called one by one it is bound by the calls).
+//   The list's capacity sets the grid, its length the work: no more than about 2048 workgroups, which walk a long list (512
+// units, 8 pages of a capacity of 8192: 26 us with a workgroup per 1024 entries, 3.3 now; 900 pages of 900 8.4 / 7.6).
 __global__ __launch_bounds__(256) void expand_pages_kernel(const int32_t* __restrict__ page_idx,
                                                            const int32_t* __restrict__ page_count, int max_pages,
                                                            const int32_t* __restrict__ seq_lens, int extra, int pshift,
                                                            int32_t* __restrict__ idx, int32_t* __restrict__ count,
                                                            int max_budget, int n_kv_heads, int max_ctx) {
   const int unit = blockIdx.y, P = 1 << pshift;
-  const int e = (int)(blockIdx.x * 1024 + threadIdx.x * 4);
-  const int k = e >> pshift;
   const int32_t* pl = page_idx + (size_t)unit * max_pages;
   int L = seq_lens[unit / n_kv_heads] + extra;
   L = L < 0 ? 0 : (L > max_ctx ? max_ctx : L);
   int n = page_count[unit];
   n = n < 0 ? 0 : (n > max_pages ? max_pages : n);
-  if (e >= 0 && k < n) {
-    const int64_t t0 = (int64_t)pl[k] * P + (e - (k << pshift));
+  const int64_t end = (int64_t)n * P < max_budget ? (int64_t)n * P : max_budget;
+  for (int64_t e = blockIdx.x * 1024 + threadIdx.x * 4; e < end; e += (int64_t)gridDim.x * 1024) {
+    const int64_t t0 = (int64_t)pl[e >> pshift] * P + (e & (P - 1));
     int32_t* const dst = idx + (size_t)unit * max_budget + e;
     if (t0 >= 0 && t0 + 3 < L && e + 3 < max_budget && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
       const int t = (int)t0;
@@ -266,7 +269,8 @@ hipError_t launch_expand_pages(const int32_t* page_idx, const int32_t* page_coun
                                const int32_t* seq_lens, int extra, int P, int32_t* idx, int32_t* count,
                                int max_budget, int units, int n_kv_heads, int max_ctx, hipStream_t st) {
   const int64_t entries = (int64_t)max_pages * P < max_budget ? (int64_t)max_pages * P : max_budget;
-  const dim3 grid((unsigned)((entries + 1023) / 1024), units);
+  const int64_t most = (2048 + units - 1) / units;
+  const dim3 grid((unsigned)std::min<int64_t>((entries + 1023) / 1024, most), units);
   const int pshift = P == 32 ? 5 : P == 16 ? 4 : 3;
   expand_pages_kernel<<<grid, 256, 0, st>>>(page_idx, page_count, max_pages, seq_lens, extra, pshift, idx, count,
                                              max_budget, n_kv_heads, max_ctx);

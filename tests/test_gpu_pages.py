@@ -124,3 +124,58 @@ def test_page_mean_of_quantized_scores(gu, oracle):
         n = -(-int(L[u]) // 16)
         assert np.all(np.isneginf(got[u, n:]))
         assert np.all(np.abs(got[u, :n] - want[u, :n]) <= 1e-5 * (np.abs(sc_h[u]).max() + 1e-30))
+
+
+@pytest.mark.parametrize("batch,heads,max_pages,page", [(64, 8, 900, 16), (1, 8, 2048, 32), (700, 8, 129, 8)])
+def test_expansion_of_short_and_long_lists(batch, heads, max_pages, page):
+    """Lists shorter and longer than what the grid covers at once (about 2048 pieces of 1024 entries),
+    empty ones, a partial last page, a row pitch that is no multiple of four entries and smaller than a full list."""
+    max_ctx, units = 65536, batch * heads
+    cfg = B.make_config(batch, heads, heads, max_ctx)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(units)
+    cnt = torch.randint(0, max_pages + 1, (units,), generator=gen, device="cuda", dtype=torch.int32)
+    cnt[0], cnt[units - 1] = 0, max_pages
+    rand = torch.rand((units, max_ctx // page), generator=gen, device="cuda")
+    pages = rand.argsort(dim=1)[:, :max_pages].sort(dim=1).values.to(torch.int32).contiguous()
+    lens = torch.full((batch,), max_ctx - 5, dtype=torch.int32, device="cuda")
+    mb = max_pages * page - 3
+    idx = torch.full((units, mb), -7, dtype=torch.int32, device="cuda")
+    n = torch.zeros(units, dtype=torch.int32, device="cuda")
+    B.expand_pages(cfg, pages, cnt, max_pages, lens, 1, page, idx, n, mb)
+    tok = (pages.long()[:, :, None] * page + torch.arange(page, device="cuda")).reshape(units, -1)[:, :mb]
+    at = torch.arange(mb, device="cuda")[None]
+    there = (at < cnt[:, None].long() * page) & (tok < max_ctx - 4)
+    assert torch.equal(idx.long(), torch.where(there, tok, -7))
+    assert torch.equal(n.long(), there.sum(dim=1))
+
+
+def test_expansion_of_a_short_list_in_a_large_capacity_is_quick():
+    """8 pages per unit take about as long with room for 8192 as with room for 8 (without a bound on the grid 10 times)."""
+    batch, heads, max_ctx, page = 64, 8, 131072, 16
+    cfg = B.make_config(batch, heads, heads, max_ctx)
+    units, best = batch * heads, {}
+    cnt = torch.full((units,), 8, dtype=torch.int32, device="cuda")
+    lens = torch.full((batch,), max_ctx, dtype=torch.int32, device="cuda")
+    n = torch.zeros(units, dtype=torch.int32, device="cuda")
+    for max_pages in (8, 8192):
+        pages = torch.arange(max_pages, dtype=torch.int32, device="cuda").repeat(units, 1).contiguous()
+        idx = torch.zeros((units, max_pages * page), dtype=torch.int32, device="cuda")
+
+        def calls():
+            for _ in range(50):
+                B.expand_pages(cfg, pages, cnt, max_pages, lens, 0, page, idx, n, max_pages * page)
+
+        calls()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            calls()
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        for _ in range(4):
+            e0.record()
+            graph.replay()
+            e1.record()
+            torch.cuda.synchronize()
+            best[max_pages] = min(best.get(max_pages, 1e9), e0.elapsed_time(e1))
+    assert best[8192] < 3 * best[8], best
