@@ -112,6 +112,17 @@ struct LayerBatch {
   LayerShift at[kMaxLayersPerLaunch];
   __device__ __forceinline__ int64_t ws_shift(int z) const { return (int64_t)(n - 1 - z) * ws_stride; }
 };
+// Which of a unit's n workgroups takes place `wg` in a launch of several layers.  Workgroups go round-robin to the XCDs and
+// their shader engines.  Where sequences are short and the capacity large only a unit's first workgroups have work, and with
+// an even n those of all units would meet on a few of them; unit (or group of units) number t therefore starts at a place
+// of its own.  `period`: places until the round-robin is back where it was.  us per call of 2 layers, layer by layer / in
+// order / turned: 488 units of 1899 tokens in 32000 rows, 8 heads 118 / 257 / 107; 400 of 560 in 32768, 4 heads 92 / 133 / 74;
+// over 1326 pairs of a shape with full sequences and a number of layers 0.5 % faster than in order.
+__device__ __forceinline__ int turned_wg(int wg, int n, uint32_t t, uint32_t period) {
+  const uint32_t w = (uint32_t)n;
+  if (w & 1u) return wg;
+  return (int)(((uint32_t)wg + (w == 2u ? (period == 32u ? t >> 1 : t >> 2) : t) + t * w / period) % w);
+}
 struct OneLayer {};  // a launch of a single layer: nothing to look up (the table in front of a workgroup's first loads
                      // cost 0.7 us of 19 at 8 units x 4k, 1.4 us of 31 at 32 units x 32k)
 template <typename T>

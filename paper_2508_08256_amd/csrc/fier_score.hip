@@ -116,7 +116,9 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP <= 2 ? 5 : 4) : 1) void s
   const bool append_wg = HIST && (int)blockIdx.x < n_units;
   const int wid = (int)blockIdx.x - (HIST ? n_units : 0);
   const int unit = append_wg ? (int)blockIdx.x : wid / n_x;
-  const int range = append_wg ? -1 : wid - unit * n_x;
+  int range = append_wg ? -1 : wid - unit * n_x;
+  if constexpr (std::is_same<LAYERS, LayerBatch>::value)
+    if (!append_wg) range = turned_wg(range, n_x, (uint32_t)unit, 256u);
   const int b = unit / n_kv_heads;
   if constexpr (std::is_same<LAYERS, LayerBatch>::value) {  // this workgroup's layer
     const int z = (int)blockIdx.z;

@@ -697,6 +697,9 @@ __global__ __launch_bounds__(kStepThreads, step_wgs_per_cu(NREP)) void step_atte
   }
   int unit, wg;
   step_unit_wg(a, (int)blockIdx.x, (int)blockIdx.y, unit, wg);
+  if constexpr (std::is_same<LAYERS, LayerBatch>::value)
+    if (a.order != 1)
+      wg = a.order == 2 ? turned_wg(wg, a.wgs_per_unit, (uint32_t)unit >> 3, 32u) : turned_wg(wg, a.wgs_per_unit, (uint32_t)unit, 256u);
   step_attend_body<DT, NREP, RPW, STREAM>(a, unit, wg, lds);
 }
 
