@@ -342,6 +342,21 @@ def measure(args, workload, budget_arg, detail):
                     B.decode_step_phase(*a, p)
         return run
 
+    # a step of several layers runs them side by side; a model, whose layers need each other's output, calls one by one
+    us_one_by_one = None
+    if NL > 1 and args.selector == "fier" and not args.dense_first:
+        def one_by_one(i):
+            for a in largs[i % R]:
+                B.decode_step(*a)
+
+        us_one_by_one, _ = timed(one_by_one, max(4, steps // 4), 2)
+    us_layer = us_step / NL
+    us_alone = us_layer if us_one_by_one is None else us_one_by_one / NL   # one layer's call, as dense_attn_us is
+    several = {} if us_one_by_one is None else {
+        "several_layers_per_call": "us_per_layer is a call's time over its layers, which run side by side; "
+                                   "us_per_layer_one_by_one is a call per layer, what generating a token takes",
+        "us_per_layer_one_by_one": round(us_one_by_one / NL, 3)}
+
     for r in range(R):                    # a whole step per layer cache on its own workspace
         phase(1, 2, 3)(r)
     torch.cuda.synchronize()
@@ -372,7 +387,6 @@ def measure(args, workload, budget_arg, detail):
     us_dense, _ = timed(st_dense, max(24, ns // 10), 4)
 
     ab = algorithmic_bytes(w, lens, buds)          # per layer
-    us_layer = us_step / NL
     achieved = ab["total"] / (us_layer * 1e-6) / 1e9
     # The dominant kernel by algorithmic bytes is the one that gathers the selected K / V rows (+ q in, output out):
     # the second kernel of the two-kernel form (threshold + attention + merge in one launch, timed as first + second
@@ -402,8 +416,8 @@ def measure(args, workload, budget_arg, detail):
                 "hbm_frac": round(achieved / HBM_PEAK_GBPS, 4), "kernels_us": kernels_us,
                 "dominant_kernel": {"kernel": dom_name, "GBps": round(dom_gbps, 1),
                                     "frac": round(dom_gbps / HBM_PEAK_GBPS, 4), "bytes_per_launch": gather_bytes},
-                "dense_attn_us": round(us_dense, 3), "speedup_vs_dense_attn": round(us_dense / us_layer, 3),
-                "steps": steps, "config": config}
+                "dense_attn_us": round(us_dense, 3), "speedup_vs_dense_attn": round(us_dense / us_alone, 3),
+                **several, "steps": steps, "config": config}
 
     # what this machine's memory system gives a plain streaming copy (torch's own, 1 GiB operands, far beyond the
     # 256 MB Infinity Cache): context for the roofline figures, which are quoted against the nominal 8 TB/s
@@ -524,7 +538,8 @@ def measure(args, workload, budget_arg, detail):
         "quantize_GBps": round(quant_bytes / (us_quant * 1e-6) / 1e9, 1),
         "dense_attn_us": round(us_dense, 3),
         "dense_attn_GBps": round(dense_bytes / (us_dense * 1e-6) / 1e9, 1),
-        "speedup_vs_dense_attn": round(us_dense / us_layer, 3),
+        "speedup_vs_dense_attn": round(us_dense / us_alone, 3),
+        **several,
         "measured_ceiling": ceiling,
         "roofline": {"bound": "hbm", "kernel": dom_name,
                      "achieved": round(dom_gbps, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
@@ -557,13 +572,14 @@ def decode_loop(args, w, cfg, caches, qs, kns, vns, seq_lens, budgets, lens, bud
     kn = torch.cat(kns).contiguous()
     vn = torch.cat(vns).contiguous()
     batch, Hq = w["batch"], w["n_q_heads"]
-    ws = B.make_workspace(cfg, budget)
+    ws = B.make_workspace(cfg, budget, NLt)
+    ws_one = B.make_workspace(cfg, budget, 1)
     out = torch.zeros((NLt, batch, Hq, 128), dtype=torch.float32, device="cuda")
     idx = torch.zeros((NLt, cfg.units, budget), dtype=torch.int32, device="cuda")
     cnt = torch.zeros((NLt, cfg.units), dtype=torch.int32, device="cuda")
     lens0 = seq_lens.clone()
 
-    def tokens(n, with_list=False):
+    def tokens(n, with_list=False, ws=ws):
         # the attention output is the step's result; the ascending index list is an optional output
         for _ in range(n):
             B.decode_step(cfg, layers, q, kn, vn, budgets, budget, out, idx if with_list else None,
@@ -583,6 +599,7 @@ def decode_loop(args, w, cfg, caches, qs, kns, vns, seq_lens, budgets, lens, bud
     tokens(4)                                   # warm-up
     us_eager = timed_tokens(lambda: tokens(N))
     us_eager_list = timed_tokens(lambda: tokens(N, True))
+    us_in_order = timed_tokens(lambda: tokens(N, ws=ws_one))   # a workspace of one part: the layers run in order
     us_graph = None
     try:
         seq_lens.copy_(lens0)
@@ -616,6 +633,7 @@ def decode_loop(args, w, cfg, caches, qs, kns, vns, seq_lens, budgets, lens, bud
         "achieved_GBps": round(ab["total"] / (us_layer * 1e-6) / 1e9, 1),
         "hbm_frac": round(ab["total"] / (us_layer * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
         "us_per_token_eager": round(us_eager, 3),
+        "us_per_layer_in_order": round(us_in_order / NLt, 3),   # value: the layers of a token's call side by side
         "us_per_layer_with_index_list": round(us_eager_list / NLt, 3),
         "us_per_token_graph": None if us_graph is None else round(us_graph, 3),
         "us_per_layer_graph": None if us_graph is None else round(us_graph / NLt, 3),

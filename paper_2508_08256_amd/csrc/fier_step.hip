@@ -820,8 +820,8 @@ int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
 //     4 + 4 + 2: 307 / 327 / 272; 88 units x 10k, 8 heads, B = 3239: 110 / 129 / 114);
 //   * 1500 rows or more where two layers need up to 1.4 times the workgroups the GPU holds: the second round is short,
 //     but lasts as long as a workgroup (200 units x 11.5k, 4 heads, B = 2969: 163 / 208 / 161).
-// Of 6218 measured pairs of a shape and a number of layers 151 had been slower by 2 to 27 % than layer by layer; 57 still
-// are, by 2 to 17 %, most of them two layers that fill the GPU one by one.
+// Of 6218 measured pairs of a shape and a number of layers 151 had been slower by 2 to 27 % than layer by layer; with this and
+// turned_wg 23 of 5260 are, by 2 to 15 %, most of them two layers that fill the GPU one by one.
 static int step_ranges_per_wg_layers(int units, int layers, int n_rep, int max_budget, int max_ctx) {
   const int rpw = step_ranges_per_wg(units * layers, n_rep, max_budget, max_ctx);
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
