@@ -28,10 +28,9 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint4* __restrict
                                                          float* __restrict__ pm, float* __restrict__ pl,
                                                          UnitCtl* __restrict__ ctl, float* __restrict__ out,
                                                          int n_kv_heads, int max_ctx, int unit_major, KvLayout lay) {
-  __shared__ float sh_o[NREP * kPartialFloats];
+  __shared__ __attribute__((aligned(16))) float sh_o[NREP * kPartialFloats];
   __shared__ uint32_t flag;
 
-  const int cn = threadIdx.x & 15;
   const int unit = unit_major ? blockIdx.x : blockIdx.y, split = unit_major ? blockIdx.y : blockIdx.x;
   const int b = unit / n_kv_heads;
   int n;
@@ -71,26 +70,22 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint4* __restrict
                   : kv.base + (size_t)j;
   };
 
-  uint4 qr[NREP];
-#pragma unroll
-  for (int r = 0; r < NREP; ++r) qr[r] = q[((size_t)unit * NREP + r) * (kD / 8) + cn];
-
-  AttnState<NREP> st;
+  GatherQuery<NREP> qr;
+  qr.load(q + (size_t)unit * NREP * (kD / 8));
+  GatherState<NREP> st;
   st.init();
   if constexpr (NREP >= 3) {
-    const uint4* q_unit = q + (size_t)unit * NREP * (kD / 8);
     if (sel)
-      attend_rows_mfma<DT, NREP, true, false, STREAM>(K, V, q_unit, row_sel, start, end, scale_log2e, st, sh_o, false,
-                                                      safe_row);
+      attend_rows_mfma<DT, NREP, true, false, STREAM>(K, V, qr, row_sel, start, end, scale_log2e, st, safe_row);
     else
-      attend_rows_mfma<DT, NREP, false, STREAM>(K, V, q_unit, row_all, start, end, scale_log2e, st, sh_o);
+      attend_rows_mfma<DT, NREP, false, STREAM>(K, V, qr, row_all, start, end, scale_log2e, st);
   } else {
     if (sel)
-      attend_rows<DT, NREP, true, STREAM>(K, V, qr, row_sel, start, end, scale_log2e, st, safe_row);
+      attend_rows<DT, NREP, true, STREAM>(K, V, qr.c, row_sel, start, end, scale_log2e, st, safe_row);
     else
-      attend_rows<DT, NREP, false, STREAM>(K, V, qr, row_all, start, end, scale_log2e, st);
+      attend_rows<DT, NREP, false, STREAM>(K, V, qr.c, row_all, start, end, scale_log2e, st);
   }
-  store_partials<NREP, true>(st, sh_o, unit, n_splits, split, po, pm, pl);
+  store_partials<DT, NREP, true>(st, sh_o, unit, n_splits, split, po, pm, pl);
   // the unit's last workgroup merges the partials of the splits in use
   const int used = (n + rows_per_wg - 1) / rows_per_wg;
   if (!last_arriver(&ctl[unit].arrive[0], (uint32_t)used, &flag)) return;
@@ -111,14 +106,13 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
     float* __restrict__ pm, float* __restrict__ pl, int32_t* __restrict__ idx_out, float* __restrict__ out,
     float* __restrict__ kabsmax, const float* __restrict__ newmax, int n_ranges, int n_kv_heads, int max_ctx,
     int order, int wgs_per_unit, KvLayout lay) {
-  __shared__ float sh_o[NREP * kPartialFloats > 4 * 130 ? NREP * kPartialFloats : 4 * 130];
+  __shared__ __attribute__((aligned(16))) float sh_o[NREP * kPartialFloats > 4 * 130 ? NREP * kPartialFloats : 4 * 130];
   __shared__ uint16_t rows[kRangeTokens * RPW];  // selected tokens, relative to the workgroup's first token
   __shared__ uint32_t scan_tmp[4];
   __shared__ uint32_t flag;
   __shared__ int32_t lblk[RPW * kRangeTokens / 64];  // paged rows: block numbers of this workgroup's tokens
 
   const int tid = threadIdx.x;
-  const int cn = tid & 15;
   // order: 0 = grid (workgroups, units); 1 = grid (units, workgroups); 2 = one-dimensional, groups of 8 units, a
   // group's workgroups together and unit % 8 fastest (see the launcher)
   int unit, wg;
@@ -208,10 +202,9 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
   FIER_PROF(21, unit == 0 && wg == 3)
 
   // ---- attention over the selected rows of these ranges --------------------------------------------------------
-  uint4 qr[NREP];
-#pragma unroll
-  for (int h = 0; h < NREP; ++h) qr[h] = q[((size_t)unit * NREP + h) * (kD / 8) + cn];
-  AttnState<NREP> st;
+  GatherQuery<NREP> qr;
+  qr.load(q + (size_t)unit * NREP * (kD / 8));
+  GatherState<NREP> st;
   st.init();
   const int first_block = tok0 >> kv.shift;
   auto row_of = [&](int j) {
@@ -220,13 +213,11 @@ __global__ __launch_bounds__(256) void select_attend_kernel(
                      : kv.base + (size_t)t;
   };
   if constexpr (NREP >= 3)
-    attend_rows_mfma<DT, NREP, false, false, true>(K, V, q + (size_t)unit * NREP * (kD / 8), row_of, 0, (int)n_sel_total,
-                                                   scale_log2e, st,
-                               sh_o);
+    attend_rows_mfma<DT, NREP, false, false, true>(K, V, qr, row_of, 0, (int)n_sel_total, scale_log2e, st);
   else
-    attend_rows<DT, NREP>(K, V, qr, row_of, 0, (int)n_sel_total, scale_log2e, st);
+    attend_rows<DT, NREP>(K, V, qr.c, row_of, 0, (int)n_sel_total, scale_log2e, st);
   FIER_PROF(22, unit == 0 && wg == 3)
-  store_partials<NREP, true>(st, sh_o, unit, n_slots, wg, po, pm, pl);
+  store_partials<DT, NREP, true>(st, sh_o, unit, n_slots, wg, po, pm, pl);
   FIER_PROF(23, unit == 0 && wg == 3)
   FIER_PROF_WG(6)
 

@@ -3,6 +3,8 @@
 // (fier_attn.hip) and the fused decode step (fier_step.hip).
 #pragma once
 
+#include <type_traits>
+
 #include "fier_dev.h"
 #include "fier_kernels.h"
 
@@ -111,154 +113,158 @@ __device__ __forceinline__ floatx4_t mfma_16x16x32(const uint4& a, const uint4& 
                                                  0, 0, 0);
 }
 
-constexpr int kPartialFloats = 4 * 16 * 10;  // LDS floats per query head: [wave][channel chunk][o[8], m, l]
-constexpr int kAttnMfmaLds = 4 * 144;  // LDS floats attend_rows_mfma needs: per wavefront p[16 tokens][8 heads], alpha[8]
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
+template <int DT>
+__device__ __forceinline__ floatx4_t mfma_16x16x16(uint2 a, uint2 b, floatx4_t c) {
+  if (DT == DT_F16)
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(half4_t, a), __builtin_bit_cast(half4_t, b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4_t, a), __builtin_bit_cast(short4_t, b), c, 0, 0, 0);
+}
 
-// The same for 3 to 8 query heads per kv head, where q.K^T for all heads of the group is a real (if skinny) dense
-// contraction: per wavefront and 16 gathered rows, S[head][token] comes from four v_mfma_f32_16x16x32 (A = the
-// queries, one matrix row per head, B = the K rows as they lie in memory: lane (n, kq) loads channels
-// 32c + 8kq .. + 7 of row n).  The softmax runs on S where the matrix core leaves it (lane = token, register = head),
-// the probabilities go through LDS to the lanes that own the V rows (a 16-lane row owns one V row, as in
-// attend_rows) and the P.V product stays on the vector ALUs.  One running (m, l) per head and wavefront.
-// q_unit: the unit's NREP query rows; sh: kAttnMfmaLds floats of LDS.  resume: st holds the result of an earlier
-// call by the same workgroup and the running softmax continues from it.  CHECKED / safe_row as in attend_rows.
+// LDS floats per query head of store_partials: [wave][channel chunk][o[8], m, l].  650 and not 640: the matrix-core
+// state's writes of all heads go out together, 16 lanes and a head pitch of a multiple of 64 words would meet in a bank.
+constexpr int kPartialFloats = 4 * 16 * 10 + 10;
+
+// ---- three to eight query heads per kv head: both products on the matrix cores -------------------------------------------
+// Per wavefront and tile of 16 gathered rows:
+//   S = K q^T   (rows = tokens, columns = query heads): four v_mfma_f32_16x16x32.  A = the K rows as they lie in memory
+//     (lane (n, kq) loads channels 32c + 8kq .. + 7 of row n), B = the queries.  Lane (n, kq) is left with the logits of
+//     tokens 4kq .. 4kq + 3 for column n -- which is the B operand of the second product as it stands;
+//   O^T += V^T P^T (rows = channels, columns = heads): eight v_mfma_f32_16x16x16.  Lane (n, kq) loads channels 8n .. 8n + 7
+//     of the V rows of tokens 4kq .. 4kq + 3 (a row is 16 lanes, 256 contiguous bytes); the four tokens of one of its
+//     channels, two byte permutations, are the lane's A operand of the product over channels 8m + c, m = 0..15.
+// So nothing crosses lanes but the maximum over the four lane rows, and each lane keeps 32 of its column's 128 outputs.
+// The probabilities stay exact to 24 bits: p = hi + mid + lo, each an operand of its own in the V type (8 bits each for
+// bf16; fp16, p scaled by 2^15: 11 each).  The 16 columns have room for them: column n is part n / kCols of head n % kCols,
+// kCols = NREP up to five heads; from six on hi and mid take the columns and lo, half of it each, a second product into the
+// same sums.
+//   Before, P.V ran on the vector ALUs, 32 V elements and 32 x 4 multiply-adds of each lane per tile and head group behind an
+// exchange of p through LDS: about 350 vector instructions per tile at four heads (115 now), 141 to 157 registers at four
+// or five heads and 182 to 206 at six to eight, i.e. three or two workgroups per CU instead of four.
+template <int NREP>
+struct MfmaState {
+  static constexpr int kCols = NREP <= 5 ? NREP : 8;
+  float m, l;      // running maximum of the lane's column (the same in its four lanes), its own tokens' part of the sum
+  floatx4_t o[8];  // o[c][i]: channel 8 (4 kq + i) + c of the lane's column
+  __device__ __forceinline__ void init() {
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) o[c] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+};
+
+// The running state of a gather and what it needs of the queries, by the number of query heads per kv head.
+template <int NREP>
+using GatherState = std::conditional_t<(NREP >= 3), MfmaState<NREP>, AttnState<NREP>>;
+template <int NREP>
+struct GatherQuery {
+  uint4 c[NREP >= 3 ? 4 : NREP];
+  // q_unit: the unit's NREP query rows
+  __device__ __forceinline__ void load(const uint4* __restrict__ q_unit) {
+    const int n = threadIdx.x & 15, kq = threadIdx.x >> 4 & 3;
+    if constexpr (NREP >= 3) {
+      constexpr int kCols = MfmaState<NREP>::kCols;
+      const int h = n % kCols;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] = q_unit[(size_t)(h < NREP ? h : 0) * (kD / 8) + 4 * k + kq];
+    } else {
+#pragma unroll
+      for (int r = 0; r < NREP; ++r) c[r] = q_unit[(size_t)r * (kD / 8) + n];
+    }
+  }
+};
+
+// The largest value among the four lanes with the same lane % 16.
+__device__ __forceinline__ float rows_allmax(float x) {
+  typedef unsigned int u2_t __attribute__((ext_vector_type(2)));
+  const u2_t a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const u2_t b = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// x without its leading bits (mask: those of the part's format), exactly; x for mask 0
+__device__ __forceinline__ float drop_part(float x, uint32_t mask) { return x - __uint_as_float(__float_as_uint(x) & mask); }
+// Four non-negative values, each cut off to the format's leading bits, as an operand.
+template <int DT>
+__device__ __forceinline__ uint2 pack_part(const float (&x)[4]) {
+  if (DT == DT_F16)  // rounds towards zero
+    return make_uint2(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x[0], x[1])),
+                      __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(x[2], x[3])));
+  return make_uint2(__builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u),
+                    __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07060302u));
+}
+
+// As attend_rows, for three to eight query heads per kv head.  STREAM_V: the V rows with the streaming hint (the K rows, which
+// are loaded in four pieces per row, keep plain loads in gathers).
 template <int DT, int NREP, bool CHECKED = false, bool STREAM = false, bool STREAM_V = STREAM, class RowOf>
 __device__ __forceinline__ void attend_rows_mfma(const uint4* __restrict__ K, const uint4* __restrict__ V,
-                                                 const uint4* __restrict__ q_unit, RowOf row_of, int start, int end,
-                                                 float scale_log2e, AttnState<NREP>& st, float* sh, bool resume = false,
-                                                 size_t safe_row = 0) {
-  static_assert(NREP >= 1 && NREP <= 8, "heads per kv head");
-  static_assert(NREP * kPartialFloats >= kAttnMfmaLds || NREP < 3, "the callers lend the partials' LDS");
+                                                 const GatherQuery<NREP>& q, RowOf row_of, int start, int end,
+                                                 float scale_log2e, MfmaState<NREP>& st, size_t safe_row = 0) {
+  static_assert(NREP >= 3 && NREP <= 8, "heads per kv head");
+  constexpr int kCols = MfmaState<NREP>::kCols;
+  constexpr uint32_t kLead = DT == DT_F16 ? 0xffffe000u : 0xffff0000u;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 15, kq = lane >> 4;  // matrix view: token column n, K quarter kq; result rows 4kq..4kq+3
-  float* p_sh = sh + wave * 144;            // [token][8 heads], then alpha[8]
-  uint4 qa[4];
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-    qa[c] = n < NREP ? q_unit[(size_t)n * (kD / 8) + 4 * c + kq] : make_uint4(0, 0, 0, 0);
-  // running max and sum of head 4kq + i in element i, the same in the 16 lanes of a lane row
-  float m_run[4], l_run[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    m_run[i] = -INFINITY;
-    l_run[i] = 0.f;
-  }
-  if (resume) {
-    // the state left by the earlier call: the wavefront's running maximum of head h in every lane, its running sum
-    // in lane row 0; back into the matrix view (head 4kq + i in element i) through LDS
-    if (lane == 0) {
-#pragma unroll
-      for (int h = 0; h < NREP; ++h) {
-        p_sh[h] = st.m[h];
-        p_sh[8 + h] = st.l[h];
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (4 * kq + i < NREP) {
-        m_run[i] = p_sh[4 * kq + i];
-        l_run[i] = p_sh[8 + 4 * kq + i];
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // reads done before the first tile's writes
-  }
+  const int n = lane & 15, kq = lane >> 4;
+  const int part = n / kCols;
+  const uint32_t cut1 = part >= 1 ? kLead : 0u, cut2 = part >= 2 ? kLead : 0u;
   for (int j0 = start + wave * 16; j0 < end; j0 += 64) {
-    // K rows in the matrix view (token j0 + n), V rows in the row-owner view (tokens j0 + 4u + kq, channels 8n..8n+7)
-    const int jk = j0 + n;
-    bool valid = jk < end;
     uint4 kk[4], vv[4];
-    size_t rk = row_of(valid ? jk : start);
-    if (CHECKED) {
-      valid = valid && rk != kNoRow;
-      rk = rk == kNoRow ? safe_row : rk;
-    }
+    size_t rk = row_of(j0 + n < end ? j0 + n : start);
+    if (CHECKED) rk = rk == kNoRow ? safe_row : rk;
     rk *= (kD / 8);
 #pragma unroll
     for (int c = 0; c < 4; ++c) kk[c] = STREAM ? load_stream(K + rk + 4 * c + kq) : K[rk + 4 * c + kq];
+    bool valid[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int jv = j0 + 4 * u + kq;
-      size_t rv = row_of(jv < end ? jv : start);
-      if (CHECKED) rv = rv == kNoRow ? safe_row : rv;  // its probability is zero: the K side masks it
+      const int jv = j0 + 4 * kq + u;
+      valid[u] = jv < end;
+      size_t rv = row_of(valid[u] ? jv : start);
+      if (CHECKED) {
+        valid[u] = valid[u] && rv != kNoRow;
+        rv = rv == kNoRow ? safe_row : rv;
+      }
       vv[u] = STREAM_V ? load_stream(V + rv * (kD / 8) + n) : V[rv * (kD / 8) + n];
     }
-    floatx4_t sacc = {0.f, 0.f, 0.f, 0.f};
+    floatx4_t s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) sacc = mfma_16x16x32<DT>(qa[c], kk[c], sacc);
-    float p[4], alpha[4];
+    for (int c = 0; c < 4; ++c) s = mfma_16x16x32<DT>(kk[c], q.c[c], s);
+    float p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = valid[i] ? s[i] * scale_log2e : -INFINITY;
+    const float mx = fmaxf(st.m, rows_allmax(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]))));
+    const float mref = mx == -INFINITY ? 0.f : mx;
+    const float alpha = __builtin_amdgcn_exp2f(st.m - mref);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)  // the scaled logit unrounded
+      p[i] = valid[i] ? __builtin_amdgcn_exp2f(fmaf(s[i], scale_log2e, -mref)) : 0.f;
+    st.l = st.l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+    st.m = mx;
+    if (__ballot(alpha != 1.0f)) {  // the maxima settle after a few tiles
+#pragma unroll
+      for (int c = 0; c < 8; ++c) st.o[c] *= alpha;
+    }
+    uint2 pb, pb_lo;
+    float lo[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float logit = valid ? sacc[i] * scale_log2e : -INFINITY;
-      float tmax = logit;
-      tmax = fmaxf(tmax, row_ror<8>(tmax));
-      tmax = fmaxf(tmax, row_ror<4>(tmax));
-      tmax = fmaxf(tmax, row_ror<2>(tmax));
-      tmax = fmaxf(tmax, row_ror<1>(tmax));
-      const float mx = fmaxf(m_run[i], tmax);
-      const float mref = mx == -INFINITY ? 0.f : mx;
-      alpha[i] = __builtin_amdgcn_exp2f(m_run[i] - mref);
-      p[i] = __builtin_amdgcn_exp2f(logit - mref);
-      l_run[i] = l_run[i] * alpha[i] + row_allsum(p[i]);
-      m_run[i] = mx;
+      const float x = DT == DT_F16 ? p[i] * 0x1p15f : p[i];  // the small ones stay normal fp16 numbers
+      p[i] = drop_part(drop_part(x, cut1), cut2);
+      if (kCols == 8) lo[i] = 0.5f * drop_part(drop_part(x, kLead), kLead);
     }
-    if (4 * kq < NREP) {
-      *reinterpret_cast<float4*>(p_sh + n * 8 + 4 * kq) = make_float4(p[0], p[1], p[2], p[3]);
-      if (n == 0) *reinterpret_cast<float4*>(p_sh + 128 + 4 * kq) = make_float4(alpha[0], alpha[1], alpha[2], alpha[3]);
+    pb = pack_part<DT>(p);
+    if constexpr (kCols == 8) pb_lo = pack_part<DT>(lo);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      auto word = [&](int u) { return c < 2 ? vv[u].x : (c < 4 ? vv[u].y : (c < 6 ? vv[u].z : vv[u].w)); };
+      const uint32_t sel = c & 1 ? 0x07060302u : 0x05040100u;
+      const uint2 va = make_uint2(__builtin_amdgcn_perm(word(1), word(0), sel), __builtin_amdgcn_perm(word(3), word(2), sel));
+      st.o[c] = mfma_16x16x16<DT>(va, pb, st.o[c]);
+      if constexpr (kCols == 8) st.o[c] = mfma_16x16x16<DT>(va, pb_lo, st.o[c]);
     }
-    // written and read by different lanes of this same wavefront: LDS operations of a wavefront complete in order
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float al[8], pw[4][8];
-    {
-      const float4 a0 = *reinterpret_cast<const float4*>(p_sh + 128);
-      al[0] = a0.x, al[1] = a0.y, al[2] = a0.z, al[3] = a0.w;
-      if (NREP > 4) {
-        const float4 a1 = *reinterpret_cast<const float4*>(p_sh + 132);
-        al[4] = a1.x, al[5] = a1.y, al[6] = a1.z, al[7] = a1.w;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float4 p0 = *reinterpret_cast<const float4*>(p_sh + (4 * u + kq) * 8);
-        pw[u][0] = p0.x, pw[u][1] = p0.y, pw[u][2] = p0.z, pw[u][3] = p0.w;
-        if (NREP > 4) {
-          const float4 p1 = *reinterpret_cast<const float4*>(p_sh + (4 * u + kq) * 8 + 4);
-          pw[u][4] = p1.x, pw[u][5] = p1.y, pw[u][6] = p1.z, pw[u][7] = p1.w;
-        }
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // reads done before the next tile's writes
-    float vf[4][8];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const uint32_t vw[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        vf[u][2 * c] = lo16f<DT>(vw[c]);
-        vf[u][2 * c + 1] = hi16f<DT>(vw[c]);
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < NREP; ++h)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        float o = st.o[h][c] * al[h];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) o += pw[u][h] * vf[u][c];
-        st.o[h][c] = o;
-      }
-  }
-  // the per-wavefront (m, l) into the per-lane state: every lane row carries m, the first one also l
-  if (4 * kq < NREP && n == 0) {
-    *reinterpret_cast<float4*>(p_sh + 4 * kq) = make_float4(m_run[0], m_run[1], m_run[2], m_run[3]);
-    *reinterpret_cast<float4*>(p_sh + 8 + 4 * kq) = make_float4(l_run[0], l_run[1], l_run[2], l_run[3]);
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-  for (int h = 0; h < NREP; ++h) {
-    st.m[h] = p_sh[h];
-    st.l[h] = kq == 0 ? p_sh[8 + h] : 0.f;
   }
 }
 
@@ -269,20 +275,17 @@ __device__ __forceinline__ float xor16(float x) {
 __device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32, 64); }
 
 
-// Combine the 16 lane-row states of the workgroup per query head and write one partial (m, l, o[128]) per head
-// into slot `slot` of the unit's partial arrays.  The four lane rows of a wavefront are folded with cross-lane
-// moves first, so that only one state per wavefront and head goes through LDS and all heads share one barrier.
-// sh: NREP * kPartialFloats floats.  Contains barriers: every thread of the workgroup calls it.
-// mark: the slot's l goes out as -(l + 1) (l >= 0, so the sign is free): a workgroup of the step records that way that
-// its partial lacks its threshold-bin rows (merge_heads takes such a slot with its true l).
-template <int NREP, bool COHERENT>
-__device__ __forceinline__ void store_partials(const AttnState<NREP>& st, float* sh, int unit, int n_slots, int slot,
-                                               float* __restrict__ po, float* __restrict__ pm,
-                                               float* __restrict__ pl, bool mark = false) {
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+// value of lane i + N of the row of 16 lanes (0 past its end)
+template <int N>
+__device__ __forceinline__ float row_from(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x100 + N, 0xf, 0xf, true));
+}
+
+// The wavefront's state into LDS, sh + head * kPartialFloats: [wave][channel chunk of 8][o[8], m, l].
+template <int DT, int NREP>
+__device__ __forceinline__ void wave_partials(const AttnState<NREP>& st, float* sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rs = lane >> 4, cn = lane & 15;
-  __syncthreads();  // sh may still be read as something else by a slower wavefront
 #pragma unroll
   for (int r = 0; r < NREP; ++r) {
     float M = fmaxf(st.m[r], xor16(st.m[r]));
@@ -306,6 +309,46 @@ __device__ __forceinline__ void store_partials(const AttnState<NREP>& st, float*
       dst[9] = l;
     }
   }
+}
+template <int DT, int NREP>
+__device__ __forceinline__ void wave_partials(const MfmaState<NREP>& st, float* sh) {
+  constexpr int kCols = MfmaState<NREP>::kCols;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = lane & 15, kq = lane >> 4;
+  float l = st.l;
+  l += xor16(l);
+  l += xor32(l);
+  float* dst = sh + n * kPartialFloats + (wave * 16 + 4 * kq) * 10;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float o[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {  // hi + mid + lo
+      o[c] = st.o[c][i] + row_from<kCols>(st.o[c][i]);
+      if (kCols <= 5) o[c] += row_from<2 * kCols <= 10 ? 2 * kCols : 10>(st.o[c][i]);
+      if (DT == DT_F16) o[c] *= 0x1p-15f;
+    }
+    if (n < NREP) {
+#pragma unroll
+      for (int c = 0; c < 8; c += 2) *reinterpret_cast<float2*>(dst + i * 10 + c) = make_float2(o[c], o[c + 1]);
+      *reinterpret_cast<float2*>(dst + i * 10 + 8) = make_float2(st.m, l);
+    }
+  }
+}
+
+// Combine the wavefronts' states of the workgroup per query head and write one partial (m, l, o[128]) per head into slot
+// `slot` of the unit's partial arrays.  A wavefront's lanes are folded first (wave_partials), so that only one state per
+// wavefront and head goes through LDS and all heads share one barrier.
+// sh: NREP * kPartialFloats floats.  Contains barriers: every thread of the workgroup calls it.
+// mark: the slot's l goes out as -(l + 1) (l >= 0, so the sign is free): a workgroup of the step records that way that
+// its partial lacks its threshold-bin rows (merge_heads takes such a slot with its true l).
+template <int DT, int NREP, bool COHERENT>
+__device__ __forceinline__ void store_partials(const GatherState<NREP>& st, float* sh, int unit, int n_slots, int slot,
+                                               float* __restrict__ po, float* __restrict__ pm,
+                                               float* __restrict__ pl, bool mark = false) {
+  const int tid = threadIdx.x;
+  __syncthreads();  // sh may still be read as something else by a slower wavefront
+  wave_partials<DT, NREP>(st, sh);
   __syncthreads();
   // thread -> (head parity, channel): threads 0..127 take the even heads, 128..255 the odd ones
   const int ch = tid & 127, chunk = ch >> 3, e = ch & 7;

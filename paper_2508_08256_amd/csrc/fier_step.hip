@@ -282,7 +282,6 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int cn = tid & 15;
   const int max_ctx = a.max_ctx;
   const int b = unit / a.n_kv_heads;
   UnitCtl* __restrict__ c = &a.ctl[unit];
@@ -422,11 +421,9 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
   uint32_t chk_sum = 0;  // (tests) sum of the token indices this thread put on the list
 
   // ---- 3. the exact threshold, found by the unit's last arriver ------------------------------------------------------
-  uint4 qr[NREP];
-#pragma unroll
-  for (int h = 0; h < NREP; ++h) qr[h] = a.q[((size_t)unit * NREP + h) * (kD / 8) + cn];
-  const uint4* q_unit = a.q + (size_t)unit * NREP * (kD / 8);
-  AttnState<NREP> st;
+  GatherQuery<NREP> qr;
+  qr.load(a.q + (size_t)unit * NREP * (kD / 8));
+  GatherState<NREP> st;
   st.init();
   const int first_block = tok0 >> kv.shift;
   auto row_own = [&](int j) {
@@ -434,11 +431,11 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
     return kv.blocks ? (size_t)lblk[(t >> kv.shift) - first_block] * kv.block_stride + kv.base + (size_t)(t & kv.mask)
                      : kv.base + (size_t)t;
   };
-  auto attend_own = [&](int from, int to, bool resume) {
+  auto attend_own = [&](int from, int to) {
     if constexpr (NREP >= 3)
-      attend_rows_mfma<DT, NREP, false, false, STREAM>(a.K, a.V, q_unit, row_own, from, to, a.scale_log2e, st, sh_o, resume);
+      attend_rows_mfma<DT, NREP, false, false, STREAM>(a.K, a.V, qr, row_own, from, to, a.scale_log2e, st);
     else
-      attend_rows<DT, NREP, false, STREAM>(a.K, a.V, qr, row_own, from, to, a.scale_log2e, st);
+      attend_rows<DT, NREP, false, STREAM>(a.K, a.V, qr.c, row_own, from, to, a.scale_log2e, st);
   };
   bool picked = true;  // the workgroup's threshold-bin rows are on its list (or it has none)
   uint32_t T = 0;
@@ -495,7 +492,7 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
   }
   FIER_PROF_WG(3)
   // ---- 4. attention over the sure rows, while the unit's threshold is being found ----------------------------------
-  attend_own(0, n_rows, false);
+  attend_own(0, n_rows);
   const int n_sure = n_rows;
   FIER_PROF_WG(4)
   // ---- 5. the threshold is picked up; the selected candidates join the row list -----------------------------------
@@ -547,7 +544,7 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
     __syncthreads();  // the row list is complete
   }
   if (tid == 0) store_coherent(&usel[wg], (uint32_t)n_rows);  // the merging workgroup may add to it
-  attend_own(n_sure, n_rows, true);
+  attend_own(n_sure, n_rows);
   FIER_PROF_WG(5)
   if (a.flags & 2) {
     for (int j = tid; j < n_rows; j += kStepThreads) chk_sum += (uint32_t)(tok0 + (int)rows[j]);
@@ -558,7 +555,7 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
   // a partial that lacks the workgroup's threshold-bin rows is marked as such (the sign of its l), and the workgroup
   // counts itself in the upper half of the arrival counter: the merging workgroup learns from the counter's value,
   // without loading anything, whether there are such rows
-  store_partials<NREP, true>(st, sh_o, unit, n_slots, wg, a.po, a.pm, a.pl, !picked);
+  store_partials<DT, NREP, true>(st, sh_o, unit, n_slots, wg, a.po, a.pm, a.pl, !picked);
   FIER_PROF_WG(6)
 
   const uint32_t before = arrive_add(&c->arrive[2], picked ? 1u : 0x10001u, &flag);
@@ -578,7 +575,6 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
         ss->seg_size[w] = load_coherent(&a.pl[(size_t)unit * NREP * n_slots + w]) < 0.f ? 1 : 0;  // head 0's slots
       __syncthreads();
       st.init();
-      bool resumed = false;
       uint32_t cnt_x = 0, sum_x = 0;
       for (int w = 0; w < nc; ++w) {
         if (!ss->seg_size[w]) continue;  // the same in every thread
@@ -602,11 +598,9 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
           __syncthreads();
           auto row_any = [&](int j) { return kv.row(base + (int)rows[j]); };
           if constexpr (NREP >= 3)
-            attend_rows_mfma<DT, NREP, false, false, STREAM>(a.K, a.V, q_unit, row_any, 0, (int)n_x, a.scale_log2e, st, sh_o,
-                                                             resumed);
+            attend_rows_mfma<DT, NREP, false, false, STREAM>(a.K, a.V, qr, row_any, 0, (int)n_x, a.scale_log2e, st);
           else
-            attend_rows<DT, NREP, false, STREAM>(a.K, a.V, qr, row_any, 0, (int)n_x, a.scale_log2e, st);
-          resumed = true;
+            attend_rows<DT, NREP, false, STREAM>(a.K, a.V, qr.c, row_any, 0, (int)n_x, a.scale_log2e, st);
           cnt_x += n_x;
         }
         // that workgroup's row count, for the index-list kernel (it arrived long ago: its own store is there)
@@ -617,7 +611,7 @@ __device__ __forceinline__ void step_attend_body(const StepArgs& a, const int un
         if (lane == 0 && sum_x) atomicAdd(&c->chk_sum, sum_x);
         if (tid == 0 && cnt_x) atomicAdd(&c->chk_cnt, cnt_x);
       }
-      store_partials<NREP, true>(st, sh_o, unit, n_slots, nc, a.po, a.pm, a.pl);
+      store_partials<DT, NREP, true>(st, sh_o, unit, n_slots, nc, a.po, a.pm, a.pl);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the spare slot is read back below by other wavefronts
       __syncthreads();
       n_used = nc + 1;
@@ -661,10 +655,12 @@ __device__ __forceinline__ void step_unit_wg(const StepArgs& a, int id_x, int id
 }
 
 // grid: wgs_per_unit workgroups per unit (dispatch order given by `order`), block 256.
-// (the second launch bound asks the compiler for the registers-per-thread that let 5 / 4 / 3 / 2 workgroups share a
-// CU: the gather wants many rows in flight per CU more than it wants registers -- but not at the price of spills:
-// with 4 query heads per kv head a bound of 4 left 60 bytes of scratch per lane and cost 3 to 5 us per step)
-constexpr int step_wgs_per_cu(int n_rep) { return n_rep <= 2 ? 5 : (n_rep <= 3 ? 4 : (n_rep <= 5 ? 3 : 2)); }
+// (the second launch bound asks the compiler for the registers-per-thread that let 5 or 4 workgroups share a CU: the gather
+// wants many rows in flight per CU more than it wants registers.  From three query heads per kv head on the matrix-core
+// gather takes 112 to 121 registers.  While its P.V product ran on the vector ALUs it was 3 workgroups at 4 or 5 heads and 2
+// from 6 on; us per step, then / now: 4 heads 8 units x 32k 25.8 / 24.2, 32 x 32k 37.3 / 34.7, 32 x 128k 57.7 / 55.6, 16
+// layers of 64 ragged units up to 8k 151 / 130; 7 heads 64 x 4k 29.8 / 25.8; 8 heads 32 x 16k 34.8 / 30.5)
+constexpr int step_wgs_per_cu(int n_rep) { return n_rep <= 2 ? 5 : 4; }
 // STREAM: the gathered rows are loaded with the streaming hint (with three or more query heads per kv head, where
 // the K rows go to the matrix cores in four pieces per row, the V rows only).
 template <int DT, int NREP, int RPW, bool STREAM, class LAYERS>
@@ -890,8 +886,8 @@ hipError_t launch_step_attend_dt(KvLayout lay, int n_rep, const StepBuffers& sb,
   //      workgroups in range order and unit % 8 fastest -- the same XCD assignment, but a unit's workgroups stay
   //      together in time, which also keeps the wait for the unit's threshold short;
   //   0: ranges fastest, otherwise.
-  // Order 1 only while every workgroup is resident at once (the second launch bound of the kernel: 5 / 4 / 3 / 2
-  // workgroups per CU, 256 CUs): its workgroups poll for their unit's threshold, and a unit spread over two rounds
+  // Order 1 only while every workgroup is resident at once (the second launch bound of the kernel: 5 or 4 workgroups
+  // per CU, 256 CUs): its workgroups poll for their unit's threshold, and a unit spread over two rounds
   // of workgroups would have the first round waiting for the second.
   const long resident = step_resident_wgs(n_rep);
   const int order = (long)units * lb.n * n_wgs <= resident ? 1 : (units % 8 == 0 ? 2 : 0);
