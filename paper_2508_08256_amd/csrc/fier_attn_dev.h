@@ -11,7 +11,6 @@
 namespace fier {
 
 constexpr int kAttnUnroll = 2;                  // rows per 16-lane row per iteration
-constexpr int kRowsPerIter = 4 * 4 * kAttnUnroll;  // 4 waves x 4 lane rows x unroll
 
 // Running softmax state of one 16-lane row of a wavefront, per query head: lane cn holds channels 8cn..8cn+7.
 template <int NREP>
@@ -36,16 +35,15 @@ constexpr size_t kNoRow = ~(size_t)0;
 
 // Attend over entries [start, end) of a row list; row_of(j) gives the row of entry j in the K / V arrays (the
 // callers map a token to its row: contiguous, or through the block table), or kNoRow if CHECKED and the entry
-// is to be skipped (safe_row is then read in its place and masked).  The workgroup's
-// 16 lane rows (4 waves x 4) take entries round-robin in batches of kAttnUnroll.  Calls may follow each other
-// on the same state: the running softmax simply continues.
-template <int DT, int NREP, bool CHECKED = false, bool STREAM = false, class RowOf>
+// is to be skipped (safe_row is then read in its place and masked).  The workgroup's lane rows (4 per wavefront) take entries round-robin in batches of kAttnUnroll.  Calls may follow each other
+// on the same state: the running softmax simply continues.  NW: wavefronts of the workgroup.
+template <int DT, int NREP, bool CHECKED = false, bool STREAM = false, int NW = 4, class RowOf>
 __device__ __forceinline__ void attend_rows(const uint4* __restrict__ K, const uint4* __restrict__ V,
                                             const uint4 (&qr)[NREP], RowOf row_of, int start, int end,
                                             float scale_log2e, AttnState<NREP>& st, size_t safe_row = 0) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rs = lane >> 4, cn = lane & 15;
-  for (int i0 = start + wave * (4 * kAttnUnroll); i0 < end; i0 += kRowsPerIter) {
+  for (int i0 = start + wave * (4 * kAttnUnroll); i0 < end; i0 += NW * 4 * kAttnUnroll) {
     uint4 kk[kAttnUnroll], vv[kAttnUnroll];
     bool valid[kAttnUnroll];
 #pragma unroll
@@ -199,7 +197,7 @@ __device__ __forceinline__ uint2 pack_part(const float (&x)[4]) {
 
 // As attend_rows, for three to eight query heads per kv head.  STREAM_V: the V rows with the streaming hint (the K rows, which
 // are loaded in four pieces per row, keep plain loads in gathers).
-template <int DT, int NREP, bool CHECKED = false, bool STREAM = false, bool STREAM_V = STREAM, class RowOf>
+template <int DT, int NREP, bool CHECKED = false, bool STREAM = false, bool STREAM_V = STREAM, int NW = 4, class RowOf>
 __device__ __forceinline__ void attend_rows_mfma(const uint4* __restrict__ K, const uint4* __restrict__ V,
                                                  const GatherQuery<NREP>& q, RowOf row_of, int start, int end,
                                                  float scale_log2e, MfmaState<NREP>& st, size_t safe_row = 0) {
@@ -210,7 +208,7 @@ __device__ __forceinline__ void attend_rows_mfma(const uint4* __restrict__ K, co
   const int n = lane & 15, kq = lane >> 4;
   const int part = n / kCols;
   const uint32_t cut1 = part >= 1 ? kLead : 0u, cut2 = part >= 2 ? kLead : 0u;
-  for (int j0 = start + wave * 16; j0 < end; j0 += 64) {
+  for (int j0 = start + wave * 16; j0 < end; j0 += NW * 16) {
     uint4 kk[4], vv[4];
     size_t rk = row_of(j0 + n < end ? j0 + n : start);
     if (CHECKED) rk = rk == kNoRow ? safe_row : rk;
@@ -268,12 +266,14 @@ __device__ __forceinline__ void attend_rows_mfma(const uint4* __restrict__ K, co
   }
 }
 
-// value of the lane 16 / 32 lanes away
-__device__ __forceinline__ float xor16(float x) {
-  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401f));
+// The sum over the four lanes with the same lane % 16 (lanes 16 apart first), by exchanges between registers: no LDS crossbar.
+__device__ __forceinline__ float rows_allsum(float x) {
+  typedef unsigned int u2_t __attribute__((ext_vector_type(2)));
+  const u2_t a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const u2_t b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
-__device__ __forceinline__ float xor32(float x) { return __shfl_xor(x, 32, 64); }
-
 
 // value of lane i + N of the row of 16 lanes (0 past its end)
 template <int N>
@@ -281,28 +281,21 @@ __device__ __forceinline__ float row_from(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x100 + N, 0xf, 0xf, true));
 }
 
-// The wavefront's state into LDS, sh + head * kPartialFloats: [wave][channel chunk of 8][o[8], m, l].
-template <int DT, int NREP>
+// The wavefront's state into LDS, sh + head * PITCH: [wave][channel chunk of 8][o[8], m, l].
+template <int DT, int NREP, int PITCH = kPartialFloats>
 __device__ __forceinline__ void wave_partials(const AttnState<NREP>& st, float* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rs = lane >> 4, cn = lane & 15;
 #pragma unroll
   for (int r = 0; r < NREP; ++r) {
-    float M = fmaxf(st.m[r], xor16(st.m[r]));
-    M = fmaxf(M, xor32(M));
+    const float M = rows_allmax(st.m[r]);
     const float w = st.m[r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st.m[r] - M);
-    float l = st.l[r] * w;
-    l += xor16(l);
-    l += xor32(l);
+    const float l = rows_allsum(st.l[r] * w);
     float o[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      o[c] = st.o[r][c] * w;
-      o[c] += xor16(o[c]);
-      o[c] += xor32(o[c]);
-    }
+    for (int c = 0; c < 8; ++c) o[c] = rows_allsum(st.o[r][c] * w);
     if (rs == 0) {
-      float* dst = sh + r * kPartialFloats + (wave * 16 + cn) * 10;
+      float* dst = sh + r * PITCH + (wave * 16 + cn) * 10;
 #pragma unroll
       for (int c = 0; c < 8; ++c) dst[c] = o[c];
       dst[8] = M;
@@ -310,15 +303,13 @@ __device__ __forceinline__ void wave_partials(const AttnState<NREP>& st, float* 
     }
   }
 }
-template <int DT, int NREP>
+template <int DT, int NREP, int PITCH = kPartialFloats>
 __device__ __forceinline__ void wave_partials(const MfmaState<NREP>& st, float* sh) {
   constexpr int kCols = MfmaState<NREP>::kCols;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = lane & 15, kq = lane >> 4;
-  float l = st.l;
-  l += xor16(l);
-  l += xor32(l);
-  float* dst = sh + n * kPartialFloats + (wave * 16 + 4 * kq) * 10;
+  const float l = rows_allsum(st.l);
+  float* dst = sh + n * PITCH + (wave * 16 + 4 * kq) * 10;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     float o[8];
@@ -383,19 +374,14 @@ __device__ __forceinline__ void store_partials(const GatherState<NREP>& st, floa
 }
 
 __device__ __forceinline__ float wave_allsum_f(float x) {
-  x = row_allsum(x);
-  x += xor16(x);
-  x += xor32(x);
-  return x;
+  return rows_allsum(row_allsum(x));
 }
 __device__ __forceinline__ float wave_allmax_f(float x) {
   x = fmaxf(x, row_ror<8>(x));
   x = fmaxf(x, row_ror<4>(x));
   x = fmaxf(x, row_ror<2>(x));
   x = fmaxf(x, row_ror<1>(x));
-  x = fmaxf(x, xor16(x));
-  x = fmaxf(x, xor32(x));
-  return x;
+  return rows_allmax(x);
 }
 
 // Merge the partial slots [0, n_used) of all NREP query heads of a unit into out[NREP][128].  256 threads form

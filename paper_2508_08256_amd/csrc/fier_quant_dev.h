@@ -2,17 +2,12 @@
 // fused decode step (Alg. 1 step 1; Eq. 5 read as round-to-nearest, Sec. 3.3).
 #pragma once
 
+#include <type_traits>
+
 #include "fier_dev.h"
 #include "fier_kernels.h"
 
 namespace fier {
-
-struct GroupCode {          // what one lane (channels 2l, 2l+1) learns about a group
-  uint32_t meta_lo, meta_hi;  // s | z << 16 in the K dtype
-  float s_lo, z_lo, s_hi, z_hi;  // the same as binary32
-  float amax_lo, amax_hi;     // max(|z|, |z + s|): the larger reconstruction level in magnitude
-  uint32_t bits_lo, bits_hi;  // bit t = code of token t (channel-major view of the group)
-};
 
 // ---- the decision arithmetic, in one place (binary32, no contraction) --------------------------------------------
 // z = min (-0 -> +0);  s = RN_dtype(max - z), held at the largest finite value;  bit = 2 * (k - z) >= s.
@@ -35,6 +30,9 @@ __device__ __forceinline__ void minmax_update(MinMax& m, uint32_t row, bool pres
 struct GroupScale {  // (s, z) of the lane's two channels: stored words and the same as binary32
   uint32_t s0, z0, s1, z1;
   float sf0, zf0, sf1, zf1;
+  // max(|z|, |z + s|): the larger reconstruction level in magnitude
+  __device__ __forceinline__ float amax0() const { return fmaxf(fabsf(zf0), fabsf(zf0 + sf0)); }
+  __device__ __forceinline__ float amax1() const { return fmaxf(fabsf(zf1), fabsf(zf1 + sf1)); }
 };
 template <int DT>
 __device__ __forceinline__ GroupScale group_scale(MinMax m) {
@@ -55,52 +53,47 @@ __device__ __forceinline__ GroupScale group_scale(MinMax m) {
   g.zf0 = w2f<DT>(g.z0), g.zf1 = w2f<DT>(g.z1);
   return g;
 }
-// Codes of up to 32 rows (tokens 0..ntok-1 present; FULL: all 32, ntok is not looked at) under scale g.  Lane
-// lane_base + t receives the 128-bit code word of token t in `mine`; b0 / b1 collect the lane's own two channels
-// (bit t = token t).
-template <int DT, bool FULL = false>
-__device__ __forceinline__ void code_rows(const uint32_t (&rows)[kG], int ntok, const GroupScale& g, int lane,
-                                          int lane_base, uint4& mine, uint32_t& b0, uint32_t& b1) {
+// f(T), f(T + 1), ... below n, at most kG, n the same in every lane: one scalar branch for all that are not there.  (Nested
+// and not a loop with an early exit, which the compiler does not always unroll.)
+template <int T, class F>
+__device__ __forceinline__ void first_rows(int n, F&& f) {
+  if constexpr (T < kG) {
+    if (T < n) {
+      f(std::integral_constant<int, T>());
+      first_rows<T + 1>(n, f);
+    }
+  }
+}
+
+// Code of row t of a group, into lane lane_base + t.
+template <int DT>
+__device__ __forceinline__ void code_row(uint32_t r, int t, const GroupScale& g, int lane, int lane_base, uint4& mine) {
 #pragma clang fp contract(off)
-  b0 = 0, b1 = 0;
+  const float a = lo16f<DT>(r) - g.zf0;
+  const float b = hi16f<DT>(r) - g.zf1;
+  const bool c0 = a + a >= g.sf0, c1 = b + b >= g.sf1;
+  const uint64_t even = __ballot(c0);
+  const uint64_t odd = __ballot(c1);
+  if (lane == lane_base + t)
+    mine = make_uint4((uint32_t)even, (uint32_t)(even >> 32), (uint32_t)odd, (uint32_t)(odd >> 32));
+}
+// Codes of up to 32 rows (tokens 0..ntok-1 present) under scale g.  Lane lane_base + t receives the 128-bit code word of
+// token t in `mine`.  An empty statement that "produces" the next row and `mine`: the next row's compares cannot start before
+// this row's ballots have been used up.  Left to itself the compiler makes the ballots of all 32 rows first, and 64 of them
+// do not fit the scalar registers (they were spilled to vector lanes and read back).
+template <int DT>
+__device__ __forceinline__ void code_rows(const uint32_t (&rows)[kG], int ntok, const GroupScale& g, int lane,
+                                          int lane_base, uint4& mine) {
   uint32_t r = rows[0];
 #pragma unroll
   for (int t = 0; t < kG; ++t) {
-    // ntok is the same in every lane: a row that is not there costs one scalar branch, not a row's worth of work
-    // (the appending wavefront of a decode step is a single wavefront on the step's critical path, and a group that
-    // has just been opened holds one token)
-    if (FULL || t < ntok) {
-      const float a = lo16f<DT>(r) - g.zf0;
-      const float b = hi16f<DT>(r) - g.zf1;
-      const bool c0 = a + a >= g.sf0, c1 = b + b >= g.sf1;
-      const uint64_t even = __ballot(c0);
-      const uint64_t odd = __ballot(c1);
-      b0 |= c0 ? (1u << t) : 0u;
-      b1 |= c1 ? (1u << t) : 0u;
-      if (lane == lane_base + t)
-        mine = make_uint4((uint32_t)even, (uint32_t)(even >> 32), (uint32_t)odd, (uint32_t)(odd >> 32));
-    }
+    // ntok is the same in every lane: a row that is not there costs one scalar branch
+    if (t < ntok) code_row<DT>(r, t, g, lane, lane_base, mine);
     if (t + 1 < kG) {
-      // An empty statement that "produces" the next row and `mine`: the next row's compares cannot start before
-      // this row's ballots have been used up.  Left to itself the compiler makes the ballots of all 32 rows first,
-      // and 64 of them do not fit the scalar registers (they were spilled to vector lanes and read back).
       r = rows[t + 1];
       asm volatile("" : "+v"(r), "+v"(mine.x), "+v"(mine.y), "+v"(mine.z), "+v"(mine.w));
     }
   }
-}
-template <int DT>
-__device__ __forceinline__ void fill_code(GroupCode& gc, const GroupScale& g, uint32_t b0, uint32_t b1) {
-  gc.meta_lo = g.s0 | (g.z0 << 16);
-  gc.meta_hi = g.s1 | (g.z1 << 16);
-  gc.s_lo = g.sf0;
-  gc.z_lo = g.zf0;
-  gc.s_hi = g.sf1;
-  gc.z_hi = g.zf1;
-  gc.amax_lo = fmaxf(fabsf(g.zf0), fabsf(g.zf0 + g.sf0));
-  gc.amax_hi = fmaxf(fabsf(g.zf1), fabsf(g.zf1 + g.sf1));
-  gc.bits_lo = b0;
-  gc.bits_hi = b1;
 }
 
 // Quantize one 32-token group (ntok in [1, 32] tokens present) for the lane's two channels.
@@ -108,17 +101,14 @@ __device__ __forceinline__ void fill_code(GroupCode& gc, const GroupScale& g, ui
 // Lane lane_base + t receives the 128-bit code word of token t in `mine` (zero for tokens not present):
 // x, y = even channels 0..62 / 64..126 (bit i = channel 2i, 64 + 2i), z, w = odd channels likewise.
 template <int DT>
-__device__ __forceinline__ void quantize_group(const uint32_t (&rows)[kG], int ntok, int lane, int lane_base,
-                                               uint4& mine, GroupCode& gc) {
+__device__ __forceinline__ GroupScale quantize_group(const uint32_t (&rows)[kG], int ntok, int lane, int lane_base,
+                                                     uint4& mine) {
   MinMax m;
   minmax_first<DT>(m, rows[0]);
-#pragma unroll
-  for (int t = 1; t < kG; ++t)
-    if (t < ntok) minmax_update<DT>(m, rows[t], true);  // the same in every lane: a scalar branch per absent row
+  first_rows<1>(ntok, [&](auto t) { minmax_update<DT>(m, rows[t], true); });
   const GroupScale g = group_scale<DT>(m);
-  uint32_t b0, b1;
-  code_rows<DT>(rows, ntok, g, lane, lane_base, mine, b0, b1);
-  fill_code<DT>(gc, g, b0, b1);
+  code_rows<DT>(rows, ntok, g, lane, lane_base, mine);
+  return g;
 }
 
 // Groups of g = 32 ns tokens, ns in {2, 4, 8}: the group's rows do not fit the registers, so they are read twice
@@ -144,40 +134,60 @@ __device__ __forceinline__ void raise_absmax(float* __restrict__ slot, float a) 
   if (a > *reinterpret_cast<volatile float*>(slot)) atomicMax(reinterpret_cast<unsigned int*>(slot), __float_as_uint(a));
 }
 
-// One wavefront appends row L of a unit (lane = channel pair): writes the K/V rows, re-derives the group the row
-// falls in from the rows present (the new row comes from registers) and stores its code words and (s, z).
-// Returns the group's code in gc; t0 = first token of the group, ntok = tokens now present in it.
-template <int DT>
-__device__ __forceinline__ void append_load_rows(const uint32_t* __restrict__ K, const KvRows kv, int L, uint32_t kn,
-                                                 int lane, uint32_t (&rows)[kG], int& t0, int& ntok) {
-  const int Gi = L / kG;
-  t0 = Gi * kG;
-  ntok = L - t0 + 1;
+// The rows of chunk c (32 tokens) of a tail group that the cache holds: t0 its first token, ntok tokens with the new one,
+// which comes from registers (token ntok - 1: never the row the append writes); zeros past them.
+__device__ __forceinline__ void append_load_rows(const uint32_t* __restrict__ K, const KvRows kv, int t0, int ntok, int c,
+                                                  int lane, uint32_t (&rows)[kG]) {
   const uint32_t* src = K + kv.row(t0) * (kD / 2) + lane;  // a group lies inside one block
+  const int first = c * kG, old = ntok - 1 - first;
 #pragma unroll
-  for (int t = 0; t < kG; ++t) {
-    // rows before the new one come from memory (t0 + t < L: never the row the append writes)
-    uint32_t r = t < ntok - 1 ? src[(size_t)t * (kD / 2)] : 0u;
-    rows[t] = (t == ntok - 1) ? kn : r;
-  }
+  for (int t = 0; t < kG; ++t) rows[t] = 0;
+  first_rows<0>(old, [&](auto t) { rows[t] = src[(size_t)(first + t) * (kD / 2)]; });
+}
+// Minima and maxima of such a chunk, the new row kn with it if it is its token: with 32-token groups they start from the
+// group's first row, else from infinities.
+template <int DT>
+__device__ __forceinline__ MinMax append_minmax(const uint32_t (&rows)[kG], int ntok, int c, uint32_t kn, bool long_group) {
+  const int old = ntok - 1 - c * kG;
+  MinMax m = {INFINITY, -INFINITY, INFINITY, -INFINITY};
+  if (!long_group) minmax_first<DT>(m, old > 0 ? rows[0] : kn);
+  first_rows<0>(old, [&](auto t) { minmax_update<DT>(m, rows[t], true); });
+  if (old >= 0 && old < kG) minmax_update<DT>(m, kn, true);
+  return m;
+}
+// Its codes: lane lane_base + t receives the code word of token t.
+template <int DT>
+__device__ __forceinline__ void append_codes(const uint32_t (&rows)[kG], int ntok, int c, uint32_t kn, const GroupScale& g,
+                                             int lane, int lane_base, uint4& mine) {
+  const int old = ntok - 1 - c * kG;
+  mine = make_uint4(0, 0, 0, 0);
+  first_rows<0>(old, [&](auto t) {
+    uint32_t r = rows[t];  // see code_rows
+    asm volatile("" : "+v"(r), "+v"(mine.x), "+v"(mine.y), "+v"(mine.z), "+v"(mine.w));
+    code_row<DT>(r, t, g, lane, lane_base, mine);
+  });
+  if (old >= 0 && old < kG) code_row<DT>(kn, old, g, lane, lane_base, mine);
 }
 
-// rows, t0, ntok: from append_load_rows (which may run well before: the loads are the long part of the chain)
+// One wavefront appends row L of a unit (lane = channel pair): writes the K/V rows, re-derives the group the row
+// falls in from the rows present (the new row comes from registers) and stores its code words and (s, z).
+// t0 = first token of the group, ntok = tokens now present in it; rows: from append_load_rows (which may run well before:
+// the loads are the long part of the chain).  Returns the group's scale in gs, the code word of token t0 + t in lane t.
 template <int DT>
 __device__ __forceinline__ void append_finish(uint32_t* __restrict__ K, uint32_t* __restrict__ V, const KvRows kv,
                                               uint32_t* __restrict__ kbits, uint32_t* __restrict__ kmeta, int unit,
                                               int L, int max_ctx, uint32_t kn, uint32_t vn, int lane,
-                                              const uint32_t (&rows)[kG], int t0, int ntok, GroupCode& gc,
+                                              const uint32_t (&rows)[kG], int t0, int ntok, GroupScale& gs,
                                               uint4& mine) {
   const int n_groups = max_ctx / kG;
   K[kv.row(L) * (kD / 2) + lane] = kn;
   V[kv.row(L) * (kD / 2) + lane] = vn;
   const int Gi = L / kG;
-  mine = make_uint4(0, 0, 0, 0);
-  quantize_group<DT>(rows, ntok, lane, 0, mine, gc);
+  gs = group_scale<DT>(append_minmax<DT>(rows, ntok, 0, kn, false));
+  append_codes<DT>(rows, ntok, 0, kn, gs, lane, 0, mine);
   uint4* bdst = reinterpret_cast<uint4*>(kbits) + (size_t)unit * max_ctx + t0;
   uint2* mdst = reinterpret_cast<uint2*>(kmeta + ((size_t)unit * n_groups + Gi) * kD) + lane;
-  *mdst = make_uint2(gc.meta_lo, gc.meta_hi);
+  *mdst = make_uint2(gs.s0 | (gs.z0 << 16), gs.s1 | (gs.z1 << 16));
   const bool opens_pair_block = (Gi & 1) == 0 && ntok == 1;  // its second group holds no token yet
   if (lane < kG || opens_pair_block) bdst[lane] = mine;
   if (opens_pair_block) {
@@ -190,7 +200,6 @@ __device__ __forceinline__ void append_finish(uint32_t* __restrict__ K, uint32_t
 // group's 32-token chunks w and w + 4 (the second one only at g = 256).  Latency bound, a chain of dependent steps at the
 // start of every decode step: one wavefront that read the group twice, 32 rows at a time, made the first kernel of the
 // step 15.8 us at 16 units x 20k tokens and g = 128, and two such layers per call 42.2 us; this way they take 37.5.
-//
 // The rows of chunk c of the tail group (t0 its first token, ntok tokens with the new one), zeros past the end.
 __device__ __forceinline__ void append_load_chunk(const uint32_t* __restrict__ K, const KvRows kv, int t0, int ntok, int c,
                                                   uint32_t kn, int lane, uint32_t (&rows)[kG]) {
@@ -257,8 +266,7 @@ __device__ __forceinline__ GroupScale append_row_long(uint32_t* __restrict__ K, 
     int nt = ntok - c * kG;
     nt = nt > kG ? kG : nt;
     uint4 mine = make_uint4(0, 0, 0, 0);
-    uint32_t b0, b1;
-    code_rows<DT>(rows, nt, gs, lane, (c & 1) * kG, mine, b0, b1);
+    code_rows<DT>(rows, nt, gs, lane, (c & 1) * kG, mine);
     if (c < ns && (c >> 1) * kPair < ntok && lane >> 5 == (c & 1)) bdst[(c >> 1) * kPair + lane] = mine;
     if (nt > 0) on_chunk(c, mine, gs);
     c += 4;

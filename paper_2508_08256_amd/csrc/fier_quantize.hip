@@ -51,12 +51,11 @@ __device__ __forceinline__ void quantize_tail_short(const uint32_t* __restrict__
       const uint32_t* src = K + lay.rows_of(unit).row(t0) * (kD / 2) + lane;
 #pragma unroll
       for (int t = 0; t < kG; ++t) rows[t] = src[(size_t)(t < ntok ? t : 0) * (kD / 2)];
-      GroupCode gc;
-      quantize_group<DT>(rows, ntok, lane, h * kG, mine, gc);
-      meta0 = gc.meta_lo;
-      meta1 = gc.meta_hi;
-      amax0 = fmaxf(amax0, gc.amax_lo);
-      amax1 = fmaxf(amax1, gc.amax_hi);
+      const GroupScale gs = quantize_group<DT>(rows, ntok, lane, h * kG, mine);
+      meta0 = gs.s0 | (gs.z0 << 16);
+      meta1 = gs.s1 | (gs.z1 << 16);
+      amax0 = fmaxf(amax0, gs.amax0());
+      amax1 = fmaxf(amax1, gs.amax1());
     }
     uint2* mdst = reinterpret_cast<uint2*>(kmeta + ((size_t)unit * n_groups + 2 * P + h) * kD) + lane;
     *mdst = make_uint2(meta0, meta1);
@@ -97,14 +96,13 @@ __device__ __forceinline__ void quantize_tail_long(const uint32_t* __restrict__ 
         uint32_t rows[kG];
 #pragma unroll
         for (int t = 0; t < kG; ++t) rows[t] = row_at(c0 + t < ntok ? c0 + t : 0);
-        uint32_t b0, b1;
-        code_rows<DT>(rows, nt, gs, lane, h * kG, mine, b0, b1);
+        code_rows<DT>(rows, nt, gs, lane, h * kG, mine);
       }
     }
     reinterpret_cast<uint4*>(kbits)[(size_t)unit * max_ctx + t0 + pb * kPair + lane] = mine;
   }
-  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane, fmaxf(fabsf(gs.zf0), fabsf(gs.zf0 + gs.sf0)));
-  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane + 1, fmaxf(fabsf(gs.zf1), fabsf(gs.zf1 + gs.sf1)));
+  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane, gs.amax0());
+  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane + 1, gs.amax1());
 }
 
 template <int DT, int NS>
@@ -467,12 +465,12 @@ __global__ __launch_bounds__(LONG ? 256 : 64) void append_kernel(uint32_t* __res
   float amax_lo, amax_hi;
   uint32_t rows[kG];
   if constexpr (!LONG) {
-    GroupCode gc;
+    GroupScale gs;
     uint4 mine;
-    int t0, ntok;
-    append_load_rows<DT>(K, lay.rows_of(unit), L, kn, lane, rows, t0, ntok);
-    append_finish<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, kn, vn, lane, rows, t0, ntok, gc, mine);
-    amax_lo = gc.amax_lo, amax_hi = gc.amax_hi;
+    const int t0 = L / kG * kG, ntok = L - t0 + 1;
+    append_load_rows(K, lay.rows_of(unit), t0, ntok, 0, lane, rows);
+    append_finish<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, kn, vn, lane, rows, t0, ntok, gs, mine);
+    amax_lo = gs.amax0(), amax_hi = gs.amax1();
   } else {
     __shared__ float4 xch[4 * 64];
     const int t0 = L / (kG * ns) * (kG * ns);
@@ -480,8 +478,7 @@ __global__ __launch_bounds__(LONG ? 256 : 64) void append_kernel(uint32_t* __res
     const GroupScale gs = append_row_long<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, ns, kn, vn, lane,
                                               wave, rows, xch, [](int, const uint4&, const GroupScale&) {});
     if (wave != 0) return;
-    amax_lo = fmaxf(fabsf(gs.zf0), fabsf(gs.zf0 + gs.sf0));
-    amax_hi = fmaxf(fabsf(gs.zf1), fabsf(gs.zf1 + gs.sf1));
+    amax_lo = gs.amax0(), amax_hi = gs.amax1();
   }
   raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane, amax_lo);
   raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane + 1, amax_hi);

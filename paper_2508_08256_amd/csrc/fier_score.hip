@@ -1,73 +1,15 @@
-// Approximate scores from the 1-bit key cache (Alg. 1 step 2):
-//   score[j] = sum_c q_c * (z[G(j)][c] + bit[j][c] * s[G(j)][c]),  q = sum of the unit's query heads.
-//
-// The contraction over the 128 channels runs on the matrix cores as an int8 product
-// (v_mfma_i32_16x16x64_i8), one wavefront per pair block (64 tokens = groups 2P and 2P+1) at a time:
-//   * B operand = the codes.  A byte with a single bit k set IS the integer 2^k (bit 7: -128), so one v_and of a
-//     code word with 0x01010101 << k yields four B elements: 8 vector ops expand 32 codes.  Lane (n, kq) of the
-//     wavefront owns word kq of token n of a 16-token tile, which is exactly the B layout (k = 16 kq + 0..15);
-//     the words arrive as one 16-byte load per token and are put into that order by four lane-row swaps;
-//   * A operand = the weights.  w = q_c s_c (binary32 product), divided by its bit's power of two and turned
-//     into a 31-bit fixed-point number relative to the largest |w| of its own group (the scale is a power of
-//     two, found per group with a DPP max), then cut into four signed bytes: F = d0 + 2^8 d1 + 2^16 d2 + 2^24 d3.
-//     The four digits are four rows of A.  The rows are built once per pair block by the lanes that hold the
-//     group's (s, z) and reach the A layout through 1.3 KiB of LDS per wavefront;
-//   * the digit rows are read back as two A operands, one with the digits in rows 0-3 / 8-11 and zeros elsewhere
-//     for the first tile of each group, one with them in rows 4-7 / 12-15 for the second tile: both tiles of a
-//     group accumulate into one 16x16 result that holds tile t in rows 4t..4t+3, the rows lane row t receives.
-//     Lane l ends up with the four digit sums of token l of the block, recombines them in binary32 and adds
-//     base[G] = sum_c q_c z[G][c];
-//   * the integer accumulation is exact; the only rounding is the fixed-point step of the weights,
-//     <= 2^(k-1) * 2^-30 * 2 max_c|w_c| per channel, about 4e-6 max|w| in the worst case over 128 channels.
-//
-// Channel bookkeeping.  Row r = lane / 16 works for group g = r / 2 and channel half h = r % 2; lane n of the row
-// loads (s, z) of channels c = 64h + 4n + e, e = 0..3, as one 16-byte request.  Channel c sits in code word
-// kq = h + 2(e & 1) at bit i = 2n + (e >> 1), i.e. byte y = i / 8, bit k = i % 8: MFMA j = k / 4, B register
-// r = k % 4, contraction index K = 16 kq + 4r + y.
+// Approximate scores from the 1-bit key cache (Alg. 1 step 2) over many workgroups per unit; first kernel of the fused step.
+// How a wavefront scores a pair block: fier_score_dev.h.
 #include <type_traits>
 
 #include "fier_dev.h"
 #include "fier_kernels.h"
 #include "fier_quant_dev.h"
+#include "fier_score_dev.h"
 
 namespace fier {
 
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-
-
-// LDS image of one wavefront's A operand: [j (K half)][group][digit][64 bytes], a zero row per j, padded so that
-// the (group, j) sub-blocks start in different banks.
-constexpr int kADigit = 64;
-constexpr int kAGroup = 320;
-constexpr int kAZeroRow = 576;
-constexpr int kAPlane = 672;
-constexpr int kAWave = 2 * kAPlane;
 constexpr int kScoreMaxBpw = 13;  // pair blocks per wavefront at most (the launcher keeps to it)
-
-__device__ __forceinline__ float wave_allsum(float x) {
-  x = row_allsum(x);
-  x += __shfl_xor(x, 16, 64);
-  x += __shfl_xor(x, 32, 64);
-  return x;
-}
-
-// value of the lane 16 away (rows 0 <-> 1, 2 <-> 3)
-__device__ __forceinline__ float swap_rows(float x) {
-  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401f));  // bit mode: xor 16
-}
-// max over the 16 lanes of a row of non-negative floats, as unsigned integers (their bit patterns order alike)
-template <int N>
-__device__ __forceinline__ uint32_t row_ror_u32(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + N, 0xf, 0xf, true);
-}
-__device__ __forceinline__ uint32_t row_allmax_u32(uint32_t x) {
-  x = max(x, row_ror_u32<8>(x));
-  x = max(x, row_ror_u32<4>(x));
-  x = max(x, row_ror_u32<2>(x));
-  x = max(x, row_ror_u32<1>(x));
-  return x;
-}
 
 // grid (units * (n_x [+ 1 if HIST])), n_x = ceil(max_ctx / (256 bpw)), block 256: scoring workgroup x of a unit
 // owns 4 bpw consecutive pair blocks, wave w the blocks 4 bpw x + w, + 4, + 8, ...  The launcher picks bpw so that the whole grid is
@@ -85,12 +27,12 @@ __device__ __forceinline__ uint32_t row_allmax_u32(uint32_t x) {
 // of the step through `newmax`.  A score outside [-R, R] simply lands in the outermost bin.
 // LONG: quantization groups longer than 32 tokens.  (Separate variants: the long groups' append takes more registers, and
 // in one kernel with the other cost the 32-token groups their fifth workgroup per CU: 56 -> 60 us at 32 units x 128k.)
-//   The bound asks for four workgroups per CU from three query heads per kv head on: asked for five the compiler put 12 to
+//   The bound asks for four workgroups per CU from two query heads per kv head on: asked for five the compiler put 12 to
 // 36 bytes per lane into scratch, asked for four it needs at most 96 registers up to six heads (five workgroups fit all the
 // same) and 102 at eight.  us per step, with scratch / now, fp16, g = 128: 4 heads 30.7 / 30.4 at 8 units x 32k, 59.9 / 57.9
 // at 32 x 128k, 68.1 / 66.2 at 128 ragged units up to 30k; 6 heads 31.6 / 31.4 at 8 x 8k, 73.0 / 71.2 at the ragged ones.
 template <int DT, int NREP, bool HIST, bool STREAM, bool LONG, class LAYERS>
-__global__ __launch_bounds__(256, HIST && LONG ? (NREP <= 2 ? 5 : 4) : 1) void score_kernel(const uint4* kbits, const uint4* kmeta,
+__global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void score_kernel(const uint4* kbits, const uint4* kmeta,
                                                     const float* __restrict__ kabsmax, const uint16_t* __restrict__ q,
                                                     const int32_t* __restrict__ seq_lens, int extra,
                                                     float* __restrict__ scores, UnitCtl* __restrict__ ctl,
@@ -172,12 +114,11 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP <= 2 ? 5 : 4) : 1) void s
   // the four wavefronts its chunk)
   uint32_t tail_rows[kG];
   int tail_t0 = 0, tail_ntok = 0;
-  if (HIST && !LONG && append_wg && wave == 0)
-    append_load_rows<DT>(K, lay.rows_of(unit), Lold, kn, lane, tail_rows, tail_t0, tail_ntok);
-  if (HIST && LONG && append_wg) {
+  if (HIST && append_wg && (wave == 0 || LONG)) {
     tail_t0 = tail_start;
     tail_ntok = Lold - tail_start + 1;
-    append_load_chunk(K, lay.rows_of(unit), tail_t0, tail_ntok, wave, kn, lane, tail_rows);
+    if constexpr (LONG) append_load_chunk(K, lay.rows_of(unit), tail_t0, tail_ntok, wave, kn, lane, tail_rows);
+    else append_load_rows(K, lay.rows_of(unit), tail_t0, tail_ntok, 0, lane, tail_rows);
   }
   const int n_groups = max_ctx / gsize;
   const int row = lane >> 4, n = lane & 15;
@@ -254,126 +195,61 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP <= 2 ? 5 : 4) : 1) void s
   FIER_PROF(1, HIST && unit == 0 && range == 3)
   if (append_wg) {
     if constexpr (HIST) {
-      if (!LONG && wave == 0) {  // lane = channel pair (2 lane, 2 lane + 1)
-        GroupCode gc;
+      if constexpr (!LONG) if (wave == 0) {  // lane = channel pair (2 lane, 2 lane + 1)
+        GroupScale gs;
         const int t0 = tail_t0, ntok = tail_ntok;
         uint4 mine;  // lane t < 32: the code word of token t0 + t
         append_finish<DT>(K, V, lay.rows_of(unit), const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kbits)),
                           const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kmeta)), unit, Lold, max_ctx, kn, vn,
-                          lane, tail_rows, t0, ntok, gc, mine);
-        newmax[(size_t)unit * kD + 2 * lane] = gc.amax_lo;
-        newmax[(size_t)unit * kD + 2 * lane + 1] = gc.amax_hi;
+                          lane, tail_rows, t0, ntok, gs, mine);
+        newmax[(size_t)unit * kD + 2 * lane] = gs.amax0();
+        newmax[(size_t)unit * kD + 2 * lane + 1] = gs.amax1();
         float q0 = 0.f, q1 = 0.f;
 #pragma unroll
         for (int r = 0; r < NREP; ++r) {
           q0 += lo16f<DT>(qpair[r]);
           q1 += hi16f<DT>(qpair[r]);
         }
-        // lane = token: the 128 weights q_c s_c go through LDS in the order of the code word's bits (channel 2 lane
-        // is bit lane & 31 of word lane >> 5, channel 2 lane + 1 of word 2 + (lane >> 5)); every lane then adds up
-        // the weights of its own token's set bits -- one wavefront-wide sum (the base) instead of one per token
-        float* wl = reinterpret_cast<float*>(a_lds);  // 128 floats; this workgroup scores nothing else
-        wl[lane] = q0 * gc.s_lo;
-        wl[64 + lane] = q1 * gc.s_hi;
-        const float base = wave_allsum(q0 * gc.z_lo + q1 * gc.z_hi);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const uint32_t wd[4] = {mine.x, mine.y, mine.z, mine.w};
-        float acc = 0.f;
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-#pragma unroll
-          for (int i = 0; i < 32; i += 4) {
-            const float4 w4 = *reinterpret_cast<const float4*>(wl + 32 * d + i);
-            acc += (wd[d] >> i & 1u) ? w4.x : 0.f;
-            acc += (wd[d] >> (i + 1) & 1u) ? w4.y : 0.f;
-            acc += (wd[d] >> (i + 2) & 1u) ? w4.z : 0.f;
-            acc += (wd[d] >> (i + 3) & 1u) ? w4.w : 0.f;
-          }
+        // this workgroup scores nothing else: the weights take the operands' place
+        const float sc = tail_scores(mine, 0, q0, q1, gs, reinterpret_cast<float*>(a_lds));
         if (lane < ntok) {
-          const float sc = acc + base;
           scores[(size_t)unit * max_ctx + t0 + lane] = sc;
           atomicAdd(&lhist[sel_bin(sc, R, hscale, kSelBins)], 1u);
         }
-      } else if constexpr (LONG) {
+      }
+      if constexpr (LONG) {
         // Groups of 64, 128 or 256 tokens: all four wavefronts, 32 tokens at a time; a chunk is scored as soon as its
-        // code words exist, lane = token, the 128 weights q_c s_c read from LDS in the order of the code word's bits
-        // (bit i of word d is channel 64 (d & 1) + 2 i + (d >> 1)).
-        static_assert(kAWave >= 512 && sizeof(lscore) >= 4 * 64 * sizeof(float4), "scratch of the appending workgroup");
-        float* wl = reinterpret_cast<float*>(a_lds + wave * kAWave);  // 128 floats; this workgroup scores nothing else
+        // code words exist.
+        static_assert(kAWave >= 4 * kTailWeights && sizeof(lscore) >= 4 * 64 * sizeof(float4), "scratch of the appending workgroup");
         float q0 = 0.f, q1 = 0.f;
 #pragma unroll
         for (int r = 0; r < NREP; ++r) {
           q0 += lo16f<DT>(qpair[r]);
           q1 += hi16f<DT>(qpair[r]);
         }
-        float base = 0.f;
-        bool have_w = false;
         const int t0 = tail_t0, ntok = tail_ntok;
         const GroupScale gs = append_row_long<DT>(
             K, V, lay.rows_of(unit), const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kbits)),
             const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kmeta)), unit, Lold, max_ctx, 1 << gshift, kn, vn, lane,
             wave, tail_rows, reinterpret_cast<float4*>(lscore), [&](int c, const uint4& mine, const GroupScale& g) {
-              if (!have_w) {
-                have_w = true;
-                // channel 2 lane is bit (lane & 31) of word lane >> 5, channel 2 lane + 1 of word 2 + (lane >> 5)
-                wl[lane] = q0 * g.sf0;
-                wl[64 + lane] = q1 * g.sf1;
-                base = wave_allsum(q0 * g.zf0 + q1 * g.zf1);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-              }
-              const uint32_t wd[4] = {mine.x, mine.y, mine.z, mine.w};
-              float acc = 0.f;
-#pragma unroll
-              for (int d = 0; d < 4; ++d) {
-#pragma unroll
-                for (int i = 0; i < 32; i += 4) {
-                  const float4 w4 = *reinterpret_cast<const float4*>(wl + 32 * d + i);
-                  acc += (wd[d] >> i & 1u) ? w4.x : 0.f;
-                  acc += (wd[d] >> (i + 1) & 1u) ? w4.y : 0.f;
-                  acc += (wd[d] >> (i + 2) & 1u) ? w4.z : 0.f;
-                  acc += (wd[d] >> (i + 3) & 1u) ? w4.w : 0.f;
-                }
-                asm volatile("" : "+v"(acc));  // a word's weights at a time: all 128 at once would not fit the registers
-              }
+              const float sc = tail_scores(mine, c & 1, q0, q1, g, reinterpret_cast<float*>(a_lds + wave * kAWave));
               const int tok = (c >> 1) * kPair + lane;  // within the group
               if (tok < ntok && lane >> 5 == (c & 1)) {
-                const float sc = acc + base;
                 scores[(size_t)unit * max_ctx + t0 + tok] = sc;
                 atomicAdd(&lhist[sel_bin(sc, R, hscale, kSelBins)], 1u);
               }
             });
         if (wave == 0) {
-          newmax[(size_t)unit * kD + 2 * lane] = fmaxf(fabsf(gs.zf0), fabsf(gs.zf0 + gs.sf0));
-          newmax[(size_t)unit * kD + 2 * lane + 1] = fmaxf(fabsf(gs.zf1), fabsf(gs.zf1 + gs.sf1));
+          newmax[(size_t)unit * kD + 2 * lane] = gs.amax0();
+          newmax[(size_t)unit * kD + 2 * lane + 1] = gs.amax1();
         }
       }
     }
   }
 
   if (scoring) {
-    // per-lane constants of the weight rows
-    float qk[4];   // q_c divided by the integer its code bit stands for in B
-    int a_wr[4];   // LDS byte offset of digit 0 of channel e
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int kq_c = hsel + 2 * (e & 1);
-      const int i_c = 2 * n + (e >> 1);
-      const int y = i_c >> 3, k = i_c & 7;
-      // 2^-k, negative for k = 7 (a byte with only bit 7 set is -128)
-      const float inv_bit = __uint_as_float(((uint32_t)(127 - k) << 23) | (k == 7 ? 0x80000000u : 0u));
-      qk[e] = qs[e] * inv_bit;
-      a_wr[e] = wave * kAWave + (k >> 2) * kAPlane + gsel * kAGroup + 16 * kq_c + 4 * (k & 3) + y;
-    }
-    // Two A operands.  "Even" serves the first tile of each group and carries the digits of the first group in
-    // rows 0-3, of the second in rows 8-11; "odd" serves the second tiles with the same digits in rows 4-7 and
-    // 12-15; all other rows read the zero row.  The two tiles of a group then accumulate into one 16x16 result
-    // that holds tile t in rows 4t..4t+3, the rows lane row t receives.
-    if (lane < 32) *reinterpret_cast<uint32_t*>(a_lds + wave * kAWave + (lane >> 4) * kAPlane + kAZeroRow + 4 * n) = 0u;
-    const int a_real = (n >> 3) * kAGroup + (n & 3) * kADigit;
-    const int a_even = wave * kAWave + ((n & 4) ? kAZeroRow : a_real) + 16 * row;
-    const int a_odd = wave * kAWave + ((n & 4) ? a_real : kAZeroRow) + 16 * row;
+    BlockScorer<DT> scorer;
+    scorer.init(qs, a_lds + wave * kAWave);
 
     // full_tag: every token of the block is below `lim`.  The store and the count are then unmasked, so the number
     // of memory operations in flight is the same on every path and the wait for the next block's loads can leave
@@ -382,83 +258,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP <= 2 ? 5 : 4) : 1) void s
     auto score_block = [&](auto full_tag, int it) {
       constexpr bool FULL = decltype(full_tag)::value;
       const int P = P0 + 4 * it;
-      // The B layout wants, in lane (row r, n), word r of the tokens 16 t + n, t = 0..3; the load left word d of
-      // token 16 r + n in register d: a 4x4 transpose between register index and lane row, two swap stages.
-      {
-        const u32x2_t a = __builtin_amdgcn_permlane32_swap(w_cur[0], w_cur[2], false, false);
-        const u32x2_t b = __builtin_amdgcn_permlane32_swap(w_cur[1], w_cur[3], false, false);
-        const u32x2_t c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-        const u32x2_t d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-        w_cur[0] = c[0];
-        w_cur[1] = c[1];
-        w_cur[2] = d[0];
-        w_cur[3] = d[1];
-      }
-
-      // ---- this row's weights -> fixed point relative to the group's largest -> digit rows in LDS ----------
-      const uint32_t mw[4] = {m_cur.x, m_cur.y, m_cur.z, m_cur.w};
-      float wv[4];
-      float basep = 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        wv[e] = qk[e] * lo16f<DT>(mw[e]);
-        basep += qs[e] * hi16f<DT>(mw[e]);
-      }
-      uint32_t mx = __float_as_uint(fmaxf(fmaxf(fabsf(wv[0]), fabsf(wv[1])), fmaxf(fabsf(wv[2]), fabsf(wv[3]))));
-      mx = row_allmax_u32(mx);
-      mx = max(mx, (uint32_t)__builtin_amdgcn_ds_swizzle((int)mx, 0x401f));  // over all 128 channels of the group
-      // max|w| < 2^(ex - 126), ex its biased exponent: scale = 2^(156 - ex) keeps |w * scale| < 2^30
-      uint32_t exb = mx & 0x7f800000u;
-      exb = exb < (29u << 23) ? (29u << 23) : exb;
-      const float scale = __uint_as_float(0x8d800000u - exb);      // (283 - ex) << 23
-      const float inv_scale = __uint_as_float(exb - (29u << 23));  // 2^(ex - 156); 0 when the group carries nothing
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int F = (int)rintf(wv[e] * scale);
-        // signed digits: the bytes of (F + 0x808080) ^ 0x808080, the top one as it is
-        const uint32_t X = ((uint32_t)F + 0x00808080u) ^ 0x00808080u;
-        unsigned char* dst = a_lds + a_wr[e];
-        dst[0] = (unsigned char)X;
-        dst[kADigit] = (unsigned char)(X >> 8);
-        dst[2 * kADigit] = (unsigned char)(X >> 16);
-        dst[3 * kADigit] = (unsigned char)(X >> 24);
-      }
-      float base = row_allsum(basep);
-      base += swap_rows(base);  // every lane of rows 2g, 2g + 1: base of group g
-      // the writes above come from other lanes of this same wavefront: LDS operations of a wavefront complete
-      // in order, the fences keep the compiler from moving the reads above them
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-      // ---- 4 tiles x 2 K-halves ----------------------------------------------------------------------------
-      const i32x4_t ae0 = *reinterpret_cast<const i32x4_t*>(a_lds + a_even);
-      const i32x4_t ae1 = *reinterpret_cast<const i32x4_t*>(a_lds + a_even + kAPlane);
-      const i32x4_t ao0 = *reinterpret_cast<const i32x4_t*>(a_lds + a_odd);
-      const i32x4_t ao1 = *reinterpret_cast<const i32x4_t*>(a_lds + a_odd + kAPlane);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // reads done before the next block's writes
-      i32x4_t acc[2];
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        i32x4_t b[2][2];  // [tile of the group][K half]
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            b[u][0][r] = (int)(w_cur[2 * g + u] & (0x01010101u << r));
-            b[u][1][r] = (int)(w_cur[2 * g + u] & (0x01010101u << (4 + r)));
-          }
-        acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ae0, b[0][0], i32x4_t{0, 0, 0, 0}, 0, 0, 0);
-        acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ae1, b[0][1], acc[g], 0, 0, 0);
-        acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ao0, b[1][0], acc[g], 0, 0, 0);
-        acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ao1, b[1][1], acc[g], 0, 0, 0);
-      }
-      // lane l = 16 row + n is token l of the block: its digit sums are registers 0..3 of its group's result
-      const i32x4_t dg = gsel ? acc[1] : acc[0];
-      float f = (float)dg[0];
-      f = fmaf((float)dg[1], 256.0f, f);
-      f = fmaf((float)dg[2], 65536.0f, f);
-      f = fmaf((float)dg[3], 16777216.0f, f);
-      const float sc = fmaf(f, inv_scale, base);
+      const float sc = scorer.score(w_cur, m_cur);
       const int tok = P * kPair + lane;
       lscore[(wave + 4 * it) * kPair + lane] = sc;
       if (HIST && (FULL || tok < lim)) atomicAdd(&lhist[sel_bin(sc, R, hscale, kSelBins)], 1u);
