@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libfier.so")
 SOURCES = ["fier_api.hip", "fier_quantize.hip", "fier_score.hip", "fier_select.hip", "fier_topk.hip",
-           "fier_attn.hip", "fier_step.hip", "fier_page.hip"]
+           "fier_attn.hip", "fier_step.hip", "fier_unit.hip", "fier_page.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-mfma-vgpr-form=1",  # matrix-core results stay in ordinary vector registers
@@ -47,8 +47,8 @@ def build(verbose: bool = False, prof: bool = False) -> str:
     flags = FLAGS + (["-DFIER_PROF_ENABLE", "-fgpu-rdc"] if prof else [])
     lib = os.path.join(HERE, "libfier_prof.so") if prof else LIB
     jobs = []
-    # the variants of the step's two kernels, the longest compilations, in parts of their own and first
-    for name, parts in (("score", 2), ("step", 4)):
+    # the variants of the step's kernels, the longest compilations, in parts of their own and first
+    for name, parts in (("score", 2), ("step", 4), ("unit", 4)):
         for part in range(parts):
             obj = os.path.join(objdir, "fier_%s_%d.o" % (name, part))
             jobs.append(([hipcc] + flags + ["-DFIER_%s_PART=%d" % (name.upper(), part), "-c",

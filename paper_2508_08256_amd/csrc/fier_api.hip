@@ -263,6 +263,7 @@ size_t fier_workspace_scores_offset(const fier_config* cfg, int32_t max_budget) 
 int fier_decode_step_kernels(const fier_config* cfg, int32_t max_budget, int32_t with_index_list) {
   if (check_cfg(cfg) != FIER_OK || max_budget < 1) return 0;
   if (max_budget > cfg->max_ctx) max_budget = cfg->max_ctx;
+  if (fier::unit_form(units_of(cfg), 1, n_rep_of(cfg), max_budget, cfg->max_ctx, cfg->group_size)) return 1;
   return fier::step_two_kernel_form(units_of(cfg), n_rep_of(cfg), max_budget, cfg->max_ctx, with_index_list != 0) ? 2 : 3;
 }
 
@@ -435,8 +436,22 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
       clear_parts = 1;
       continue;
     }
-    const fier::LayerBatch lb =
-        batch_of(cfg, c, dense_layers ? dense_layers + l : nullptr, std::min(most, n_layers - l), w.bytes);
+    fier::LayerBatch lb = batch_of(cfg, c, dense_layers ? dense_layers + l : nullptr,
+                                   std::min(phase == 0 ? fier::kMaxLayersPerLaunch : most, n_layers - l), w.bytes);
+    // One workgroup per unit and one launch for short contexts: needs no part of the workspace per layer.  Its phase 2 is
+    // that kernel on the scores of phase 1.
+    const int unit_waves = phase > 3 ? 0 : fier::unit_form(units, lb.n, n_rep, max_budget, cfg->max_ctx, cfg->group_size);
+    if (unit_waves && (phase == 0 || phase == 2)) {
+      e = fier::launch_unit_step(unit_waves, cfg->kv_dtype, lay, n_rep, c->kbits, c->kmeta, c->kabsmax, ql, c->seq_lens, w.sb,
+                                 budgets, max_budget, cfg->sm_scale, c->k, c->v, kn, vn, outl, idxl, cntl, cfg->batch,
+                                 cfg->n_kv_heads, cfg->max_ctx, cfg->group_size,
+                                 fier::kRangeTokens * fier::step_ranges_per_wg_layers(units, lb.n, n_rep, max_budget, cfg->max_ctx),
+                                 phase == 2, lb, s);
+      if (e != hipSuccess) return FIER_EHIP;
+      n_done = lb.n;
+      continue;
+    }
+    lb.n = std::min(lb.n, most);
     n_done = lb.n;
     if (lb.n > clear_parts && phase < 2) {  // later phases work on what phase 1 left there
       e = zero_parts(static_cast<char*>(workspace) + clear_parts * w.bytes, w.zero_bytes / sizeof(uint32_t), w.bytes,
@@ -450,7 +465,7 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
                              cfg->max_ctx, cfg->group_size, lb, s);
       if (e != hipSuccess) return FIER_EHIP;
     }
-    // After scoring: one launch (exact threshold + attention + merge, then the index list if asked for) wherever that
+    // Longer contexts, after scoring: one launch (exact threshold + attention + merge, then the index list if asked for) wherever that
     // measured faster.  A layer with launches of its own takes the threshold kernel and the selection + attention kernel
     // instead, whose workgroups never wait for each other and which write the index list while they select, on
     // grouped-query grids far beyond the resident one and whenever such a shape is asked for the list.  Layers that share
@@ -461,7 +476,7 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
     // 405; without the list, 512 x 30k, 4 heads 624 / 567, 5 heads 668 / 590).
     const bool two_kernels =
         phase > 3 ? (phase >> 4) <= 3
-                  : lb.n > 1 || fier::step_two_kernel_form(units, n_rep, max_budget, cfg->max_ctx, idx_out != nullptr);
+                  : unit_waves != 0 || lb.n > 1 || fier::step_two_kernel_form(units, n_rep, max_budget, cfg->max_ctx, idx_out != nullptr);
     if (two_kernels) {
       if (phase == 0 || (phase & 15) == 2) {
         e = fier::launch_step_attend(cfg->kv_dtype, lay, n_rep, w.sb, c->k, c->v, ql, c->seq_lens, extra, budgets,

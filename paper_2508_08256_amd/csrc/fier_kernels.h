@@ -171,7 +171,19 @@ hipError_t launch_step_attend(int dtype, KvLayout lay, int n_rep, const StepBuff
 hipError_t launch_step_emit_idx(const StepBuffers& sb, const int32_t* seq_lens, int extra, int max_budget, int32_t* idx,
                                 int units, int n_rep, int n_kv_heads, int max_ctx, const LayerBatch& lb, hipStream_t st);
 int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx);
+int step_ranges_per_wg_layers(int units, int layers, int n_rep, int max_budget, int max_ctx);
 bool step_two_kernel_form(int units, int n_rep, int max_budget, int max_ctx, bool with_index_list);
+
+// The whole step of a unit by one workgroup of nw wavefronts, for short contexts (unit_form: nw, or 0 where the others are
+// faster).  scored: phase 2 of it, on the scores and histograms that launch_score has left.  range_tokens: of a workgroup of
+// launch_step_emit_idx.
+int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx, int group_size);
+hipError_t launch_unit_step(int nw, int dtype, KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta,
+                            float* kabsmax, const void* q, const int32_t* seq_lens, const StepBuffers& sb,
+                            const int32_t* budgets, int max_budget, float sm_scale, void* K, void* V, const void* k_new,
+                            const void* v_new, float* out, int32_t* idx_out, int32_t* count_out, int batch, int n_kv_heads,
+                            int max_ctx, int group_size, int range_tokens, bool scored, const LayerBatch& lb,
+                            hipStream_t st);
 
 hipError_t launch_topk(const float* scores, const int32_t* seq_lens, int extra, const int32_t* budgets,
                        int max_budget, int32_t* idx, int32_t* count, int units, int n_kv_heads, int max_ctx,

@@ -818,7 +818,7 @@ int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
 //     but lasts as long as a workgroup (200 units x 11.5k, 4 heads, B = 2969: 163 / 208 / 161).
 // Of 6218 measured pairs of a shape and a number of layers 151 had been slower by 2 to 27 % than layer by layer; with this and
 // turned_wg 23 of 5260 are, by 2 to 15 %, most of them two layers that fill the GPU one by one.
-static int step_ranges_per_wg_layers(int units, int layers, int n_rep, int max_budget, int max_ctx) {
+int step_ranges_per_wg_layers(int units, int layers, int n_rep, int max_budget, int max_ctx) {
   const int rpw = step_ranges_per_wg(units * layers, n_rep, max_budget, max_ctx);
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;
   if (layers == 1 || rpw < 4 || n_ranges <= rpw) return rpw;
