@@ -238,14 +238,13 @@ int fier_decode_step_mixed(const fier_config *cfg, const fier_cache *layers, int
 
 /*
  * One kernel of fier_decode_step alone, for measurement and tests.  After the first kernel (phase 1: append + score +
- * score histogram) the step takes one of three forms, chosen from cfg, max_budget, the number of layers that share the
- * launch and whether idx_out is given; fier_decode_step_kernels returns the number of kernels of the form a call gets (not
- * counting the optional index-list kernel; with_index_list != 0: a call with idx_out), 0 for an invalid configuration.
- * (That is for a layer with launches of its own: of layers that share theirs, some 300 units and more may take the 1-kernel
- * form at longer contexts than one of them, and if not they take 2 kernels.)
- *   1 kernel at short contexts (with few units to about 5000 tokens and rows, with more to at most 12000): one workgroup
- *     does a unit's whole step, the index list included.  As phases it is phase 1 as below, phase 2 the same kernel on the
- *     scores of phase 1, phase 3 = the ascending index list (may be repeated);
+ * score histogram) the step takes one of two forms, chosen from cfg, max_budget and whether idx_out is given;
+ * fier_decode_step_kernels returns the number of kernels of the form a call gets (not counting the optional
+ * index-list kernel; with_index_list != 0: a call with idx_out), 0 for an invalid configuration.  (That is for a layer
+ * with launches of its own: layers that share theirs always take the two-kernel form.)
+ * At short contexts (with few units to about 5000 tokens and rows, with more to at most 12000) fier_decode_step does the
+ * same in one launch, a workgroup per unit; phase 2 is then that kernel on the scores of phase 1, the other phases and the
+ * count of the kernels are those of the two-kernel form.
  *   2 kernels, with one or two query heads per kv head; with more of them if idx_out is null and the second kernel
  *     has at most twice the workgroups the GPU holds at once: phase 2 = exact threshold + attention over the selected
  *     rows + merge in one launch; phase 3 = the ascending index list (launched by the step only if idx_out is given;

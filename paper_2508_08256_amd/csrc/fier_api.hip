@@ -263,7 +263,6 @@ size_t fier_workspace_scores_offset(const fier_config* cfg, int32_t max_budget) 
 int fier_decode_step_kernels(const fier_config* cfg, int32_t max_budget, int32_t with_index_list) {
   if (check_cfg(cfg) != FIER_OK || max_budget < 1) return 0;
   if (max_budget > cfg->max_ctx) max_budget = cfg->max_ctx;
-  if (fier::unit_form(units_of(cfg), 1, n_rep_of(cfg), max_budget, cfg->max_ctx, cfg->group_size)) return 1;
   return fier::step_two_kernel_form(units_of(cfg), n_rep_of(cfg), max_budget, cfg->max_ctx, with_index_list != 0) ? 2 : 3;
 }
 
