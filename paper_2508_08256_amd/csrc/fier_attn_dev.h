@@ -418,7 +418,7 @@ __device__ __forceinline__ void merge_heads(const float* __restrict__ po, const 
         const int s = s0 + GPH * k;
         os[k] = load_coherent(reinterpret_cast<const unsigned long long*>(&po[(base + (s < n_used ? s : s0)) * kD + k2]));
       }
-      __builtin_amdgcn_sched_barrier(0);  // without it 14 registers spill at two heads
+      if (NREP == 2) __builtin_amdgcn_sched_barrier(0);  // without it 14 registers spill
       lj = lj < 0.f ? -lj - 1.f : lj;
       const float mx = fmaxf(M, wave_allmax_f(mj));
       const float mref = mx == -INFINITY ? 0.f : mx;

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   // ones (their single wavefront has the longest chain of dependent loads: started last, it would end the kernel
   // late), then n_x scoring workgroups per unit, a unit's ranges next to each other.
   const int n_units = (int)gridDim.x / (n_x + (HIST ? 1 : 0));
-  const bool append_wg = HIST && (int)blockIdx.x < n_units;
+  const bool append_wg = HIST && __builtin_expect((int)blockIdx.x < n_units, 0);  // its code out of the others' way
   const int wid = (int)blockIdx.x - (HIST ? n_units : 0);
   const int unit = append_wg ? (int)blockIdx.x : wid / n_x;
   int range = append_wg ? -1 : wid - unit * n_x;
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   uint32_t kn = 0, vn = 0, qpair[NREP];
 #pragma unroll
   for (int r = 0; r < NREP; ++r) qpair[r] = 0;
-  if (append_wg && (wave == 0 || LONG) && k_new != nullptr) {
+  if (__builtin_expect(append_wg, 0) && (wave == 0 || LONG) && k_new != nullptr) {
     kn = k_new[(size_t)unit * (kD / 2) + lane];
     vn = v_new[(size_t)unit * (kD / 2) + lane];
 #pragma unroll
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   const int gshift = LONG ? group_shift : 0;
   const int gsize = kG << gshift;  // tokens per quantization group: 32, 64, 128 or 256
   const int tail_start = app ? (Lold / gsize) * gsize : L;  // tokens from here on are scored by the appending wave
-  if (append_wg) {
+  if (__builtin_expect(append_wg, 0)) {
     if (!app) return;
   } else {
     // range 0 of a unit always runs so that an empty unit still gets its control block written
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   // the four wavefronts its chunk)
   uint32_t tail_rows[kG];
   int tail_t0 = 0, tail_ntok = 0;
-  if (HIST && append_wg && (wave == 0 || LONG)) {
+  if (HIST && __builtin_expect(append_wg, 0) && (wave == 0 || LONG)) {
     tail_t0 = tail_start;
     tail_ntok = Lold - tail_start + 1;
     if constexpr (LONG) append_load_chunk(K, lay.rows_of(unit), tail_t0, tail_ntok, wave, kn, lane, tail_rows);
@@ -137,8 +137,11 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   // lane l loads the whole 16-byte code word of token l of the block (one contiguous 1 KiB request per wavefront);
   // the lane's (s, z) quad of block P is at meta_u[((2 P + gsel) >> gshift) * 32 + 16 hsel + n]: half-block
   // 2 P + gsel (32 tokens) lies in group (2 P + gsel) >> gshift
-  const uint4* const pb = reinterpret_cast<const uint4*>(bits_u) + ((size_t)P0 * kPair + lane);
-  const uint4* const pm = meta_u + ((size_t)((2 * P0 + gsel) >> gshift) * 32 + 16 * hsel + n);
+  // (wavefronts that score nothing load the unit's first block: with the first loads under a branch the compiler moved their
+  // results to other registers behind it, and so waited for them before it issued the query's loads)
+  const int Pl = scoring ? P0 : 0;
+  const uint4* const pb = reinterpret_cast<const uint4*>(bits_u) + ((size_t)Pl * kPair + lane);
+  const uint4* const pm = meta_u + ((size_t)((2 * Pl + gsel) >> gshift) * 32 + 16 * hsel + n);
   const int pm_step = 256 >> gshift;  // uint4 per block step: a wave's next block is 4 blocks = 8 half-blocks on
   // blocks of this wave that hold tokens to score: P0, P0 + 4, ... below ceil(lim / 64), at most bpw; only the
   // last of them can be a partial one
@@ -148,6 +151,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   // keep the count of outstanding requests the same on every path)
   auto fetch = [&](uint32_t (&w)[4], uint4& m, int i) {
     i = i < nb ? i : nb - 1;
+    i = i < 0 ? 0 : i;
     // STREAM: the codes and metadata are read once per step and, from a size on, are better kept out of the caches
     // (see the launcher)
     const uint4 v = STREAM ? load_stream(pb + (size_t)i * (4 * kPair)) : pb[(size_t)i * (4 * kPair)];
@@ -157,9 +161,10 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
     w[3] = v.w;
     m = STREAM ? load_stream(pm + (size_t)i * pm_step) : pm[(size_t)i * pm_step];
   };
-  uint32_t w_cur[4] = {0, 0, 0, 0};
-  uint4 m_cur = make_uint4(0, 0, 0, 0);
-  if (scoring) fetch(w_cur, m_cur, 0);
+  uint32_t w_cur[4];
+  uint4 m_cur;
+  fetch(w_cur, m_cur, 0);
+  __builtin_amdgcn_sched_barrier(0);
 
   // ---- the lane's 4 query channels c = 64 hsel + 4 n + e, summed over the query heads of this kv head ------
   float qs[4];
@@ -193,7 +198,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   }
 
   FIER_PROF(1, HIST && unit == 0 && range == 3)
-  if (append_wg) {
+  if (__builtin_expect(append_wg, 0)) {
     if constexpr (HIST) {
       if constexpr (!LONG) if (wave == 0) {  // lane = channel pair (2 lane, 2 lane + 1)
         GroupScale gs;
