@@ -53,14 +53,14 @@ __device__ __forceinline__ GroupScale group_scale(MinMax m) {
   g.zf0 = w2f<DT>(g.z0), g.zf1 = w2f<DT>(g.z1);
   return g;
 }
-// f(T), f(T + 1), ... below n, at most kG, n the same in every lane: one scalar branch for all that are not there.  (Nested
+// f(T), f(T + 1), ... below n, at most N, n the same in every lane: one scalar branch for all that are not there.  (Nested
 // and not a loop with an early exit, which the compiler does not always unroll.)
-template <int T, class F>
+template <int T, int N, class F>
 __device__ __forceinline__ void first_rows(int n, F&& f) {
-  if constexpr (T < kG) {
+  if constexpr (T < N) {
     if (T < n) {
       f(std::integral_constant<int, T>());
-      first_rows<T + 1>(n, f);
+      first_rows<T + 1, N>(n, f);
     }
   }
 }
@@ -105,7 +105,7 @@ __device__ __forceinline__ GroupScale quantize_group(const uint32_t (&rows)[kG],
                                                      uint4& mine) {
   MinMax m;
   minmax_first<DT>(m, rows[0]);
-  first_rows<1>(ntok, [&](auto t) { minmax_update<DT>(m, rows[t], true); });
+  first_rows<1, kG>(ntok, [&](auto t) { minmax_update<DT>(m, rows[t], true); });
   const GroupScale g = group_scale<DT>(m);
   code_rows<DT>(rows, ntok, g, lane, lane_base, mine);
   return g;
@@ -134,72 +134,100 @@ __device__ __forceinline__ void raise_absmax(float* __restrict__ slot, float a) 
   if (a > *reinterpret_cast<volatile float*>(slot)) atomicMax(reinterpret_cast<unsigned int*>(slot), __float_as_uint(a));
 }
 
-// The rows of chunk c (32 tokens) of a tail group that the cache holds: t0 its first token, ntok tokens with the new one,
-// which comes from registers (token ntok - 1: never the row the append writes); zeros past them.
-__device__ __forceinline__ void append_load_rows(const uint32_t* __restrict__ K, const KvRows kv, int t0, int ntok, int c,
-                                                  int lane, uint32_t (&rows)[kG]) {
-  const uint32_t* src = K + kv.row(t0) * (kD / 2) + lane;  // a group lies inside one block
-  const int first = c * kG, old = ntok - 1 - first;
+// ---- the group an appended row falls in, eight tokens per wavefront ------------------------------------------------------------
+// The group's re-quantization is a chain of dependent steps at the start of every decode step, on its critical path (one
+// wavefront for the whole group of 32: steps of 8 units x 16k, 4 heads, took 23.7 us with 24 tokens in it and 24.8 with 32, now
+// 22.0, where one with a single token takes 21.2): a
+// wavefront to every kTailRows tokens (chunk c; N in the functions below), minima and maxima through LDS.  t0: the group's first token, ntok: its tokens
+// with the new one, which comes from registers (kn, token ntok - 1: never the row the append writes).
+constexpr int kTailRows = 8;
+// The rows of the chunk that the cache holds; zeros past them.
+template <int N>
+__device__ __forceinline__ void tail_load(const uint32_t* __restrict__ K, const KvRows kv, int t0, int ntok, int c, int lane,
+                                          uint32_t (&rows)[N]) {
+  const uint32_t* src = K + (kv.row(t0) + (size_t)(c * N)) * (kD / 2) + lane;  // a group lies inside one block
 #pragma unroll
-  for (int t = 0; t < kG; ++t) rows[t] = 0;
-  first_rows<0>(old, [&](auto t) { rows[t] = src[(size_t)(first + t) * (kD / 2)]; });
+  for (int t = 0; t < N; ++t) rows[t] = 0;
+  first_rows<0, N>(ntok - 1 - c * N, [&](auto t) { rows[t] = src[(size_t)t * (kD / 2)]; });
 }
-// Minima and maxima of such a chunk, the new row kn with it if it is its token: with 32-token groups they start from the
-// group's first row, else from infinities.
-template <int DT>
-__device__ __forceinline__ MinMax append_minmax(const uint32_t (&rows)[kG], int ntok, int c, uint32_t kn, bool long_group) {
-  const int old = ntok - 1 - c * kG;
+// Its minima and maxima joined to m, the new row with them if it is the chunk's.
+template <int DT, int N>
+__device__ __forceinline__ void tail_minmax(MinMax& m, const uint32_t (&rows)[N], int ntok, int c, uint32_t kn) {
+  const int old = ntok - 1 - c * N;
+  first_rows<0, N>(old, [&](auto t) { minmax_update<DT>(m, rows[t], true); });
+  if (old >= 0 && old < N) minmax_update<DT>(m, kn, true);
+}
+// What a wavefront starts from: with 32-token groups the first one from the group's first row, else infinities.
+template <int DT, int N>
+__device__ __forceinline__ MinMax tail_minmax_start(const uint32_t (&rows)[N], int ntok, int c, uint32_t kn, bool long_group) {
   MinMax m = {INFINITY, -INFINITY, INFINITY, -INFINITY};
-  if (!long_group) minmax_first<DT>(m, old > 0 ? rows[0] : kn);
-  first_rows<0>(old, [&](auto t) { minmax_update<DT>(m, rows[t], true); });
-  if (old >= 0 && old < kG) minmax_update<DT>(m, kn, true);
+  if (!long_group && c == 0) minmax_first<DT>(m, ntok > 1 ? rows[0] : kn);
   return m;
 }
-// Its codes: lane lane_base + t receives the code word of token t.
-template <int DT>
-__device__ __forceinline__ void append_codes(const uint32_t (&rows)[kG], int ntok, int c, uint32_t kn, const GroupScale& g,
-                                             int lane, int lane_base, uint4& mine) {
-  const int old = ntok - 1 - c * kG;
-  mine = make_uint4(0, 0, 0, 0);
-  first_rows<0>(old, [&](auto t) {
+// Of all wavefronts, in their order; n of them have stored theirs, 64 a wavefront.
+__device__ __forceinline__ MinMax tail_join(const float4* xch, int n, int lane) {
+  const float4 f = xch[lane];
+  MinMax m = {f.x, f.y, f.z, f.w};
+  for (int w = 1; w < n; ++w) {
+    const float4 o = xch[w * 64 + lane];
+    m.mn0 = o.x < m.mn0 ? o.x : m.mn0;
+    m.mx0 = o.y > m.mx0 ? o.y : m.mx0;
+    m.mn1 = o.z < m.mn1 ? o.z : m.mn1;
+    m.mx1 = o.w > m.mx1 ? o.w : m.mx1;
+  }
+  return m;
+}
+// Its codes: lane (N c + t) % 64 receives the code word of token N c + t of the group.
+template <int DT, int N>
+__device__ __forceinline__ uint4 tail_codes(const uint32_t (&rows)[N], int ntok, int c, uint32_t kn, const GroupScale& g,
+                                            int lane) {
+  const int old = ntok - 1 - c * N, base = c * N & (kPair - 1);
+  uint4 mine = make_uint4(0, 0, 0, 0);
+  first_rows<0, N>(old, [&](auto t) {
     uint32_t r = rows[t];  // see code_rows
     asm volatile("" : "+v"(r), "+v"(mine.x), "+v"(mine.y), "+v"(mine.z), "+v"(mine.w));
-    code_row<DT>(r, t, g, lane, lane_base, mine);
+    code_row<DT>(r, t, g, lane, base, mine);
   });
-  if (old >= 0 && old < kG) code_row<DT>(kn, old, g, lane, lane_base, mine);
+  if (old >= 0 && old < N) code_row<DT>(kn, old, g, lane, base, mine);
+  return mine;
 }
 
-// One wavefront appends row L of a unit (lane = channel pair): writes the K/V rows, re-derives the group the row
-// falls in from the rows present (the new row comes from registers) and stores its code words and (s, z).
-// t0 = first token of the group, ntok = tokens now present in it; rows: from append_load_rows (which may run well before:
-// the loads are the long part of the chain).  Returns the group's scale in gs, the code word of token t0 + t in lane t.
+// Row L of a unit appended by four wavefronts, 32-token groups (lane = channel pair): the K/V rows written, the group the row
+// falls in re-derived from the rows present, its code words and (s, z) stored.  rows: chunk `wave`, from tail_load (which may
+// run well before: the loads are the long part of the chain).  xch: 256 float4 in LDS.  Returns the group's scale; mine: the
+// code words of the wavefront's tokens in lanes 8 wave ...  Has a barrier.
 template <int DT>
-__device__ __forceinline__ void append_finish(uint32_t* __restrict__ K, uint32_t* __restrict__ V, const KvRows kv,
-                                              uint32_t* __restrict__ kbits, uint32_t* __restrict__ kmeta, int unit,
-                                              int L, int max_ctx, uint32_t kn, uint32_t vn, int lane,
-                                              const uint32_t (&rows)[kG], int t0, int ntok, GroupScale& gs,
-                                              uint4& mine) {
-  const int n_groups = max_ctx / kG;
-  K[kv.row(L) * (kD / 2) + lane] = kn;
-  V[kv.row(L) * (kD / 2) + lane] = vn;
-  const int Gi = L / kG;
-  gs = group_scale<DT>(append_minmax<DT>(rows, ntok, 0, kn, false));
-  append_codes<DT>(rows, ntok, 0, kn, gs, lane, 0, mine);
-  uint4* bdst = reinterpret_cast<uint4*>(kbits) + (size_t)unit * max_ctx + t0;
-  uint2* mdst = reinterpret_cast<uint2*>(kmeta + ((size_t)unit * n_groups + Gi) * kD) + lane;
-  *mdst = make_uint2(gs.s0 | (gs.z0 << 16), gs.s1 | (gs.z1 << 16));
-  const bool opens_pair_block = (Gi & 1) == 0 && ntok == 1;  // its second group holds no token yet
-  if (lane < kG || opens_pair_block) bdst[lane] = mine;
-  if (opens_pair_block) {
-    uint2* mdst1 = reinterpret_cast<uint2*>(kmeta + ((size_t)unit * n_groups + Gi + 1) * kD) + lane;
-    *mdst1 = make_uint2(0, 0);
+__device__ __forceinline__ GroupScale append_row_short(uint32_t* __restrict__ K, uint32_t* __restrict__ V, const KvRows kv,
+                                                       uint32_t* __restrict__ kbits, uint32_t* __restrict__ kmeta, int unit,
+                                                       int L, int max_ctx, uint32_t kn, uint32_t vn, int lane, int wave,
+                                                       const uint32_t (&rows)[kTailRows], float4* xch, uint4& mine) {
+  const int n_groups = max_ctx / kG, Gi = L / kG, t0 = Gi * kG, ntok = L - t0 + 1;
+  MinMax m = tail_minmax_start<DT>(rows, ntok, wave, kn, false);
+  tail_minmax<DT>(m, rows, ntok, wave, kn);
+  xch[wave * 64 + lane] = make_float4(m.mn0, m.mx0, m.mn1, m.mx1);
+  if (wave == 0) {
+    K[kv.row(L) * (kD / 2) + lane] = kn;
+    V[kv.row(L) * (kD / 2) + lane] = vn;
   }
+  __syncthreads();
+  const GroupScale gs = group_scale<DT>(tail_join(xch, 4, lane));
+  mine = tail_codes<DT>(rows, ntok, wave, kn, gs, lane);
+  const bool opens_pair_block = (Gi & 1) == 0 && ntok == 1;  // its second group holds no token yet
+  uint4* bdst = reinterpret_cast<uint4*>(kbits) + (size_t)unit * max_ctx + t0;
+  if (lane >> 3 == wave || (opens_pair_block && wave == 0 && lane >= kG)) bdst[lane] = mine;
+  if (wave == 0) {
+    uint2* mdst = reinterpret_cast<uint2*>(kmeta + ((size_t)unit * n_groups + Gi) * kD) + lane;
+    *mdst = make_uint2(gs.s0 | (gs.z0 << 16), gs.s1 | (gs.z1 << 16));
+    if (opens_pair_block) mdst[kD / 2] = make_uint2(0, 0);
+  }
+  return gs;
 }
 
 // The same for groups of g = 32 ns tokens (ns in {2, 4, 8}), by a workgroup of four wavefronts: wavefront w takes the
 // group's 32-token chunks w and w + 4 (the second one only at g = 256).  Latency bound, a chain of dependent steps at the
 // start of every decode step: one wavefront that read the group twice, 32 rows at a time, made the first kernel of the
 // step 15.8 us at 16 units x 20k tokens and g = 128, and two such layers per call 42.2 us; this way they take 37.5.
+//
 // The rows of chunk c of the tail group (t0 its first token, ntok tokens with the new one), zeros past the end.
 __device__ __forceinline__ void append_load_chunk(const uint32_t* __restrict__ K, const KvRows kv, int t0, int ntok, int c,
                                                   uint32_t kn, int lane, uint32_t (&rows)[kG]) {

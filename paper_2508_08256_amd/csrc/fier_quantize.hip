@@ -444,44 +444,37 @@ __global__ void zero_absmax_kernel(float* __restrict__ kabsmax, int n) {
   if (i < n) kabsmax[i] = 0.f;
 }
 
-// grid (units), block 64 (g = 32) or 256 (longer groups).  Writes the new K/V rows at position L = seq_len and
-// re-derives the group that row falls in from the rows present (the new row comes from registers).
+// grid (units), block 256.  Writes the new K/V rows at position L = seq_len and re-derives the group that row falls in from
+// the rows present (the new row comes from registers).
 template <int DT, bool LONG>
-__global__ __launch_bounds__(LONG ? 256 : 64) void append_kernel(uint32_t* __restrict__ K, uint32_t* __restrict__ V,
-                                                                 uint32_t* __restrict__ kbits,
-                                                                 uint32_t* __restrict__ kmeta,
-                                                                 float* __restrict__ kabsmax,
-                                                                 const int32_t* __restrict__ seq_lens,
-                                                                 const uint32_t* __restrict__ k_new,
-                                                                 const uint32_t* __restrict__ v_new, int n_kv_heads,
-                                                                 int max_ctx, int ns, KvLayout lay) {
+__global__ __launch_bounds__(256) void append_kernel(uint32_t* __restrict__ K, uint32_t* __restrict__ V,
+                                                     uint32_t* __restrict__ kbits, uint32_t* __restrict__ kmeta,
+                                                     float* __restrict__ kabsmax, const int32_t* __restrict__ seq_lens,
+                                                     const uint32_t* __restrict__ k_new, const uint32_t* __restrict__ v_new,
+                                                     int n_kv_heads, int max_ctx, int ns, KvLayout lay) {
+  __shared__ float4 xch[4 * 64];
   const int lane = threadIdx.x & 63;
-  const int wave = LONG ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int unit = blockIdx.x;
   const int L = seq_lens[unit / n_kv_heads];
   if (L < 0 || L >= max_ctx) return;
   const uint32_t kn = k_new[(size_t)unit * (kD / 2) + lane];
   const uint32_t vn = v_new[(size_t)unit * (kD / 2) + lane];
-  float amax_lo, amax_hi;
-  uint32_t rows[kG];
+  const int t0 = L / (kG * ns) * (kG * ns), ntok = L - t0 + 1;
+  uint32_t rows[LONG ? kG : kTailRows];
+  GroupScale gs;
   if constexpr (!LONG) {
-    GroupScale gs;
     uint4 mine;
-    const int t0 = L / kG * kG, ntok = L - t0 + 1;
-    append_load_rows(K, lay.rows_of(unit), t0, ntok, 0, lane, rows);
-    append_finish<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, kn, vn, lane, rows, t0, ntok, gs, mine);
-    amax_lo = gs.amax0(), amax_hi = gs.amax1();
+    tail_load(K, lay.rows_of(unit), t0, ntok, wave, lane, rows);
+    gs = append_row_short<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, kn, vn, lane, wave, rows, xch, mine);
   } else {
-    __shared__ float4 xch[4 * 64];
-    const int t0 = L / (kG * ns) * (kG * ns);
-    append_load_chunk(K, lay.rows_of(unit), t0, L - t0 + 1, wave, kn, lane, rows);
-    const GroupScale gs = append_row_long<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, ns, kn, vn, lane,
-                                              wave, rows, xch, [](int, const uint4&, const GroupScale&) {});
-    if (wave != 0) return;
-    amax_lo = gs.amax0(), amax_hi = gs.amax1();
+    append_load_chunk(K, lay.rows_of(unit), t0, ntok, wave, kn, lane, rows);
+    gs = append_row_long<DT>(K, V, lay.rows_of(unit), kbits, kmeta, unit, L, max_ctx, ns, kn, vn, lane, wave, rows, xch,
+                             [](int, const uint4&, const GroupScale&) {});
   }
-  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane, amax_lo);
-  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane + 1, amax_hi);
+  if (wave != 0) return;
+  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane, gs.amax0());
+  raise_absmax(kabsmax + (size_t)unit * kD + 2 * lane + 1, gs.amax1());
 }
 
 template <int DT>
@@ -532,7 +525,7 @@ hipError_t launch_append(int dtype, KvLayout lay, void* K, void* V, uint32_t* kb
                          int max_ctx, int group_size, hipStream_t st) {
   const int ns = group_size / kG;
 #define FIER_APPEND(DT, LONG)                                                                                       \
-  append_kernel<DT, LONG><<<units, LONG ? 256 : 64, 0, st>>>((uint32_t*)K, (uint32_t*)V, kbits, kmeta, kabsmax,     \
+  append_kernel<DT, LONG><<<units, 256, 0, st>>>((uint32_t*)K, (uint32_t*)V, kbits, kmeta, kabsmax,                  \
                                                              seq_lens, (const uint32_t*)k_new,                      \
                                                              (const uint32_t*)v_new, n_kv_heads, max_ctx, ns, lay)
   if (dtype == DT_F16) {

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   uint32_t kn = 0, vn = 0, qpair[NREP];
 #pragma unroll
   for (int r = 0; r < NREP; ++r) qpair[r] = 0;
-  if (__builtin_expect(append_wg, 0) && (wave == 0 || LONG) && k_new != nullptr) {
+  if (__builtin_expect(append_wg, 0) && k_new != nullptr) {
     kn = k_new[(size_t)unit * (kD / 2) + lane];
     vn = v_new[(size_t)unit * (kD / 2) + lane];
 #pragma unroll
@@ -112,13 +112,13 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   }
   // ... and the rows of the group the new token falls in as soon as the length is known (longer groups than 32: each of
   // the four wavefronts its chunk)
-  uint32_t tail_rows[kG];
+  uint32_t tail_rows[LONG ? kG : kTailRows];
   int tail_t0 = 0, tail_ntok = 0;
-  if (HIST && __builtin_expect(append_wg, 0) && (wave == 0 || LONG)) {
+  if (HIST && __builtin_expect(append_wg, 0)) {
     tail_t0 = tail_start;
     tail_ntok = Lold - tail_start + 1;
     if constexpr (LONG) append_load_chunk(K, lay.rows_of(unit), tail_t0, tail_ntok, wave, kn, lane, tail_rows);
-    else append_load_rows(K, lay.rows_of(unit), tail_t0, tail_ntok, 0, lane, tail_rows);
+    else tail_load(K, lay.rows_of(unit), tail_t0, tail_ntok, wave, lane, tail_rows);
   }
   const int n_groups = max_ctx / gsize;
   const int row = lane >> 4, n = lane & 15;
@@ -200,32 +200,38 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
   FIER_PROF(1, HIST && unit == 0 && range == 3)
   if (__builtin_expect(append_wg, 0)) {
     if constexpr (HIST) {
-      if constexpr (!LONG) if (wave == 0) {  // lane = channel pair (2 lane, 2 lane + 1)
-        GroupScale gs;
+      if constexpr (!LONG) {
+        static_assert(kAWave >= kTailLds && sizeof(lscore) >= 4 * 64 * sizeof(float4), "scratch of the appending workgroup");
         const int t0 = tail_t0, ntok = tail_ntok;
-        uint4 mine;  // lane t < 32: the code word of token t0 + t
-        append_finish<DT>(K, V, lay.rows_of(unit), const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kbits)),
-                          const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kmeta)), unit, Lold, max_ctx, kn, vn,
-                          lane, tail_rows, t0, ntok, gs, mine);
-        newmax[(size_t)unit * kD + 2 * lane] = gs.amax0();
-        newmax[(size_t)unit * kD + 2 * lane + 1] = gs.amax1();
-        float q0 = 0.f, q1 = 0.f;
-#pragma unroll
-        for (int r = 0; r < NREP; ++r) {
-          q0 += lo16f<DT>(qpair[r]);
-          q1 += hi16f<DT>(qpair[r]);
+        uint4 mine;
+        const GroupScale gs = append_row_short<DT>(
+            K, V, lay.rows_of(unit), const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kbits)),
+            const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kmeta)), unit, Lold, max_ctx, kn, vn, lane, wave, tail_rows,
+            reinterpret_cast<float4*>(lscore), mine);
+        if (wave == 0) {
+          newmax[(size_t)unit * kD + 2 * lane] = gs.amax0();
+          newmax[(size_t)unit * kD + 2 * lane + 1] = gs.amax1();
         }
-        // this workgroup scores nothing else: the weights take the operands' place
-        const float sc = tail_scores(mine, 0, q0, q1, gs, reinterpret_cast<float*>(a_lds));
-        if (lane < ntok) {
-          scores[(size_t)unit * max_ctx + t0 + lane] = sc;
-          atomicAdd(&lhist[sel_bin(sc, R, hscale, kSelBins)], 1u);
+        if (wave * kTailRows < ntok) {
+          float q0 = 0.f, q1 = 0.f;
+#pragma unroll
+          for (int r = 0; r < NREP; ++r) {
+            q0 += lo16f<DT>(qpair[r]);
+            q1 += hi16f<DT>(qpair[r]);
+          }
+          // this workgroup scores nothing else: the weights take the operands' place
+          const float sc = tail_scores8(mine, wave, q0, q1, gs, a_lds + wave * kAWave);
+          const int tok = wave * kTailRows + lane;
+          if (lane < kTailRows && tok < ntok) {
+            scores[(size_t)unit * max_ctx + t0 + tok] = sc;
+            atomicAdd(&lhist[sel_bin(sc, R, hscale, kSelBins)], 1u);
+          }
         }
       }
       if constexpr (LONG) {
         // Groups of 64, 128 or 256 tokens: all four wavefronts, 32 tokens at a time; a chunk is scored as soon as its
         // code words exist.
-        static_assert(kAWave >= 4 * kTailWeights && sizeof(lscore) >= 4 * 64 * sizeof(float4), "scratch of the appending workgroup");
+        static_assert(kAWave >= kTailLds && sizeof(lscore) >= 4 * 64 * sizeof(float4), "scratch of the appending workgroup");
         float q0 = 0.f, q1 = 0.f;
 #pragma unroll
         for (int r = 0; r < NREP; ++r) {
@@ -237,7 +243,7 @@ __global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void s
             K, V, lay.rows_of(unit), const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kbits)),
             const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(kmeta)), unit, Lold, max_ctx, 1 << gshift, kn, vn, lane,
             wave, tail_rows, reinterpret_cast<float4*>(lscore), [&](int c, const uint4& mine, const GroupScale& g) {
-              const float sc = tail_scores(mine, c & 1, q0, q1, g, reinterpret_cast<float*>(a_lds + wave * kAWave));
+              const float sc = tail_scores(mine, c & 1, q0, q1, g, a_lds + wave * kAWave);
               const int tok = (c >> 1) * kPair + lane;  // within the group
               if (tok < ntok && lane >> 5 == (c & 1)) {
                 scores[(size_t)unit * max_ctx + t0 + tok] = sc;

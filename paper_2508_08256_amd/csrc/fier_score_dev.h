@@ -67,39 +67,67 @@ __device__ __forceinline__ uint32_t row_allmax_u32(uint32_t x) {
   return x;
 }
 
-// Scores of up to 32 tokens of one group from their code words, for the tokens an append has just quantized: lane
-// 32 half + t holds token t's word, every lane q_c (q0, q1) and the group's scale of channels c = 2 lane, 2 lane + 1.  The
-// weights are q_c s_c, base = sum_c q_c z_c.  The lower half of the lanes adds up the weights of words 0 and 1 of its token's set bits, the upper
-// half those of words 2 and 3 (bit i of word d is channel 64 (d & 1) + 2 i + (d >> 1)).  wl: kTailWeights floats of LDS.
-// Returns the score of token lane % 32.
-constexpr int kTailWeights = 132;
-__device__ __forceinline__ float tail_scores(const uint4& mine, int half, float q0, float q1, const GroupScale& g, float* wl) {
+// Scores of tokens an append has just quantized, from their code words: the weights q_c s_c of a token's set bits plus base =
+// sum_c q_c z_c.  q0, q1: q_c of channels c = 2 lane, 2 lane + 1.  The 128 bits are added up 16 at a time and these eight sums
+// in pairs, the same in both functions: tail_scores8 has a lane per (16 bits, token) of eight tokens, tail_scores a lane per
+// (half of the bits, token) of 32.  Bit i of word d is channel 64 (d & 1) + 2 i + (d >> 1).  lds: kTailLds bytes, the wavefront's.
+constexpr int kTailPitch = 20;  // floats per 16 weights: eight lanes' reads fall in different banks
+constexpr int kTailLds = 8 * kTailPitch * 4 + 8 * 16;
+__device__ __forceinline__ float tail_weights(float q0, float q1, const GroupScale& g, float* wl) {
   const int lane = threadIdx.x & 63;
-  wl[lane] = q0 * g.sf0;
-  wl[68 + lane] = q1 * g.sf1;  // 4 banks on: the two halves of the lanes read side by side
-  const float base = wave_allsum(fmaf(q1, g.zf1, q0 * g.zf0));  // the same rounding in every kernel
-  const u32x2_t a = __builtin_amdgcn_permlane32_swap(mine.x, mine.z, false, false);
-  const u32x2_t b = __builtin_amdgcn_permlane32_swap(mine.y, mine.w, false, false);
-  const uint32_t wd[2] = {half ? a[1] : a[0], half ? b[1] : b[0]};
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const float* w = wl + 68 * (lane >> 5);
+  float* w = wl + (lane >> 4) * kTailPitch + (lane & 15);
+  w[0] = q0 * g.sf0;
+  w[4 * kTailPitch] = q1 * g.sf1;
+  return wave_allsum(fmaf(q1, g.zf1, q0 * g.zf0));
+}
+__device__ __forceinline__ float tail_sum16(uint32_t bits, const float* w) {
   float acc = 0.f;
 #pragma unroll
-  for (int d = 0; d < 2; ++d) {
-#pragma unroll
-    for (int i = 0; i < 32; i += 4) {
-      const float4 w4 = *reinterpret_cast<const float4*>(w + 32 * d + i);
-      acc += (wd[d] >> i & 1u) ? w4.x : 0.f;
-      acc += (wd[d] >> (i + 1) & 1u) ? w4.y : 0.f;
-      acc += (wd[d] >> (i + 2) & 1u) ? w4.z : 0.f;
-      acc += (wd[d] >> (i + 3) & 1u) ? w4.w : 0.f;
-    }
-    asm volatile("" : "+v"(acc));  // a word's weights at a time
+  for (int i = 0; i < 16; i += 4) {
+    const float4 w4 = *reinterpret_cast<const float4*>(w + i);
+    acc += (bits >> i & 1u) ? w4.x : 0.f;
+    acc += (bits >> (i + 1) & 1u) ? w4.y : 0.f;
+    acc += (bits >> (i + 2) & 1u) ? w4.z : 0.f;
+    acc += (bits >> (i + 3) & 1u) ? w4.w : 0.f;
   }
+  return acc;
+}
+__device__ __forceinline__ float sum_swap32(float x) {
+  const u32x2_t s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+// Lane 8 c + t holds token t's word; every lane gets the score of token lane % 8.
+__device__ __forceinline__ float tail_scores8(const uint4& mine, int c, float q0, float q1, const GroupScale& g, unsigned char* lds) {
+  const int lane = threadIdx.x & 63;
+  float* wl = reinterpret_cast<float*>(lds);
+  unsigned char* words = lds + 8 * kTailPitch * 4;
+  const float base = tail_weights(q0, q1, g, wl);
+  if (lane >> 3 == c) reinterpret_cast<uint4*>(words)[lane & 7] = mine;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const uint32_t bits = *reinterpret_cast<const uint16_t*>(words + 16 * (lane & 7) + 2 * (lane >> 3));
+  float acc = tail_sum16(bits, wl + (lane >> 3) * kTailPitch);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // reads done before what comes into their place
-  const u32x2_t s = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc), __float_as_uint(acc), false, false);
-  return __uint_as_float(s[0]) + __uint_as_float(s[1]) + base;
+  acc += row_ror<8>(acc);
+  const u32x2_t s = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc), __float_as_uint(acc), false, false);
+  return sum_swap32(__uint_as_float(s[0]) + __uint_as_float(s[1])) + base;
+}
+// Lane 32 half + t holds token t's word; every lane gets the score of token lane % 32.
+__device__ __forceinline__ float tail_scores(const uint4& mine, int half, float q0, float q1, const GroupScale& g, unsigned char* lds) {
+  const int lane = threadIdx.x & 63;
+  float* wl = reinterpret_cast<float*>(lds);
+  const float base = tail_weights(q0, q1, g, wl);
+  const u32x2_t a = __builtin_amdgcn_permlane32_swap(mine.x, mine.z, false, false);
+  const u32x2_t b = __builtin_amdgcn_permlane32_swap(mine.y, mine.w, false, false);
+  const uint32_t w0 = half ? a[1] : a[0], w1 = half ? b[1] : b[0];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const float* w = wl + 4 * kTailPitch * (lane >> 5);
+  float s0 = tail_sum16(w0, w) + tail_sum16(w0 >> 16, w + kTailPitch);
+  asm volatile("" : "+v"(s0));  // a word's weights at a time
+  const float s1 = tail_sum16(w1, w + 2 * kTailPitch) + tail_sum16(w1 >> 16, w + 3 * kTailPitch);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // reads done before what comes into their place
+  return sum_swap32(s0 + s1) + base;
 }
 
 // One wavefront's scorer.  a_lds: its kAWave bytes of LDS.

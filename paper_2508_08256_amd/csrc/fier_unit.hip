@@ -3,8 +3,8 @@
 //
 // The scores of a unit fit LDS, so nothing of the step leaves the workgroup: no histogram in memory, no candidates, threshold
 // word or partials handed over, no second launch, no merge.  In order:
-//   1. the tail group's wavefronts (one per 32 tokens of the group) re-quantize it with the new row and score it from their
-//      registers; the others score pair blocks (BlockScorer), every score is binned into an LDS histogram over [-R, R];
+//   1. the tail group is re-quantized with the new row and scored from registers, a wavefront per eight tokens; the
+//      wavefronts score pair blocks (BlockScorer); every score is binned into an LDS histogram over [-R, R];
 //   2. one scan finds the threshold bin; its members (about 1 % of the tokens) are ranked against each other, a wavefront
 //      per candidate, 64 comparisons per instruction (beyond kUnitCand members: the radix selection over LDS);
 //   3. the selected tokens are listed in ascending order (LDS, and idx_out), a thread owning consecutive tokens;
@@ -26,17 +26,17 @@ constexpr int kUnitMaxCtx = 16384;
 constexpr int kUnitAhead = 3;   // pair blocks in flight per wavefront
 
 // LDS of a workgroup of nw wavefronts beyond its fixed arrays, bytes from the start: scores and the scorers' operands, whose
-// place the partials take later; the row list; for long groups the minima and maxima the tail's wavefronts exchange.
+// place the partials take later; the row list; the minima and maxima the tail's wavefronts exchange.
 struct UnitLds {
   uint32_t operands, rows, exchange, bytes;
 };
-inline UnitLds unit_lds(int nw, int n_rep, int max_ctx, int max_budget, int gshift) {
+inline UnitLds unit_lds(int nw, int n_rep, int max_ctx, int max_budget) {
   UnitLds l;
   l.operands = (uint32_t)max_ctx * 4;
   const uint32_t scoring = l.operands + (uint32_t)nw * kAWave, partials = (uint32_t)(n_rep * (nw * 160 + 10)) * 4;
   l.rows = ((scoring > partials ? scoring : partials) + 15) / 16 * 16;
   l.exchange = l.rows + ((uint32_t)max_budget * 2 + 15) / 16 * 16;
-  l.bytes = l.exchange + (gshift ? (kG / 4) * 64 * 16 : 0);
+  l.bytes = l.exchange + (uint32_t)nw * 64 * 16;
   return l;
 }
 
@@ -98,6 +98,9 @@ template <int DT, int NREP, int NW, bool STREAM>
 __global__ __launch_bounds__(64 * NW, 4) void unit_step_kernel(UnitArgs a, const LayerBatch lb) {
   constexpr int NT = 64 * NW;
   constexpr int kPitch = NW * 160 + 10;  // floats per head of the partials
+  // Tokens of the tail group per wavefront.  With two workgroups per CU the other one fills the gaps of the chain and what counts
+  // is its instructions (16 layers of 64 ragged paged units up to 8k 95.4 us, 97.9 with eight tokens a wavefront).
+  constexpr int CH = NW == 16 ? kTailRows : kG;
   extern __shared__ __attribute__((aligned(16))) unsigned char arena[];
   __shared__ __attribute__((aligned(16))) uint32_t hist[kSelBins];
   __shared__ unsigned long long cand[kUnitCand];
@@ -174,21 +177,20 @@ __global__ __launch_bounds__(64 * NW, 4) void unit_step_kernel(UnitArgs a, const
     // ---- 1. append and score --------------------------------------------------------------------------------------------
     const uint16_t* qb = a.q + (size_t)unit * NREP * kD;
     const int gsize = kG << a.gshift, t0 = Lold & ~(gsize - 1), ntok = Lold - t0 + 1;  // the tail group with the new row
-    const int ns = 1 << a.gshift;
-    const bool tail = app && wave < ns;  // this wavefront has the chunk of 32 tokens `wave` of the tail group
+    // its chunks of CH tokens, to the end of the group (32 tokens) or of the last pair block that holds one; wavefront w has
+    // the chunks w, w + NW, ...; one that has the whole group for itself scores nothing else
+    const int chunks = app ? (a.gshift ? (ntok + kPair - 1) / kPair * (kPair / CH) : kG / CH) : 0;
+    const int first = chunks == 1 ? 1 : 0, n_waves = NW - first, P0 = wave - first;
     const int tail_start = app ? t0 : n;
-    // pair blocks of this wavefront: with 32-token groups wavefront 0 has the tail to itself
-    const int first = app && ns == 1 ? 1 : 0, n_waves = NW - first;
-    const int n_blocks = (tail_start + kPair - 1) / kPair;
-    const int P0 = wave - first;
+    const int n_blocks = (tail_start + kPair - 1) / kPair;  // pair blocks P0, P0 + n_waves, ... are this wavefront's
     const int nb = P0 >= 0 && P0 < n_blocks ? (n_blocks - P0 + n_waves - 1) / n_waves : 0;
-    uint32_t kn = 0, vn = 0, trow[kG], qpair[NREP];
-    if (tail) {
+    uint32_t kn = 0, vn = 0, trow[CH], qpair[NREP];
+    if (wave < chunks) {
       kn = a.k_new[(size_t)unit * (kD / 2) + lane];
       vn = a.v_new[(size_t)unit * (kD / 2) + lane];
 #pragma unroll
       for (int r = 0; r < NREP; ++r) qpair[r] = reinterpret_cast<const uint32_t*>(qb + r * kD)[lane];
-      append_load_rows(a.K, kv, t0, ntok, wave, lane, trow);
+      tail_load(a.K, kv, t0, ntok, wave, lane, trow);
     }
     const int row = lane >> 4, m16 = lane & 15, gsel = row >> 1, hsel = row & 1;
     const uint4* const pb = a.kbits + ((size_t)unit * max_ctx + (size_t)(P0 > 0 ? P0 : 0) * kPair + lane);
@@ -233,59 +235,59 @@ __global__ __launch_bounds__(64 * NW, 4) void unit_step_kernel(UnitArgs a, const
     }
     __syncthreads();  // the histogram is clear; the loads above are on their way
     FIER_PROF_WG(1)
-    MinMax mm;
-    if (tail) {
-      if (ns == 1) __builtin_amdgcn_s_setprio(3);  // the longest chain of the phase at short contexts
-      mm = append_minmax<DT>(trow, ntok, wave, kn, ns > 1);
-      if (ns > 1) reinterpret_cast<float4*>(arena + a.lds.exchange)[wave * 64 + lane] = make_float4(mm.mn0, mm.mx0, mm.mn1, mm.mx1);
-    }
-    if (app && ns > 1) __syncthreads();  // exchanged
+    float4* const exchange = reinterpret_cast<float4*>(arena + a.lds.exchange);
     unsigned char* const operands = arena + a.lds.operands + wave * kAWave;
-    if (tail) {
-      if (ns > 1)
-        for (int k = 0; k < ns; ++k) {
-          const float4 o = reinterpret_cast<const float4*>(arena + a.lds.exchange)[k * 64 + lane];
-          mm.mn0 = fminf(mm.mn0, o.x), mm.mx0 = fmaxf(mm.mx0, o.y), mm.mn1 = fminf(mm.mn1, o.z), mm.mx1 = fmaxf(mm.mx1, o.w);
-        }
-      const GroupScale gs = group_scale<DT>(mm);
-      int nt = ntok - wave * kG;
-      nt = nt > kG ? kG : nt;
-      const int half = ns == 1 ? 0 : wave & 1;  // the chunk's lanes; with 32-token groups always the lower ones
-      uint4 mine;
-      append_codes<DT>(trow, ntok, wave, kn, gs, lane, half * kG, mine);
-      uint32_t* const meta = const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(a.kmeta)) +
-                             ((size_t)unit * (max_ctx >> (5 + a.gshift)) + (size_t)(t0 >> (5 + a.gshift))) * kD;
+    if (wave < chunks) {
+      MinMax mm = tail_minmax_start<DT>(trow, ntok, wave, kn, a.gshift != 0);
+      tail_minmax<DT>(mm, trow, ntok, wave, kn);
+      for (int c = wave + NW; c * CH < ntok; c += NW) {
+        uint32_t r[CH];
+        tail_load(a.K, kv, t0, ntok, c, lane, r);
+        tail_minmax<DT>(mm, r, ntok, c, kn);
+      }
+      exchange[wave * 64 + lane] = make_float4(mm.mn0, mm.mx0, mm.mn1, mm.mx1);
+    }
+    if (chunks > 1) __syncthreads();
+    if (wave < chunks) {
+      const GroupScale gs = group_scale<DT>(tail_join(exchange, chunks < NW ? chunks : NW, lane));
+      uint2* const meta = reinterpret_cast<uint2*>(const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(a.kmeta)) +
+                             ((size_t)unit * (max_ctx >> (5 + a.gshift)) + (size_t)(t0 >> (5 + a.gshift))) * kD) + lane;
       uint4* const bits = const_cast<uint4*>(a.kbits) + (size_t)unit * max_ctx + t0;
       if (wave == 0) {
         a.K[kv.row(Lold) * (kD / 2) + lane] = kn;
         a.V[kv.row(Lold) * (kD / 2) + lane] = vn;
-        reinterpret_cast<uint2*>(meta)[lane] = make_uint2(gs.s0 | (gs.z0 << 16), gs.s1 | (gs.z1 << 16));
+        *meta = make_uint2(gs.s0 | (gs.z0 << 16), gs.s1 | (gs.z1 << 16));
         amax_lo = gs.amax0();
         amax_hi = gs.amax1();
+        if (a.gshift == 0 && (t0 & kG) == 0 && ntok == 1) {  // opens a pair block: its second group holds no token yet
+          if (lane >= kG) bits[lane] = make_uint4(0, 0, 0, 0);
+          meta[kD / 2] = make_uint2(0, 0);
+        }
       }
-      if (ns == 1) {
-        // a row that opens a pair block: its second group holds no token yet
-        const bool opens = (t0 & kG) == 0 && ntok == 1;
-        if (lane < kG || opens) bits[lane] = mine;
-        if (opens) reinterpret_cast<uint2*>(meta + kD)[lane] = make_uint2(0, 0);
-      } else if ((wave >> 1) * kPair < ntok && lane >> 5 == half) {
-        bits[(wave >> 1) * kPair + lane] = mine;
-      }
-      if (nt > 0) {
-        float q0 = 0.f, q1 = 0.f;
+      float q0 = 0.f, q1 = 0.f;
 #pragma unroll
-        for (int r = 0; r < NREP; ++r) {
-          q0 += lo16f<DT>(qpair[r]);
-          q1 += hi16f<DT>(qpair[r]);
-        }
-        const float sc = tail_scores(mine, half, q0, q1, gs, reinterpret_cast<float*>(operands));
-        const int tok = wave * kG + lane - half * kG;
-        if (lane >> 5 == half && tok < ntok) {
-          scores[t0 + tok] = sc;
-          atomicAdd(&hist[sel_bin(sc, R, hscale, kSelBins)], 1u);
-        }
+      for (int r = 0; r < NREP; ++r) {
+        q0 += lo16f<DT>(qpair[r]);
+        q1 += hi16f<DT>(qpair[r]);
       }
-      __builtin_amdgcn_s_setprio(0);
+#pragma unroll 1
+      for (int c = wave;;) {
+        const uint4 mine = tail_codes<DT>(trow, ntok, c, kn, gs, lane);
+        if (lane / CH == c % (kPair / CH)) bits[c * CH / kPair * kPair + lane] = mine;
+        if (c * CH < ntok) {
+          float sc;
+          if constexpr (CH == kG) sc = tail_scores(mine, c & 1, q0, q1, gs, operands);
+          else sc = tail_scores8(mine, c & 7, q0, q1, gs, operands);
+          const int tok = c * CH + lane;
+          if (lane < CH && tok < ntok) {
+            scores[t0 + tok] = sc;
+            atomicAdd(&hist[sel_bin(sc, R, hscale, kSelBins)], 1u);
+          }
+        }
+        c += NW;
+        if (c >= chunks) break;
+        tail_load(a.K, kv, t0, ntok, c, lane, trow);
+      }
     }
     FIER_PROF_WG(2)
     if (nb > 0) {
@@ -565,7 +567,7 @@ int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx, int
   const int nw = grid <= 256 ? 16 : 8;
   const int64_t limit = grid <= 64 ? 5500 : grid <= 256 ? 5500 + (grid - 64) * 40 : grid <= 512 || n_rep >= 3 ? 12000 : 8000;
   if (work > limit) return 0;
-  return unit_lds(nw, n_rep, max_ctx, max_budget, group_size > kG).bytes + kUnitFixedLds <= (nw == 16 ? 160u : 80u) * 1024u ? nw : 0;
+  return unit_lds(nw, n_rep, max_ctx, max_budget).bytes + kUnitFixedLds <= (nw == 16 ? 160u : 80u) * 1024u ? nw : 0;
 }
 
 hipError_t launch_unit_step(int nw, int dtype, KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta,
@@ -604,7 +606,7 @@ hipError_t launch_unit_step(int nw, int dtype, KvLayout lay, int n_rep, const ui
   a.by_length = batch > 1 && batch <= 64 && grid > 256L * (16 / nw);  // at four wavefronts per SIMD
   a.scored = scored;
   a.lay = lay;
-  a.lds = unit_lds(nw, n_rep, max_ctx, max_budget, a.gshift);
+  a.lds = unit_lds(nw, n_rep, max_ctx, max_budget);
   const bool stream = grid * max_budget * (2 * kD * 2) >= (8L << 20);  // as the other gathers
   if (dtype == DT_F16)
     return (nw == 16 ? launch_unit_step_dt<DT_F16, 16> : launch_unit_step_dt<DT_F16, 8>)(a, n_rep, stream, lb, st);
