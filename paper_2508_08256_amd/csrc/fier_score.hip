@@ -27,12 +27,14 @@ constexpr int kScoreMaxBpw = 13;  // pair blocks per wavefront at most (the laun
 // of the step through `newmax`.  A score outside [-R, R] simply lands in the outermost bin.
 // LONG: quantization groups longer than 32 tokens.  (Separate variants: the long groups' append takes more registers, and
 // in one kernel with the other cost the 32-token groups their fifth workgroup per CU: 56 -> 60 us at 32 units x 128k.)
-//   The bound asks for four workgroups per CU from two query heads per kv head on: asked for five the compiler put 12 to
+//   The bound asks for six workgroups per CU with 32-token groups (69 to 77 registers; us per step at five / six / seven: 32 units
+// x 128k 55.0 / 53.3 / 53.6, 128 ragged units up to 64k 96.9 / 96.7 / 97.2, three such layers 266.6 / 265.6 / 265.2, 32 x 32k
+// 32.0 / 32.1 / 31.9), with longer ones for four from two query heads per kv head on: asked for five the compiler put 12 to
 // 36 bytes per lane into scratch, asked for four it needs at most 96 registers up to six heads (five workgroups fit all the
 // same) and 102 at eight.  us per step, with scratch / now, fp16, g = 128: 4 heads 30.7 / 30.4 at 8 units x 32k, 59.9 / 57.9
 // at 32 x 128k, 68.1 / 66.2 at 128 ragged units up to 30k; 6 heads 31.6 / 31.4 at 8 x 8k, 73.0 / 71.2 at the ragged ones.
 template <int DT, int NREP, bool HIST, bool STREAM, bool LONG, class LAYERS>
-__global__ __launch_bounds__(256, HIST && LONG ? (NREP == 1 ? 5 : 4) : 1) void score_kernel(const uint4* kbits, const uint4* kmeta,
+__global__ __launch_bounds__(256, HIST ? (!LONG ? 6 : NREP == 1 ? 5 : 4) : 1) void score_kernel(const uint4* kbits, const uint4* kmeta,
                                                     const float* __restrict__ kabsmax, const uint16_t* __restrict__ q,
                                                     const int32_t* __restrict__ seq_lens, int extra,
                                                     float* __restrict__ scores, UnitCtl* __restrict__ ctl,
@@ -340,8 +342,8 @@ hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits, const
                                   int group_size, const LayerBatch& lb, hipStream_t st) {
   const int gshift = group_size == 256 ? 3 : group_size == 128 ? 2 : group_size == 64 ? 1 : 0;
   // Blocks per wavefront.  The smallest that lets every workgroup be resident at once (256 CUs; the registers
-  // allow 5 workgroups per CU for the fused kernel -- 4 with 8 query heads per kv head, or 7 at longer groups --, 8 for the score-only
-  // one), at least 4: prologue (q, R) and epilogue (histogram flush) are then paid once.  Beyond 12 the grid is cut into several rounds of shorter
+  // allow 6 workgroups per CU for the fused kernel, 5 at longer groups -- 4 with 7 or 8 query heads per kv head --, 8 for the
+  // score-only one), at least 4: prologue (q, R) and epilogue (histogram flush) are then paid once.  Beyond 12 the grid is cut into several rounds of shorter
   // workgroups instead: a workgroup's lifetime bounds the ragged end of the kernel, and in a batch of unequal
   // contexts (the host cannot see the lengths) the short units' workgroups exit at once and the dispatcher
   // backfills the machine with the long units' -- with one round, a few long units would stream alone at one
@@ -349,7 +351,7 @@ hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits, const
   // collide in the memory channels: measured 8 vs 7 or 9, 16 vs 13).
   const int n_blocks = (max_ctx + kPair - 1) / kPair;
   const int all_units = units * lb.n;  // of all layers of the launch
-  const int wg_slots = HIST ? 256 * 5 - all_units : 256 * 8;
+  const int wg_slots = HIST ? 256 * (gshift ? 5 : 6) - all_units : 256 * 8;
   const int per_unit = wg_slots / all_units > 0 ? wg_slots / all_units : 1;
   int bpw = (n_blocks + 4 * per_unit - 1) / (4 * per_unit);
   bpw = bpw < 4 ? 4 : bpw;
