@@ -30,9 +30,18 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint4* __restrict
                                                          int n_kv_heads, int max_ctx, int unit_major, KvLayout lay) {
   __shared__ __attribute__((aligned(16))) float sh_o[NREP * kPartialFloats];
   __shared__ uint32_t flag;
+  // The rows of the workgroup's entries of the list, looked up once and all at once, before the unit's count is known: a lookup
+  // per tile put a list entry's (and a paged row's block number's) round trip in front of every tile's rows.
+  __shared__ size_t lrow[kAttnRowsSparse];
 
   const int unit = unit_major ? blockIdx.x : blockIdx.y, split = unit_major ? blockIdx.y : blockIdx.x;
   const int b = unit / n_kv_heads;
+  const KvRows kv = lay.rows_of(unit);
+  if (idx && threadIdx.x < kAttnRowsSparse && split * rows_per_wg + (int)threadIdx.x < max_budget) {
+    const int t = idx[(size_t)unit * max_budget + split * rows_per_wg + threadIdx.x];
+    // an index outside the cache places no row: the entry is skipped (it gets no weight); entries past the count are not used
+    lrow[threadIdx.x] = (t < 0 || t >= max_ctx) ? kNoRow : kv.row(t);
+  }
   int n;
   if (idx) {
     n = count[unit];
@@ -48,8 +57,8 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint4* __restrict
   }
   if (start >= n) return;
   const int end = n < start + rows_per_wg ? n : start + rows_per_wg;
-  const int32_t* __restrict__ sel = idx ? idx + (size_t)unit * max_budget : nullptr;
-  const KvRows kv = lay.rows_of(unit);
+  const bool sel = idx != nullptr;
+  if (sel) __syncthreads();
   // whole-cache attention over paged rows: the block numbers of this workgroup's rows wait in LDS
   __shared__ int32_t lblk[kAttnRowsDenseMax / 64];
   const bool window = !sel && kv.blocks != nullptr;
@@ -59,11 +68,7 @@ __global__ __launch_bounds__(256) void attn_split_kernel(const uint4* __restrict
     __syncthreads();
   }
   const int first_block = start >> kv.shift;
-  // an index outside the cache places no row: the entry is skipped (it gets no weight)
-  auto row_sel = [&](int j) {
-    const int t = sel[j];
-    return (t < 0 || t >= max_ctx) ? kNoRow : kv.row(t);
-  };
+  auto row_sel = [&](int j) { return lrow[j - start]; };
   const size_t safe_row = kv.row(0);
   auto row_all = [&](int j) {
     return window ? (size_t)lblk[(j >> kv.shift) - first_block] * kv.block_stride + kv.base + (size_t)(j & kv.mask)
@@ -246,7 +251,7 @@ static hipError_t launch_attn_dt(KvLayout lay, int n_rep, const void* K, const v
   const int unit_major = idx != nullptr && (long)units * n_splits <= 2 * 256L * (n_rep >= 3 ? 4 : 7) ? 1 : 0;
   dim3 grid = unit_major ? dim3(units, n_splits) : dim3(n_splits, units);
   const float sl2 = sm_scale * 1.4426950408889634f;
-  if (!idx && rows_per_wg > kAttnRowsDenseMax) return hipErrorInvalidValue;  // the kernel's block-number window
+  if (rows_per_wg > (idx ? kAttnRowsSparse : kAttnRowsDenseMax)) return hipErrorInvalidValue;  // the kernel's row list and window
   // Whole-cache attention reads every row once: from 64 MB of rows on they are loaded with the streaming hint
   // (measured: 32 units x 32k 98-101 -> 90-91 us, 32 x 64k 186 -> 165-172, 32 x 128k at 4 heads per kv head 398-406 ->
   // 384; 8 units x 4k, which the caches hold, 15.5 -> 19.2 with it).
