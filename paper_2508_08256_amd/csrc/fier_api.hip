@@ -142,8 +142,9 @@ inline int hip_status(hipError_t e) { return e == hipSuccess ? FIER_OK : FIER_EH
 // Layers of one fused-step launch: up to 16, up to 2^25 cached tokens and units, and up to 512 MiB of workspace.  Layer by
 // layer, a small layer pays two launches, their prologues and drains and its serial hand-offs (threshold, merge) with most
 // of the chip idle; side by side the layers fill each other's gaps.  Measured (us per call, layer by layer / side by side):
-// 16 layers of 64 units x 1k..8k, paged, 4 query heads per kv head 499 / 139; 8 layers of 8 units x 32k, 4 heads 209 / 55; 2
-// layers of 16 units x 20k with the index list 73 / 42.  Layers that fill the chip by themselves gain little: 4 layers of
+// 16 layers of 64 units x 1k..8k, paged, 4 query heads per kv head 499 / 139 (93-95 by the kernel for short contexts, which
+// takes that shape now); 8 layers of 8 units x 32k, 4 heads 209 / 55 (now 52.6); 2 layers of 16 units x 20k with the index
+// list 73 / 42 (now 35.3).  Layers that fill the chip by themselves gain little: 4 layers of
 // 128 units x 8k..64k (65600 rows of capacity) 409 one by one, 399 as 2 + 2, 390 as 3 + 1, 372 all four.  The two bounds
 // hold the memory back: 2^25 tokens need 270 MB at one head per kv head (3 layers of that batch), several times as much at
 // 8 heads and budgets of the whole context, which the bytes stop.
@@ -439,7 +440,7 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
                                    std::min(phase == 0 ? fier::kMaxLayersPerLaunch : most, n_layers - l), w.bytes);
     // One workgroup per unit and one launch for short contexts: needs no part of the workspace per layer.  Its phase 2 is
     // that kernel on the scores of phase 1.
-    const int unit_waves = phase > 3 ? 0 : fier::unit_form(units, lb.n, n_rep, max_budget, cfg->max_ctx, cfg->group_size);
+    const int unit_waves = phase > 3 ? 0 : fier::unit_form(units, lb.n, n_rep, max_budget, cfg->max_ctx);
     if (unit_waves && (phase == 0 || phase == 2)) {
       e = fier::launch_unit_step(unit_waves, cfg->kv_dtype, lay, n_rep, c->kbits, c->kmeta, c->kabsmax, ql, c->seq_lens, w.sb,
                                  budgets, max_budget, cfg->sm_scale, c->k, c->v, kn, vn, outl, idxl, cntl, cfg->batch,

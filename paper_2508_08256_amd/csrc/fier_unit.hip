@@ -556,12 +556,12 @@ FIER_UNIT_INSTANCE(extern, DT_BF16, 16)
 //   128 units     1k 19.7 / 11.3 / 10.8  2k 22.3 / 15.7 / 16.9   4k 24.8 / 21.8 / 26.1   8k 33.1 / 35.4 / 45.6
 //   256, 4 heads  1k 22.8 / 14.0 / 13.4  4k 35.1 / 29.2 / 31.0   8k 52.1 / 45.5 / 51.8   16k 79.8 / 81.9 / 98.0
 //   512, 4 heads  1k 29.9 / 27.0 / 17.8  4k 54.9 / 55.8 / 43.6   8k 83.7 / 86.9 / 73.3
-//   16 layers of 64 ragged paged units up to 8k, 4 heads  126 / - / 95
+//   16 layers of 64 ragged paged units up to 8k, 4 heads  126 / - / 93-95 per call of all 16
 // Hence up to 256 workgroups 16 wavefronts, to a number of tokens and rows that grows with the share of the GPU in use;
 // beyond, 8 wavefronts (two workgroups per CU), to 12000 tokens and rows, with one or two heads, whose two-kernel form has
 // more wavefronts per CU, and more workgroups than are resident to 8000.  Over 491 random shapes up to 16k tokens (1 to 17
 // layers, 4 to 6000 units, budgets of 4 to 50 %) 1.28 times as fast as two kernels everywhere, and at most 1.07 times as slow.
-int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx, int group_size) {
+int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx) {
   if (max_ctx > kUnitMaxCtx) return 0;
   const int64_t grid = (int64_t)units * layers, work = (int64_t)max_ctx + max_budget;
   const int nw = grid <= 256 ? 16 : 8;
