@@ -195,6 +195,7 @@ __device__ __forceinline__ uint2 pack_part(const float (&x)[4]) {
                     __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07060302u));
 }
 
+constexpr float kLargeLogit = 0x1p22f;  // below it a logit's rounding error is at most 1/8 and a weight at most 1.1
 // As attend_rows, for three to eight query heads per kv head.  STREAM_V: the V rows with the streaming hint (the K rows, which
 // are loaded in four pieces per row, keep plain loads in gathers).
 template <int DT, int NREP, bool CHECKED = false, bool STREAM = false, bool STREAM_V = STREAM, int NW = 4, class RowOf>
@@ -208,6 +209,7 @@ __device__ __forceinline__ void attend_rows_mfma(const uint4* __restrict__ K, co
   const int n = lane & 15, kq = lane >> 4;
   const int part = n / kCols;
   const uint32_t cut1 = part >= 1 ? kLead : 0u, cut2 = part >= 2 ? kLead : 0u;
+  bool large = __ballot(st.m != -INFINITY && fabsf(st.m) >= kLargeLogit) != 0ull;  // some column's maximum
   for (int j0 = start + wave * 16; j0 < end; j0 += NW * 16) {
     uint4 kk[4], vv[4];
     size_t rk = row_of(j0 + n < end ? j0 + n : start);
@@ -236,15 +238,25 @@ __device__ __forceinline__ void attend_rows_mfma(const uint4* __restrict__ K, co
     const float mx = fmaxf(st.m, rows_allmax(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]))));
     const float mref = mx == -INFINITY ? 0.f : mx;
     const float alpha = __builtin_amdgcn_exp2f(st.m - mref);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)  // the scaled logit unrounded
-      p[i] = valid[i] ? __builtin_amdgcn_exp2f(fmaf(s[i], scale_log2e, -mref)) : 0.f;
-    st.l = st.l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
-    st.m = mx;
     if (__ballot(alpha != 1.0f)) {  // the maxima settle after a few tiles
 #pragma unroll
       for (int c = 0; c < 8; ++c) st.o[c] *= alpha;
+      large = __ballot(fabsf(mref) >= kLargeLogit) != 0ull;
     }
+    // The weights take the scaled logit unrounded, which is the more accurate while logits are small: its distance from the
+    // rounded maximum then is, for the largest one, that one's rounding error, which from 2^24 on moves the largest weight itself
+    // away from 1 by powers of two.  Large logits are rounded as their maximum is: no weight above 1, the largest one 1.
+    float e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = fmaf(s[i], scale_log2e, -mref);
+    if (__builtin_expect(large, 0)) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) e[i] = fabsf(mref) >= kLargeLogit ? p[i] - mref : e[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p[i] = valid[i] ? __builtin_amdgcn_exp2f(e[i]) : 0.f;
+    st.l = st.l * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
+    st.m = mx;
     uint2 pb, pb_lo;
     float lo[4];
 #pragma unroll
