@@ -112,7 +112,8 @@ size_t fier_workspace_bytes(const fier_config *cfg, int32_t max_budget);
 /* The size from which fier_decode_step over n_layers layers runs them in as few launches as it can: a workspace of j
  * times fier_workspace_bytes lets up to j layers share a launch (at most 16, fewer where the layers are large), as long
  * as no two of them share an array they write; those that do run in order.  Block pools count as shared if their base
- * addresses are equal: pools that overlap at different bases must not hold one block for two layers of a call.
+ * addresses are equal: pools that overlap at different bases must not hold one block for two layers of a call with such a
+ * workspace (of one part, paged layers always run in order).
  * At most 512 MiB, or fier_workspace_bytes where that is more.  Any size from fier_workspace_bytes on gives the same
  * selections, and outputs that agree to the order of summation.  For fier_decode_step_mixed the larger of this, at its
  * max_budget, and fier_workspace_bytes(cfg, max_ctx).  0 if invalid. */
@@ -201,7 +202,8 @@ int fier_dense_attn(const fier_config *cfg, const fier_cache *cache, const void 
  *   idx_out / count_out   optional (NULL): [n_layers][units][max_budget] / [n_layers][units], the
  *            selection of every layer, for inspection
  *   workspace  at least fier_workspace_bytes(cfg, max_budget) bytes, reused by every layer; with more (see
- *            fier_workspace_bytes_layers) several layers run side by side
+ *            fier_workspace_bytes_layers) several layers run side by side; at short contexts layers whose rows are not paged
+ *            do so in any workspace
  * seq_lens are not modified.  A sequence whose cache is full (seq_len >= max_ctx) is not appended
  * to: the step works on its max_ctx rows as if k_new were NULL for it.
  */

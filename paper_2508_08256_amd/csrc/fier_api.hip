@@ -436,10 +436,12 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
       clear_parts = 1;
       continue;
     }
-    fier::LayerBatch lb = batch_of(cfg, c, dense_layers ? dense_layers + l : nullptr,
-                                   std::min(phase == 0 ? fier::kMaxLayersPerLaunch : most, n_layers - l), w.bytes);
-    // One workgroup per unit and one launch for short contexts: needs no part of the workspace per layer.  Its phase 2 is
-    // that kernel on the scores of phase 1.
+    // One workgroup per unit and one launch for short contexts: needs no part of the workspace per layer, so layers share it
+    // whatever the workspace -- unless their rows are paged: pools are told apart by their base addresses alone, and layers
+    // of overlapping pools that hold one block in common run in order in a workspace of one part.  Its phase 2 is that kernel
+    // on the scores of phase 1.
+    const int together = phase == 0 && !c->block_table ? fier::kMaxLayersPerLaunch : most;
+    fier::LayerBatch lb = batch_of(cfg, c, dense_layers ? dense_layers + l : nullptr, std::min(together, n_layers - l), w.bytes);
     const int unit_waves = phase > 3 ? 0 : fier::unit_form(units, lb.n, n_rep, max_budget, cfg->max_ctx);
     if (unit_waves && (phase == 0 || phase == 2)) {
       e = fier::launch_unit_step(unit_waves, cfg->kv_dtype, lay, n_rep, c->kbits, c->kmeta, c->kabsmax, ql, c->seq_lens, w.sb,

@@ -110,6 +110,32 @@ def test_layers_of_one_call_equal_single_layer_calls(case, parts):
             assert torch.equal(a[u, :n], b[u, :n])
 
 
+@pytest.mark.parametrize("ctx,max_ctx", [(700, 768), (6000, 6144)])
+def test_layers_of_overlapping_pools_run_in_order(ctx, max_ctx):
+    """Two layers on the same blocks of one pool, reached through two base addresses a block apart: in a workspace of one part
+    the second layer's append follows the first's, in the one-launch form of short contexts too, and it attends over its own row."""
+    batch, hq, hkv, bt, budget = 2, 8, 4, 64, 90
+    cfg = B.make_config(batch, hq, hkv, max_ctx, F16)
+    per = max_ctx // bt
+    rows = [torch.randn((batch * per + 1, hkv, bt, 128), device="cuda").half() for _ in range(2)]
+    table = 1 + torch.randperm(batch * per, device="cuda").to(torch.int32).view(batch, per)
+    lens, buds = (torch.full((batch,), x, dtype=torch.int32, device="cuda") for x in (ctx, budget))
+    q, kn, vn = (torch.randn((2, n, 128), device="cuda").half() for n in (batch * hq, cfg.units, cfg.units))
+    q[1] = kn[1].view(cfg.units, 1, 128).expand(-1, cfg.n_rep, -1).reshape(-1, 128)  # drawn to the second layer's own row
+    res = []
+    for calls in ([slice(0, 1), slice(1, 2)], [slice(0, 2)]):
+        k, v = (r.clone() for r in rows)
+        caches = [B.DeviceCache(cfg, k[:-1], v[:-1], lens, table), B.DeviceCache(cfg, k[1:], v[1:], lens, table - 1)]
+        for c in caches:
+            B.quantize_keys(cfg, c)
+        out, ws = torch.zeros((2, batch * hq, 128), device="cuda"), B.make_workspace(cfg, budget, 1)
+        for l in calls:
+            B.decode_step(cfg, caches[l], q[l], kn[l], vn[l], buds, budget, out[l], None, None, ws)
+        res.append([out, k, v] + [t for c in caches for t in (c.kbits, c.kmeta, c.kabsmax)])
+    assert float((res[0][0] - res[1][0]).abs().max()) <= 1e-4  # 90 terms in any order: 90 * 2^-24 * 5
+    assert all(torch.equal(a, b) for a, b in zip(res[0][1:], res[1][1:]))
+
+
 def test_workspace_for_layers_follows_the_number_of_layers():
     cfg = B.make_config(1, 8, 8, 4160)
     one = B.workspace_bytes(cfg, 512)
