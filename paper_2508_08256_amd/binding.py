@@ -147,6 +147,14 @@ def _ptr(t):
 _current_stream = None
 
 
+def _forget_stream():
+    global _current_stream
+    _current_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_stream)  # in a child torch refuses to use the GPU; the raw handle would not
+
+
 def _stream():
     """The handle of torch's current stream on the current device.  torch.cuda.current_stream makes a Stream object for it,
     which took 3.0 of the 8.9 us of a small call; the raw handle takes 0.2."""
