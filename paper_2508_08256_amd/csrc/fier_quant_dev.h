@@ -294,7 +294,11 @@ __device__ __forceinline__ GroupScale append_row_long(uint32_t* __restrict__ K, 
     int nt = ntok - c * kG;
     nt = nt > kG ? kG : nt;
     uint4 mine = make_uint4(0, 0, 0, 0);
-    code_rows<DT>(rows, nt, gs, lane, (c & 1) * kG, mine);
+    // Where the lane stands in the chunk, unknown to the compiler: it made the 32 row numbers and the 32 masks of lanes before the
+    // loop, 32 vector registers and 64 scalar ones, which spilled into a 97th vector register (score kernel, two to six heads).
+    int at = lane - (c & 1) * kG;
+    asm volatile("" : "+v"(at));
+    code_rows<DT>(rows, nt, gs, at, 0, mine);
     if (c < ns && (c >> 1) * kPair < ntok && lane >> 5 == (c & 1)) bdst[(c >> 1) * kPair + lane] = mine;
     if (nt > 0) on_chunk(c, mine, gs);
     c += 4;

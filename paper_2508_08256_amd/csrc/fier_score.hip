@@ -29,10 +29,11 @@ constexpr int kScoreMaxBpw = 13;  // pair blocks per wavefront at most (the laun
 // in one kernel with the other cost the 32-token groups their fifth workgroup per CU: 56 -> 60 us at 32 units x 128k.)
 //   The bound asks for six workgroups per CU with 32-token groups (69 to 77 registers; us per step at five / six / seven: 32 units
 // x 128k 55.0 / 53.3 / 53.6, 128 ragged units up to 64k 96.9 / 96.7 / 97.2, three such layers 266.6 / 265.6 / 265.2, 32 x 32k
-// 32.0 / 32.1 / 31.9), with longer ones for four from two query heads per kv head on: asked for five the compiler put 12 to
-// 36 bytes per lane into scratch, asked for four it needs at most 96 registers up to six heads (five workgroups fit all the
-// same) and 102 at eight.  us per step, with scratch / now, fp16, g = 128: 4 heads 30.7 / 30.4 at 8 units x 32k, 59.9 / 57.9
-// at 32 x 128k, 68.1 / 66.2 at 128 ragged units up to 30k; 6 heads 31.6 / 31.4 at 8 x 8k, 73.0 / 71.2 at the ragged ones.
+// 32.0 / 32.1 / 31.9), with longer ones for four from two query heads per kv head on: asked for five the compiler puts 8 to 20 bytes
+// per lane into scratch at five, seven and eight heads, asked for four it needs 88 to 96 registers up to seven heads (five workgroups fit
+// all the same) and 101 at eight.  us per step, fp16, 97 registers at two to seven heads / now, g = 128: 4 heads 28.1 / 27.9 at 8
+// units x 32k, 35.8 / 34.6 at 32 x 32k, 55.5 / 53.7 at 32 x 128k, 56.7 / 55.9 at 128 ragged units up to 30k; 6 heads 30.4 / 29.9,
+// 38.0 / 36.8 and 59.1 / 58.2 at the first, second and last; 7 heads 58.4 / 56.3 at 32 x 128k.
 template <int DT, int NREP, bool HIST, bool STREAM, bool LONG, class LAYERS>
 __global__ __launch_bounds__(256, HIST ? (!LONG ? 6 : NREP == 1 ? 5 : 4) : 1) void score_kernel(const uint4* kbits, const uint4* kmeta,
                                                     const float* __restrict__ kabsmax, const uint16_t* __restrict__ q,
@@ -342,7 +343,7 @@ hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits, const
                                   int group_size, const LayerBatch& lb, hipStream_t st) {
   const int gshift = group_size == 256 ? 3 : group_size == 128 ? 2 : group_size == 64 ? 1 : 0;
   // Blocks per wavefront.  The smallest that lets every workgroup be resident at once (256 CUs; the registers
-  // allow 6 workgroups per CU for the fused kernel, 5 at longer groups -- 4 with 7 or 8 query heads per kv head --, 8 for the
+  // allow 6 workgroups per CU for the fused kernel, 5 at longer groups -- 4 with 8 query heads per kv head --, 8 for the
   // score-only one), at least 4: prologue (q, R) and epilogue (histogram flush) are then paid once.  Beyond 12 the grid is cut into several rounds of shorter
   // workgroups instead: a workgroup's lifetime bounds the ragged end of the kernel, and in a batch of unequal
   // contexts (the host cannot see the lengths) the short units' workgroups exit at once and the dispatcher

@@ -67,6 +67,23 @@ def test_every_variant_of_the_gather_has_both_kinds_of_loads(objects):
                         assert f"18step_attend_kernelILi{dt}ELi{heads}ELi{ranges}ELb{stream}ENS_{layers}E" in names
 
 
+def test_registers_allow_the_workgroups_the_grids_are_sized_for(objects):
+    """The launchers cut the step's work into as many workgroups of four wavefronts as the 256 CUs hold at once: 512 registers
+    per SIMD lane, given out in eights, for one wavefront of each workgroup of the CU."""
+    seen = set()
+    for k in (k for o in objects for k in _kernels(o)):
+        want = None
+        if m := re.match(r"_ZN4fier12score_kernelILi(\d)ELi(\d)ELb1ELb\dELb(\d)ENS_", k[".name"]):
+            want = 6 if m[3] == "0" else 5 if int(m[2]) <= 7 else 4  # 32-token groups; longer ones
+        elif m := re.match(r"_ZN4fier18step_attend_kernelILi(\d)ELi(\d)E", k[".name"]):
+            want = 5 if int(m[2]) <= 2 else 4
+        if want:
+            fit = 512 // (-(-k[".vgpr_count"] // 8) * 8)
+            assert fit >= want, (k[".name"], k[".vgpr_count"])
+            seen.add((k[".name"][9:14], m[1], m[2]))
+    assert len(seen) == 2 * 2 * 8
+
+
 def _vgprs(operand):
     m = re.fullmatch(r"v(\d+)|v\[(\d+):(\d+)\]", operand)
     if not m:
