@@ -442,7 +442,14 @@ static int decode_step_impl(const fier_config* cfg, const fier_cache* layers, in
     // on the scores of phase 1.
     const int together = phase == 0 && !c->block_table ? fier::kMaxLayersPerLaunch : most;
     fier::LayerBatch lb = batch_of(cfg, c, dense_layers ? dense_layers + l : nullptr, std::min(together, n_layers - l), w.bytes);
-    const int unit_waves = phase > 3 ? 0 : fier::unit_form(units, lb.n, n_rep, max_budget, cfg->max_ctx);
+    // (More layers than the workspace has parts: as many as that form takes.)
+    int unit_layers = lb.n;
+    auto unit_form = [&] {
+      return phase > 3 ? 0 : fier::unit_form(units, unit_layers, n_rep, max_budget, cfg->max_ctx, idxl != nullptr);
+    };
+    int unit_waves = unit_form();
+    for (; !unit_waves && phase == 0 && unit_layers > most; unit_waves = unit_form()) --unit_layers;
+    lb.n = unit_layers;
     if (unit_waves && (phase == 0 || phase == 2)) {
       e = fier::launch_unit_step(unit_waves, cfg->kv_dtype, lay, n_rep, c->kbits, c->kmeta, c->kabsmax, ql, c->seq_lens, w.sb,
                                  budgets, max_budget, cfg->sm_scale, c->k, c->v, kn, vn, outl, idxl, cntl, cfg->batch,

@@ -177,7 +177,7 @@ bool step_two_kernel_form(int units, int n_rep, int max_budget, int max_ctx, boo
 // The whole step of a unit by one workgroup of nw wavefronts, for short contexts (unit_form: nw, or 0 where the others are
 // faster).  scored: phase 2 of it, on the scores and histograms that launch_score has left.  range_tokens: of a workgroup of
 // launch_step_emit_idx.
-int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx);
+int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx, bool with_index_list);
 hipError_t launch_unit_step(int nw, int dtype, KvLayout lay, int n_rep, const uint32_t* kbits, const uint32_t* kmeta,
                             float* kabsmax, const void* q, const int32_t* seq_lens, const StepBuffers& sb,
                             const int32_t* budgets, int max_budget, float sm_scale, void* K, void* V, const void* k_new,

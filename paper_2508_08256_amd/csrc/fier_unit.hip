@@ -557,15 +557,38 @@ FIER_UNIT_INSTANCE(extern, DT_BF16, 16)
 //   256, 4 heads  1k 22.8 / 14.0 / 13.4  4k 35.1 / 29.2 / 31.0   8k 52.1 / 45.5 / 51.8   16k 79.8 / 81.9 / 98.0
 //   512, 4 heads  1k 29.9 / 27.0 / 17.8  4k 54.9 / 55.8 / 43.6   8k 83.7 / 86.9 / 73.3
 //   16 layers of 64 ragged paged units up to 8k, 4 heads  126 / - / 93-95 per call of all 16
-// Hence up to 256 workgroups 16 wavefronts, to a number of tokens and rows that grows with the share of the GPU in use;
-// beyond, 8 wavefronts (two workgroups per CU), to 12000 tokens and rows, with one or two heads, whose two-kernel form has
-// more wavefronts per CU, and more workgroups than are resident to 8000.  Over 491 random shapes up to 16k tokens (1 to 17
-// layers, 4 to 6000 units, budgets of 4 to 50 %) 1.28 times as fast as two kernels everywhere, and at most 1.07 times as slow.
-int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx) {
+// Hence up to 256 workgroups 16 wavefronts, to a number of tokens and rows that grows with the share of the GPU in use; beyond, 8
+// wavefronts (two workgroups per CU), with three heads or more to 12000.
+//   One or two heads: the gather is on the vector units here, past 64 workgroups a row counts twice (25 % budgets: 128 units x 6.4k 37.8 / 43.7, 104 x
+// 5.2k 36.2 / 40.4), and the two-kernel form has five workgroups per CU, so that up to 1280 short units are one round of it where
+// this kernel needs two or three.  Of several layers it clears the parts first, so this kernel is worth more there.  Its time over
+// that of two kernels, equal contexts, mean / worst of 5 to 570 random shapes each:
+//   workgroups                 257-320    -384       -512       -640       -768      -1024      -1280      -1536      -2048      -3072
+//   one layer, to 4000         .77/0.99  .77/0.97   .76/0.92  1.03/1.24  1.02/1.16  1.03/1.24  1.14/1.44   .90/0.98  1.01/1.13  1.03/1.13
+//     4000 to 8000            1.03/1.12  .94/1.04   .88/1.00  1.13/1.29  1.09/1.18  1.03/1.07  1.07/1.14   .92/0.96  1.00/1.09
+//     8000 to 12000           1.15/1.22 1.04/1.12   .97/1.08
+//   several layers, to 4000    .65/0.85  .64/0.84   .63/0.88   .86/1.07   .85/1.04   .85/1.00   .97/1.23   .80/0.93   .89/1.03   .95/1.12
+//     4000 to 8000             .86/0.98  .81/0.93   .75/0.89   .99/1.14   .95/1.04   .91/1.02  1.00/1.13   .89/0.99   .96/1.05   .97/1.09
+//     8000 to 12000            .94/1.09  .89/1.03   .85/0.99
+// One layer therefore takes it up to 512 and from 1281 to 1536 workgroups, several up to 1024 and from 1281 to 2048, eight and more up
+// to 3072.  Calls that want the index list, another launch there, keep the larger limits (66 shapes past these .91, 1.12 at worst).
+//   Against the two kernels as they were before this kernel: three heads and more, 4900 random shapes that take it (1 to 8 layers, 1 to
+// 2000 units, budgets of 3 to 25 %) .54 to .71 of the time by their number of workgroups, 1 of them more than 1.07 (1.09); one and two
+// heads, 5800 shapes past 200 workgroups .785, 12 of them more than 1.07 (1.12 at worst; 283 and 1.32 with the larger limits for all).
+int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx, bool with_index_list) {
   if (max_ctx > kUnitMaxCtx) return 0;
-  const int64_t grid = (int64_t)units * layers, work = (int64_t)max_ctx + max_budget;
+  const int64_t grid = (int64_t)units * layers;
+  const int64_t work = n_rep <= 2 && grid > 64 ? (max_ctx + 2 * (int64_t)max_budget) * 10 / 11 : (int64_t)max_ctx + max_budget;
   const int nw = grid <= 256 ? 16 : 8;
-  const int64_t limit = grid <= 64 ? 5500 : grid <= 256 ? 5500 + (grid - 64) * 40 : grid <= 512 || n_rep >= 3 ? 12000 : 8000;
+  int64_t limit = 12000;
+  if (grid <= 64) limit = 5500;
+  else if (grid <= 256) limit = 5500 + (grid - 64) * 40;
+  else if (n_rep <= 2) {
+    const bool filled = grid <= 1024 ? layers > 1 : grid > 1280 && grid <= (layers > 1 ? 2048 : 1536);
+    if (with_index_list) limit = grid <= 512 ? 12000 : 8000;
+    else if (grid <= 512) limit = layers > 1 ? 8000 + (grid - 256) * 16 : 4000 + (grid - 256) * 31;
+    else limit = filled || (layers >= 8 && grid <= 3072) ? 8000 : 0;
+  }
   if (work > limit) return 0;
   return unit_lds(nw, n_rep, max_ctx, max_budget).bytes + kUnitFixedLds <= (nw == 16 ? 160u : 80u) * 1024u ? nw : 0;
 }

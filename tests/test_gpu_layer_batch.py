@@ -110,6 +110,31 @@ def test_layers_of_one_call_equal_single_layer_calls(case, parts):
             assert torch.equal(a[u, :n], b[u, :n])
 
 
+@pytest.mark.parametrize("batch,hq,hkv,layers", [(20, 8, 8, 17), (33, 16, 8, 9), (10, 32, 16, 12)])
+@pytest.mark.parametrize("parts,with_list", [(1, False), (3, False), (16, False), (1, True)])
+def test_forms_that_follow_each_other_in_a_call(batch, hq, hkv, layers, parts, with_list):
+    """Short contexts of one and two heads, where the number of units and of layers left decides on the form of every launch of a
+    call: 160 units x 17 layers is 16 + 1 layers, 12 + 5 in a workspace of one part; 264 x 9, 160 x 12: one launch of 7 + 2 or of
+    two kernels.  Selections, caches and the last layer's scores as layer by layer; at most 60 terms in the outputs' sums."""
+    lens = [100 - 3 * i % 97 for i in range(batch)]
+    dws = [RandomLayer(900 + l, batch, hq, hkv, lens, [60 - i for i in range(batch)], F16, 128, 0, 32) for l in range(layers)]
+    start, cfg, order, dense = [_state(d) for d in dws], dws[0].cfg, range(layers), [False] * layers
+    one = B.workspace_bytes(cfg, 60)
+    ref, ws = B.make_workspace(cfg, 60, 1), torch.full((one * parts,), 0x5A, dtype=torch.uint8, device="cuda")
+    ws[:one] = 0
+    want = _run(dws, order, dense, ref, with_list, True, True)
+    for d, s in zip(dws, start):
+        _restore(d, s)
+    got = _run(dws, order, dense, ws, with_list, True, False)
+    assert float((got[0] - want[0]).abs().max()) <= 60 * 5 * 2.0 ** -24
+    if with_list:
+        assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    assert all(torch.equal(x, y) for a, b in zip(got[3], want[3]) for x, y in zip(a, b))
+    a, b = (B.workspace_scores(cfg, 60, w) for w in (ws, ref))
+    assert all(torch.equal(a[u, :lens[u // hkv] + 1], b[u, :lens[u // hkv] + 1]) for u in range(cfg.units))
+    assert not ws[64 * cfg.units:(64 + 2048) * cfg.units].any()  # the histograms of the first part
+
+
 @pytest.mark.parametrize("ctx,max_ctx", [(700, 768), (6000, 6144)])
 def test_layers_of_overlapping_pools_run_in_order(ctx, max_ctx):
     """Two layers on the same blocks of one pool, reached through two base addresses a block apart: in a workspace of one part
