@@ -258,6 +258,7 @@ LARGE = [
     (5, 9, 3, (131000, 1.2), 4.58, F16, 131136, 0, 32, True, 6),      # 3 heads; the same with 17 workgroups per unit
     (16, 64, 8, (6000, 2), 11, BF16, 6016, 64, 32, True, 6),         # 8 heads, paged, 128 units: order 2, not resident at once
     (21, 15, 3, (5000, 2), 30, F16, 5056, 64, 64, True, 3),          # 5 heads, paged; 1 range
+    (1, 32, 8, (60000, 1), 11, BF16, 60032, 0, 32, True, 2),         # 4 heads; 2 ranges because one would make 59 workgroups per unit
 ]
 
 
