@@ -815,9 +815,9 @@ static long step_resident_wgs(int n_rep) { return 256L * step_wgs_per_cu(n_rep);
 //     four; 32 units x 16k (two ranges = one workgroup per CU): 25.8 / 27.4; 32 units x 64k, B = 7209: 50.9 with two
 //     ranges (225 rows), 51.5 with four; 64 units x 32k: 50.6 with two, 51.9 with four.
 //   * and twice as many, from four heads on, where a unit would have more than 40 workgroups -- what its merge folds at once -- and
-//     320 or more of at most 576 rows remain: few units of long contexts, one range / two: 7 units x 115k, 4 heads 90.6 / 73.7, 8 x
-//     124k, 7 heads 54.5 / 45.8, 8 x 100k, 4 heads 45.6 / 39.1.  Over 289 random shapes that it changes .941 of the time (237 with full
-//     sequences .921, 1.03 at worst; 52 in twice the capacity, of whose workgroups half have no token, 1.04 and 1.24).  (While three or
+//     288 or more of at most 576 rows remain: few units of long contexts, one range / two: 7 units x 115k, 4 heads 90.6 / 73.7, 8 x
+//     124k, 7 heads 54.5 / 45.8, 8 x 100k, 4 heads 45.6 / 39.1.  Over 3100 random shapes around it .97 of the
+//     time: full sequences .92 to .96, 1.10 at worst, twice the capacity, of whose workgroups half have no token, 1.02, 1.24 at worst.  (While three or
 //     two workgroups were resident at these heads, and not four, the second rule made most of these cuts.)
 int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
   const double per_range = 1024.0 * (double)max_budget / (double)max_ctx;
@@ -828,7 +828,7 @@ int step_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
   while (rpw < 8 && wgs(rpw) > step_resident_wgs(n_rep)) rpw *= 2;
   if (rpw < 8 && per_range * (2 * rpw) <= 288.0 && wgs(2 * rpw) >= 512) rpw *= 2;
   auto more_than_a_batch = [&](int r) { return (n_ranges + r - 1) / r > 40; };
-  while (n_rep >= 4 && rpw < 8 && more_than_a_batch(rpw) && per_range * (2 * rpw) <= 576.0 && wgs(2 * rpw) >= 320) rpw *= 2;
+  while (n_rep >= 4 && rpw < 8 && more_than_a_batch(rpw) && per_range * (2 * rpw) <= 576.0 && wgs(2 * rpw) >= 288) rpw *= 2;
   return rpw;
 }
 
