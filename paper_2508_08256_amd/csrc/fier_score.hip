@@ -362,10 +362,11 @@ hipError_t launch_score_dt(KvLayout lay, int n_rep, const uint32_t* kbits, const
   if (bpw > kScoreMaxBpw) return hipErrorInvalidValue;  // cannot happen: at most 12, + 1
   int n_x = (n_blocks + 4 * bpw - 1) / (4 * bpw);  // scoring workgroups per unit
   // Workgroups go round-robin to the eight XCDs: with n_x a multiple of four the same ranges of all units are on one or two of
-  // them, and of unequal contexts (or short ones in a large capacity) the ranges with tokens are few.  One more, empty workgroup per
-  // unit.  (Several layers: turned_wg.)  us per step: 54 sequences of up to 22k, 5 units each, n_x = 8, 66.0 / 58.9; 21 of up to 44k
-  // in 88k, 8 units, 4 heads, n_x = 16, 135.8 / 111.2; over 551 random ragged shapes with such n_x .99 (.75 to 1.04), equal ones 1.00.
-  if (lb.n == 1 && units > 1 && n_x % 4 == 0) ++n_x;
+  // them, and of unequal contexts the ranges with tokens are few.  Hence one more, empty workgroup per unit where there are several
+  // sequences.  (Several layers: turned_wg.)  us per step: 54 sequences of up to 22k, 5 units each, n_x = 8, 66.0 / 58.9; 21 of up to
+  // 44k in 88k, 8 units, 4 heads, n_x = 16, 135.8 / 111.2; over 551 random ragged shapes with such n_x .99 (.75 to 1.04), equal ones
+  // 1.00; the score-only launch of one sequence of 65k, 8 units, lost 0.9 of 38.4.
+  if (HIST && lb.n == 1 && units > n_kv_heads && n_x % 4 == 0) ++n_x;
   dim3 grid((unsigned)units * (unsigned)(n_x + (HIST ? 1 : 0)), 1, (unsigned)lb.n);
   // Streaming hint on the loads of the codes and their metadata (read once per step).  Measured with the step
   // rotating over 12 layer caches, this kernel alone, us without / with it: 32 units x 128k 34.4 / 30.6, 32 x 64k
