@@ -1,4 +1,5 @@
 """fier_decode_step over several layers: layers that share a launch give what single-layer calls give."""
+import ctypes as C
 from types import SimpleNamespace
 
 import numpy as np
@@ -72,13 +73,16 @@ CASES = [
 
 @pytest.mark.parametrize("case", CASES)
 @pytest.mark.parametrize("parts", [1, 2, 16])
-def test_layers_of_one_call_equal_single_layer_calls(case, parts):
+@pytest.mark.parametrize("capacity", [0, 9216], ids=["short", "long"])
+def test_layers_of_one_call_equal_single_layer_calls(case, parts, capacity):
     """Contexts cross group, pair-block and range edges; the workspace holds one, two or 16 layers, and what lies
     behind its first part is garbage.  Appended rows, packed caches and (with the list) selections must be the same,
     outputs too up to the order of summation: at most 700 terms in binary32, |error| <= 700 * 2^-24 * max|v| (about
-    4.5) < 2e-4, far above what is seen."""
+    4.5) < 2e-4, far above what is seen.
+    The case's own capacity is short enough for the kernel that does a unit's whole step, which needs one part; the same
+    contexts in a capacity of 9216 take the two-kernel form, whose layers have a part each."""
     batch, hq, hkv, lens, buds, dtype, max_ctx, bt, group, with_list, append, order, dense_at = case
-    order = list(order)
+    order, max_ctx = list(order), capacity or max_ctx
     dws = _layers(700, max(order) + 1, batch, hq, hkv, lens, buds, dtype, max_ctx, bt, group)
     dense = [l in dense_at for l in range(len(order))]
     cfg, mb = dws[0].cfg, max_ctx if dense_at else int(dws[0].wl.budgets.max())
@@ -98,6 +102,11 @@ def test_layers_of_one_call_equal_single_layer_calls(case, parts):
     for a, b in zip(got[3], want[3]):
         for x, y in zip(a, b):
             assert torch.equal(x, y)
+    # the two-kernel form hands the bounds of the appended groups over behind the scores of the first part
+    end = int(B.lib().fier_workspace_scores_offset(C.byref(cfg), int(dws[0].wl.budgets.max()))) + 4 * cfg.units * max_ctx
+    bounds = ws[-(-end // 256) * 256:][:512 * cfg.units].view(torch.float32)
+    if append and not dense_at and max(lens) < max_ctx:
+        assert bool((bounds > 0).any()) == (capacity > 0 or case is CASES[3])
     # the scores the workspace shows are those of the call's last layer
     if not dense_at:
         ref = B.make_workspace(cfg, mb, 1)
