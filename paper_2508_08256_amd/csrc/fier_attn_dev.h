@@ -133,8 +133,9 @@ constexpr int kPartialFloats = 4 * 16 * 10 + 10;
 //     of the V rows of tokens 4kq .. 4kq + 3 (a row is 16 lanes, 256 contiguous bytes); the four tokens of one of its
 //     channels, two byte permutations, are the lane's A operand of the product over channels 8m + c, m = 0..15.
 // So nothing crosses lanes but the maximum over the four lane rows, and each lane keeps 32 of its column's 128 outputs.
-// The probabilities stay exact to 24 bits: p = hi + mid + lo, each an operand of its own in the V type (8 bits each for
-// bf16; fp16, p scaled by 2^15: 11 each).  The 16 columns have room for them: column n is part n / kCols of head n % kCols,
+// The probabilities are three operands in the V type, p = hi + mid + lo: with bf16 (8 bits each) all 24 bits of p; with fp16 (11 each,
+// p scaled by 2^15) all of them down to 2^-16 of the wavefront's running maximum, below that to the format's last place, an error of
+// at most 2^-39 of the maximum per row (2^-38 from six heads on).  The 16 columns have room for the parts: column n is part n / kCols of head n % kCols,
 // kCols = NREP up to five heads; from six on hi and mid take the columns and lo, half of it each, a second product into the
 // same sums.
 //   Before, P.V ran on the vector ALUs, 32 V elements and 32 x 4 multiply-adds of each lane per tile and head group behind an

@@ -54,3 +54,27 @@ def test_gather_at_tile_edges(n_rep, dtype):
         want = _exact(cfg, k, v, q, rows)
         rel = ((out.double() - want).flatten(1).norm(dim=1) / want.flatten(1).norm(dim=1)).cpu().numpy()
         assert rel.max() <= 2e-6, (n_rep, COUNTS[int(rel.argmax())], rel)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("n_rep", [3, 5, 6, 8])
+def test_weights_far_below_the_largest(n_rep, dtype):
+    """A row of weight 1 with V = 0 and 63 rows of weights 2^-1 .. 2^-45 (q k = the base-2 logit): all that comes out is theirs.
+    bf16: their binary32 values, the scale's rounding times 45.  fp16: to 2^-39 of the largest weight per row, 2^-38 from six heads on."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_rep)
+    cfg = B.make_config(45, n_rep, 1, 64, B.F16 if dtype == torch.float16 else B.BF16)
+    cfg.sm_scale = 0.6931471805599453
+    k, q = (torch.zeros(s, dtype=dtype, device="cuda") for s in ((45, 64, D), (45, n_rep, D)))
+    q[:, :, 0] = 1
+    k[:, 1:, 0] = -torch.arange(1, 46, device="cuda", dtype=dtype)[:, None]
+    v = torch.randn((45, 64, D), generator=gen, device="cuda").to(dtype)
+    v[:, 0] = 0
+    lens = torch.full((45,), 64, dtype=torch.int32, device="cuda")
+    out = torch.empty(q.shape, dtype=torch.float32, device="cuda")
+    B.dense_attn(cfg, B.DeviceCache(cfg, k, v, lens), q, 0, out, B.make_workspace(cfg, 64, 1))
+    p = torch.softmax(k[:, :, 0].double() * float(cfg.sm_scale), -1)
+    want, size = ((p[:, :, None] * x.double()).sum(1)[:, None] for x in (v, v.abs()))
+    part = (2.0 ** -39 if n_rep <= 5 else 2.0 ** -38) if dtype == torch.float16 else 0.0
+    bound = 1e-5 * size + 63 * part * v.abs().double().amax(1)[:, None]
+    assert bool(((out.double() - want).abs() <= bound).all())
