@@ -408,6 +408,7 @@ def measure(args, workload, budget_arg, detail):
               "context": L if w["L"] != "ragged" else [int(x) for x in lens],
               "budget": budget if w["budget"] != "11%" else [int(x) for x in buds],
               "group_size": args.group_size, "layers_per_step": NL, "rotating_caches": R * NL,
+              # of the form without the one launch of short contexts (config 1), which the phases timed above take apart
               "kernels_per_layer_step": n_kernels,
               "kernels_per_layer_step_with_index_list": B.decode_step_kernels(cfg, budget, True),
               "algorithmic_bytes_per_layer": ab["total"]}

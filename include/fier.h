@@ -178,7 +178,8 @@ int fier_topk_ws(const fier_config *cfg, const float *scores, const int32_t *seq
 
 /*
  * Alg. 1 step 4.  For every query head: p = softmax(sm_scale * q . K[S]^T), out = p V[S], with
- * S = idx[u][0 .. count[u]) (rows of this unit's cache, any order; an entry outside [0, max_ctx) is skipped).  Inputs are
+ * S = idx[u][0 .. count[u]) (rows of this unit's cache, any order; an entry outside [0, max_ctx) is skipped).  idx has max_budget
+ * entries for every unit; those past count[u] may be loaded but are never used.  Inputs are
  * read in the K dtype, logits, softmax and the output are binary32.  out is
  * [batch][n_q_heads][D] float, device.  count[u] == 0 gives zeros.
  */
@@ -241,12 +242,14 @@ int fier_decode_step_mixed(const fier_config *cfg, const fier_cache *layers, int
 /*
  * One kernel of fier_decode_step alone, for measurement and tests.  After the first kernel (phase 1: append + score +
  * score histogram) the step takes one of two forms, chosen from cfg, max_budget and whether idx_out is given;
- * fier_decode_step_kernels returns the number of kernels of the form a call gets (not counting the optional
- * index-list kernel; with_index_list != 0: a call with idx_out), 0 for an invalid configuration.  (That is for a layer
- * with launches of its own: layers that share theirs always take the two-kernel form.)
- * At short contexts (with few units to about 5000 tokens and rows, with more to at most 12000) fier_decode_step does the
- * same in one launch, a workgroup per unit; phase 2 is then that kernel on the scores of phase 1, the other phases and the
- * count of the kernels are those of the two-kernel form.
+ * fier_decode_step_kernels returns the number of kernels of that form (not counting the optional index-list kernel;
+ * with_index_list != 0: a call with idx_out), 0 for an invalid configuration.  (That is for a layer with launches of its
+ * own: layers that share theirs take the two-kernel form.)
+ * At short contexts fier_decode_step does all of it in ONE launch of one or several layers, a workgroup per unit: up to 5500 tokens
+ * and rows (max_ctx + max_budget) with at most 64 units in the launch, up to 5500 + 40 for each unit past 64 with at most 256, up to
+ * 12000 with more; with one or two query heads per kv head and more than 64 units to fewer.  fier_decode_step_kernels does not tell:
+ * it returns the count of the form without that limit.  Phase 2 of such a call is that one kernel on the scores of phase 1; phases 1 and 3
+ * are those of the two-kernel form.
  *   2 kernels, with one or two query heads per kv head; with more of them if idx_out is null and the second kernel
  *     has at most twice the workgroups the GPU holds at once: phase 2 = exact threshold + attention over the selected
  *     rows + merge in one launch; phase 3 = the ascending index list (launched by the step only if idx_out is given;
@@ -254,8 +257,9 @@ int fier_decode_step_mixed(const fier_config *cfg, const fier_cache *layers, int
  *   3 kernels otherwise: phase 2 = exact threshold, phase 3 = selection + attention + merge, which also writes
  *     idx_out (may be repeated).
  * Same arguments as fier_decode_step.  Phase p works on what phases 1..p-1 of the latest step on this workspace and
- * these layers left behind, so the sequence 1, 2, 3 equals fier_decode_step (of several layers: if they all share one
- * launch).  Phase 1 adds its scores to the workspace's histograms and phase 2 consumes and clears them: phase 1 may be repeated for timing (follow it with one
+ * these layers left behind, so the sequence 1, 2, 3 equals fier_decode_step -- of several layers if the workspace has a part for
+ * each of them and they share their launches: with fewer parts a phase runs them in groups, or one by one, on the same parts, and
+ * what a later layer's phase 1 leaves there replaces an earlier one's.  Phase 1 adds its scores to the workspace's histograms and phase 2 consumes and clears them: phase 1 may be repeated for timing (follow it with one
  * phase 2 before the next real step), phase 2 only after a phase 1.  Phases 2 + 16 f and 3 + 16 f, f = 1..3, are for
  * tests: the two-kernel form whatever the shape, its second kernel with flags f (1: no workgroup picks up the
  * threshold itself, the merging workgroup attends over all threshold-bin rows; 2: checksums of the attended rows in

@@ -198,9 +198,9 @@ def workspace_scores(cfg: Config, max_budget: int, workspace):
 
 
 def decode_step_kernels(cfg: Config, max_budget: int, with_index_list: bool = False) -> int:
-    """2 or 3: the number of kernels fier_decode_step launches per layer for this shape, without or with idx_out
-    (the optional index-list kernel of the two-kernel form not counted); layers that share their launches always take
-    two.  At short contexts the two are one launch, see fier.h."""
+    """2 or 3: the number of kernels of the form that fier_decode_step takes per layer for this shape, without or with idx_out
+    (the optional index-list kernel of the two-kernel form not counted).  Layers that share their launches take two; at
+    short contexts, whatever this returns, a call is one launch (fier.h has the limits)."""
     return int(lib().fier_decode_step_kernels(C.byref(cfg), int(max_budget), 1 if with_index_list else 0))
 
 

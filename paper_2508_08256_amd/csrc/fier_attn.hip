@@ -326,11 +326,11 @@ static hipError_t launch_select_attend_dt(KvLayout lay, int n_rep, const StepBuf
 
 // Ranges per workgroup (rows per 1024-token range = 1024 * budget / context): at least 96 selected rows per workgroup,
 // and twice that -- up to 288 rows -- where the grid is far beyond what the chip holds at once (more than two rounds)
-// or a unit has more than 64 workgroups (its merge then reads that many partials).  Measured (us per step; 32 query
-// / 8 kv heads): batch 16 x 16k at 11 % 67.2 -> 61.1, batch 8 x 64k 110.8 -> 105.4, the ragged 16-sequence batch
-// 63.7 -> 61.8 (this kernel), batch 1 x 128k at 11 % 48.3 -> 46.0 with twice the ranges; but batch 1 x 32k 28.0 ->
-// 30.6, batch 2 x 32k (24 query heads) 32.2 -> 34.0, batch 4 x 32k 41.7 -> 42.5, and the 4 x 128k shape at B = 4096
-// 26.8 -> 29.4 (this kernel) -- grids of about one round -- lose by it, as does halving (64 rows: 34.4).
+// or a unit has more than 64 workgroups (its merge then reads that many partials).  us per step with the index list, 11 % unless
+// noted, half as many ranges (at least one) / these / twice as many; 4 heads: 8 units x 32k 27.2 / 27.1 / 29.1, 16 x 32k 31.1 / 31.2 /
+// 32.5, 32 x 32k 38.2 / 38.2 / 38.3, 128 x 16k 61.1 / 61.1 / 58.9, 64 x 64k 101.7 / 95.5 / 93.3, 8 x 128k 45.4 / 42.5 / 43.9, 32 x 128k (3 %)
+// 66.7 / 62.4 / 64.8, 128 ragged units of 8k..64k 111.5 / 106.9 / 110.2; 8 heads: 29.9 / 30.1 / 32.2, 34.2 / 34.2 / 35.3, 41.1 / 41.1 / 41.4,
+// 67.2 / 67.5 / 63.2, 115.2 / 99.4 / 97.1, 53.5 / 47.5 / 47.4, 72.2 / 66.4 / 68.8, 122.9 / 116.7 / 118.2.
 int select_attend_ranges_per_wg(int units, int n_rep, int max_budget, int max_ctx) {
   const double per_range = 1024.0 * (double)max_budget / (double)max_ctx;
   const int n_ranges = (max_ctx + kRangeTokens - 1) / kRangeTokens;

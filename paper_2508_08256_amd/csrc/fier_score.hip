@@ -20,9 +20,10 @@ constexpr int kScoreMaxBpw = 13;  // pair blocks per wavefront at most (the laun
 // scoring and histogramming are one pass.  The workgroup's LDS histogram is added to the unit's histogram in
 // memory with device atomics and the workgroup is done: nobody waits or counts arrivals here; the threshold
 // kernel reads the merged histogram (and clears it for the next call).
-// The extra workgroup of a unit performs the decode-stage append (Sec. 3.1) when k_new is given: one wavefront (four
-// for groups longer than 32 tokens) writes the new K/V rows, re-quantizes the group the row falls in and scores that
-// group's tokens straight from its registers; the other workgroups leave those tokens alone.  The bound R uses the absmax of before the
+// The extra workgroup of a unit performs the decode-stage append (Sec. 3.1) when k_new is given: its four wavefronts share the
+// tokens of the group the new row falls in (eight each of 32-token groups, 32 and up to twice 32 of longer ones), exchange their minima
+// and maxima through lscore across a barrier that all four reach, and re-quantize and score their tokens straight from registers; wavefront
+// 0 writes the new K/V rows and the group's (s, z).  The other workgroups leave those tokens alone.  The bound R uses the absmax of before the
 // append (every workgroup must bin with the same R); the new group's contribution is handed to the last kernel
 // of the step through `newmax`.  A score outside [-R, R] simply lands in the outermost bin.
 // LONG: quantization groups longer than 32 tokens.  (Separate variants: the long groups' append takes more registers, and
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(256, HIST ? (!LONG ? 6 : NREP == 1 ? 5 : 4) : 1) vo
   const int lane = tid & 63;
   const int wave = tid >> 6;
   // Workgroups are dispatched in the order of their index.  HIST: the first `units` workgroups are the appending
-  // ones (their single wavefront has the longest chain of dependent loads: started last, it would end the kernel
+  // ones (theirs is the longest chain of dependent loads: started last, they would end the kernel
   // late), then n_x scoring workgroups per unit, a unit's ranges next to each other.
   const int n_units = (int)gridDim.x / (n_x + (HIST ? 1 : 0));
   const bool append_wg = HIST && __builtin_expect((int)blockIdx.x < n_units, 0);  // its code out of the others' way
@@ -88,8 +89,8 @@ __global__ __launch_bounds__(256, HIST ? (!LONG ? 6 : NREP == 1 ? 5 : 4) : 1) vo
     }
   }
   const uint16_t* qb = q + (size_t)unit * NREP * kD;
-  // The appending wavefront's chain of dependent loads is the longest in the kernel: what it needs and what does
-  // not depend on the sequence length (the new rows, its lanes' query values) leaves before anything else.
+  // The appending wavefronts' chain of dependent loads is the longest in the kernel: what it needs and what does
+  // not depend on the sequence length (the new rows, their lanes' query values) leaves before anything else.
   uint32_t kn = 0, vn = 0, qpair[NREP];
 #pragma unroll
   for (int r = 0; r < NREP; ++r) qpair[r] = 0;
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(256, HIST ? (!LONG ? 6 : NREP == 1 ? 5 : 4) : 1) vo
   L = L > max_ctx ? max_ctx : L;
   const int gshift = LONG ? group_shift : 0;
   const int gsize = kG << gshift;  // tokens per quantization group: 32, 64, 128 or 256
-  const int tail_start = app ? (Lold / gsize) * gsize : L;  // tokens from here on are scored by the appending wave
+  const int tail_start = app ? (Lold / gsize) * gsize : L;  // tokens from here on are scored by the appending workgroup
   if (__builtin_expect(append_wg, 0)) {
     if (!app) return;
   } else {

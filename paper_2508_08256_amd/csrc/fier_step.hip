@@ -889,8 +889,11 @@ static bool fill_step_args(StepArgs& a, int rpw, int order, KvLayout lay, const 
   a.wgs_per_unit = n_wgs;
   a.cand_pitch = sb.cand_pitch;
   a.flags = flags;
-  // Beyond the resident grid the last workgroups to start end the launch: those of the longest sequences start first (16
-  // sequences of 8k..64k, 128 units, this kernel: one layer 78.3 -> 66.9 us, three layers 174.5 / 176.2).
+  // Beyond the resident grid the last workgroups to start end the launch: those of the longest sequences start first.  us per step
+  // without / with it, 16 sequences of 8k..64k, 128 units: one layer of 4 heads 101.8 / 95.2, of 8 heads 108.4 / 101.1; given in
+  // the order of their lengths already 92.4 / 94.8 and 98.3 / 100.3 (the ranking at every workgroup's start); 2, 3 and 4 (3 + 1)
+  // layers, 4 heads, 181.5 / 182.0, 261.9 / 263.5, 369.0 / 363.3.  Random ragged shapes: of 4280 with launches of their own 59 gain
+  // more than 3 % and 36 lose as much, of 2357 that share them 51 and 21.
   a.by_length = order != 1 && units > n_kv_heads && units / n_kv_heads <= 64;
   a.lay = lay;
   return (size_t)n_wgs * (rpw * kRangeTokens / 4) <= sb.cand_pitch && n_wgs <= sb.seg_pitch;
@@ -997,18 +1000,19 @@ hipError_t launch_step_attend(int dtype, KvLayout lay, int n_rep, const StepBuff
 
 // Whether the step's second part is one launch (step_attend_kernel) for this shape.
 bool step_two_kernel_form(int units, int n_rep, int max_budget, int max_ctx, bool with_index_list) {
-  // Measured against the threshold kernel + selection-and-attention kernel (us per step, fp16, budget = 11 % of the
-  // context unless noted): with 4 query heads per kv head, 8 units x 32k 25.8 / 28.5, 64 x 32k 57.0 / 62.0, 128 x 32k
-  // 95.7 / 108.8, 32 x 128k (budget 4096) 65.7 / 71.5, and on grids that are not resident at once 64 x 128k 121.2 /
-  // 118.0, 256 x 32k 194.2 / 191.9; with one query head per kv head on such grids 256 x 128k 391 / 425, 2048 x 4k
-  // 194 / 215, 1024 x 32k 664 / 698, 512 x 32k 341 / 348, 1024 x 8k 214 / 206.
-  //   On the ragged batch of 128 such units x 8k..64k (budget 11 % of each length), whose grid at full length is 1.5
-  //   times the resident one: 107 / 117.  Hence: always with 1 or 2 query heads per kv head; with more, up to twice
-  //   the resident grid.
-  //   With the ascending index list as an output the one-launch form needs one more kernel, which reads the scores
-  //   again (config 2 +4.3 us, 32 units x 128k +10), while the selection + attention kernel writes the list as it
-  //   selects: 32 x 128k at 4 heads per kv head 73.4 / 68.5, the ragged batch 115.3 / 108.7, 8 x 32k 29.3 / 28.5, but
-  //   config 2 37.5 / 41.2.  Hence: with the list and 3 or more heads per kv head, three kernels.
+  // us per step, fp16, budget = 11 % of the context unless noted, this form / the threshold kernel + selection-and-attention kernel,
+  // one layer.  Up to twice the resident grid: 4 heads 64 units x 32k 47.5 / 56.6, 128 x 32k 79.3 / 89.7, 256 x 32k 151.8 / 174.3, 32 x
+  // 128k (3 %) 56.9 / 64.7, 64 x 128k (3 %) 96.3 / 111.1, 512 x 8k (25 %) 136.2 / 136.5, 128 ragged units of 8k..64k 96.4 / 106.3; 8 heads,
+  // the same shapes, 51.0 / 60.3, 83.3 / 94.4, 155.8 / 184.2, 60.1 / 70.1, 98.6 / 113.9, 138.0 / 138.2, 103.8 / 114.6; 3 and 5 to 7 heads
+  // between them.  (While the gather of three heads and more held three or two workgroups per CU, the line was at those.)
+  //   With the ascending index list as an output this form needs one more kernel, which reads the scores again, while the
+  // selection + attention kernel writes the list as it selects: 1 head 32 x 32k 36.5 / 36.9, 128 x 32k 86.4 / 97.3, 32 x 128k (3 %) 64.3 /
+  // 60.6, ragged 108.9 / 112.4; 4 heads 8 x 32k 26.7 / 27.1, 32 x 32k 36.3 / 38.2, 128 x 16k 55.2 / 61.1, 8 x 128k 46.7 / 42.5, 32 x 128k (3
+  // %) 65.3 / 62.4, ragged 107.1 / 106.9; 8 heads 29.8 / 30.1, 39.5 / 41.1, 60.4 / 67.5, 51.2 / 47.5, 68.1 / 66.4, 115.5 / 116.7.
+  //   Hence: always with 1 or 2 query heads per kv head; with more, without the list and up to twice the resident grid.  Both limits for
+  // three heads and more are from that slower gather, when the other form was ahead past them.  Now this one is with the list and many
+  // units, as above, and beyond the grid (4 heads 256 x 128k 612 / 658, 1024 x 32k 582 / 661, 512 x 64k 582 / 644; 8 heads 612 / 680, 607 /
+  // 688, 604 / 678) ahead and could take these calls; either way they are as fast as or faster than with that gather.
   if (n_rep <= 2) return true;
   if (with_index_list) return false;
   const int rpw = step_ranges_per_wg(units, n_rep, max_budget, max_ctx);
