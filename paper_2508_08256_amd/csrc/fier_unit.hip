@@ -570,11 +570,13 @@ FIER_UNIT_INSTANCE(extern, DT_BF16, 16)
 //   several layers, to 4000    .65/0.85  .64/0.84   .63/0.88   .86/1.07   .85/1.04   .85/1.00   .97/1.23   .80/0.93   .89/1.03   .95/1.12
 //     4000 to 8000             .86/0.98  .81/0.93   .75/0.89   .99/1.14   .95/1.04   .91/1.02  1.00/1.13   .89/0.99   .96/1.05   .97/1.09
 //     8000 to 12000            .94/1.09  .89/1.03   .85/0.99
-// One layer therefore takes it up to 512 and from 1281 to 1536 workgroups, several up to 1024 and from 1281 to 2048, eight and more up
-// to 3072.  Calls that want the index list, another launch there, keep the larger limits (66 shapes past these .91, 1.12 at worst).
+// One layer therefore takes it up to 512 and from 1281 to 1536 workgroups, several up to 1024 and from 1281 to 2048, four and more up
+// to 3072 (at 1025 to 1280 and 2049 to 3072, 6039 shapes of 4 / 8 / 16 layers: .92 / .91 / .90, 50 of them more than 1.07, 1.14 at
+// worst, half of those 50 with contexts below 300; 184 of 2 / 3 layers: .97 / .95).  Calls that want the index list, another launch
+// there, keep the larger limits (66 shapes past these .91, 1.12 at worst).
 //   Against the two kernels as they were before this kernel: three heads and more, 4900 random shapes that take it (1 to 8 layers, 1 to
 // 2000 units, budgets of 3 to 25 %) .54 to .71 of the time by their number of workgroups, 1 of them more than 1.07 (1.09); one and two
-// heads, 5800 shapes past 200 workgroups .785, 12 of them more than 1.07 (1.12 at worst; 283 and 1.32 with the larger limits for all).
+// heads, 5800 shapes past 200 workgroups .785, 14 of them more than 1.07 (1.12 at worst; 283 and 1.32 with the larger limits for all).
 int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx, bool with_index_list) {
   if (max_ctx > kUnitMaxCtx) return 0;
   const int64_t grid = (int64_t)units * layers;
@@ -587,7 +589,7 @@ int unit_form(int units, int layers, int n_rep, int max_budget, int max_ctx, boo
     const bool filled = grid <= 1024 ? layers > 1 : grid > 1280 && grid <= (layers > 1 ? 2048 : 1536);
     if (with_index_list) limit = grid <= 512 ? 12000 : 8000;
     else if (grid <= 512) limit = layers > 1 ? 8000 + (grid - 256) * 16 : 4000 + (grid - 256) * 31;
-    else limit = filled || (layers >= 8 && grid <= 3072) ? 8000 : 0;
+    else limit = filled || (layers >= 4 && grid <= 3072) ? 8000 : 0;
   }
   if (work > limit) return 0;
   return unit_lds(nw, n_rep, max_ctx, max_budget).bytes + kUnitFixedLds <= (nw == 16 ? 160u : 80u) * 1024u ? nw : 0;
